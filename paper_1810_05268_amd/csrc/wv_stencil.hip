@@ -72,7 +72,12 @@ __device__ __forceinline__ void ntstore4(float *p, float a, float b, float c, fl
 //   * interior LDS values come from the queue, so HBM is read once per value
 //     (plus the 2K-plane warm-up of each z chunk); halos are lines the neighbouring
 //     tiles of the same XCD read as their interior.
-// VEC: nx % 4 == 0, every float4 of a row is either inside or outside the grid.
+// Rows are pitched to a multiple of four and their pad columns hold zeros, so every field
+// access is an aligned float4 at any nx.  WHOLE: nx % 4 == 0, no float4 reaches past nx;
+// otherwise the last lane of a row stores zeros to its pad columns, and the dense binary64
+// gradient is accessed one value at a time.  (Scalar field accesses for such rows took
+// 32.9 us for a forward step of a 183 x 139 x 125 grid at order 8, 49.8 us for an adjoint
+// step that updates the gradient.)
 // `prev` (u^{n-1}) and `fout` (u^{n+1}) may be the same array: each point of it is
 // read and then written by the same lane only.
 //
@@ -91,7 +96,7 @@ __device__ __forceinline__ void ntstore4(float *p, float a, float b, float c, fl
 //   kGCarryOut: cr = t rounded to binary32, G untouched;
 //   kGCarryIn:  G += gscale (t + cr), cr from the kGCarryOut step before.
 // A pair of adjoint steps thus reads and writes the binary64 gradient once.
-template <int K, int GM, bool VEC, int MODE>
+template <int K, int GM, bool WHOLE, int MODE>
 __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *__restrict__ fin,
                                                  const float *prev, float *fout, const float *__restrict__ w,
                                                  const float *__restrict__ uk, const float *__restrict__ xtra,
@@ -112,8 +117,8 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     constexpr int NH = NHX + 2 * K * (TX / 4);    // all halo float4s per plane (<= 256)
     static_assert(NH <= 256, "one halo float4 per lane at most");
     // planes between a stage's loads and its use: two where three stages fit in 256
-    // registers without spilling (no gradient, aligned rows, not the OT4 update)
-    constexpr int AHEAD = (!GRAD && VEC && MODE != kOT4) ? 2 : 1;
+    // registers without spilling (no gradient, not the OT4 update)
+    constexpr int AHEAD = (!GRAD && MODE != kOT4) ? 2 : 1;
     __shared__ __align__(16) float tile[2][LY][LX];
 
     const int nwg = tiles_x * tiles_y * zchunks;
@@ -127,6 +132,7 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     const int tid = threadIdx.x;
     const int tx4 = tid & 7, ty = tid >> 3;
     const int nx = g.nx, ny = g.ny, nz = g.nz, px = g.px;
+    const int nxl = (nx - 1) & ~3;                // first column of a row's last float4
     const long long sxy = (long long)px * ny;     // pitched field plane
     const int x0 = tix * TX + 4 * tx4;
     const int y = tiy * TY + ty;
@@ -163,22 +169,13 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
         const bool in = ok && z >= 0 && z < nz && yy >= 0 && yy < ny;
         const int zc = min(max(z, 0), nz - 1), yc = min(max(yy, 0), ny - 1);
         const float *row = base + (long long)zc * sxy + (long long)yc * px;
+        const bool inx = in && gx >= 0 && gx < nx;
+        const float4 t = *reinterpret_cast<const float4 *>(row + min(max(gx, 0), nxl));
         float4 v;
-        if constexpr (VEC) {
-            const bool inx = in && gx >= 0 && gx < nx;
-            const float4 t = *reinterpret_cast<const float4 *>(row + min(max(gx, 0), nx - 4));
-            v.x = inx ? t.x : 0.0f;
-            v.y = inx ? t.y : 0.0f;
-            v.z = inx ? t.z : 0.0f;
-            v.w = inx ? t.w : 0.0f;
-        } else {
-            const float t0 = row[min(max(gx + 0, 0), nx - 1)], t1 = row[min(max(gx + 1, 0), nx - 1)];
-            const float t2 = row[min(max(gx + 2, 0), nx - 1)], t3 = row[min(max(gx + 3, 0), nx - 1)];
-            v.x = (in && gx + 0 >= 0 && gx + 0 < nx) ? t0 : 0.0f;
-            v.y = (in && gx + 1 >= 0 && gx + 1 < nx) ? t1 : 0.0f;
-            v.z = (in && gx + 2 >= 0 && gx + 2 < nx) ? t2 : 0.0f;
-            v.w = (in && gx + 3 >= 0 && gx + 3 < nx) ? t3 : 0.0f;
-        }
+        v.x = inx ? t.x : 0.0f;
+        v.y = inx ? t.y : 0.0f;
+        v.z = inx ? t.z : 0.0f;
+        v.w = inx ? t.w : 0.0f;
         return v;
     };
 
@@ -193,9 +190,7 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     auto load4p = [&](const float *base, int z, int gx) -> float4 {
         const int zc = min(z, nz - 1), yc = min(y, ny - 1);
         const float *row = base + (long long)zc * sxy + (long long)yc * px;
-        if constexpr (VEC) return ntload4(row + min(gx, nx - 4));
-        return make_float4(row[min(gx + 0, nx - 1)], row[min(gx + 1, nx - 1)], row[min(gx + 2, nx - 1)],
-                           row[min(gx + 3, nx - 1)]);
+        return ntload4(row + min(gx, nxl));
     };
     auto fill = [&](Stage &S, int z) {
         if constexpr (MODE != kLapW) S.p = load4p(prev, z, x0);
@@ -205,7 +200,7 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
         if constexpr (GM == kGCarryIn) S.t = load4p(cr, z, x0);
         if constexpr (GRW) {
             const long long pg = ((long long)min(z, nz - 1) * ny + min(y, ny - 1)) * nx;   // dense
-            if constexpr (VEC) {
+            if constexpr (WHOLE) {
                 // two 16-byte loads per lane, normally cached: the line a lane pair shares
                 // stays in L2 between them
                 const double2 g0 = *reinterpret_cast<const double2 *>(&G[pg + min(x0, nx - 4)]);
@@ -334,24 +329,16 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
         if (ptin) {
             const long long p0 = (long long)z * sxy + rowoff + x0;
             const long long p0g = ((long long)z * ny + y) * nx + x0;   // dense gradient
-            if constexpr (VEC) {
-                ntstore4(fout + p0, on[0], on[1], on[2], on[3]);
-            } else {
+            if constexpr (!WHOLE) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (x0 + i < nx) fout[p0 + i] = on[i];
+                for (int i = 1; i < 4; ++i) on[i] = x0 + i < nx ? on[i] : 0.0f;   // pad columns stay zero
             }
+            ntstore4(fout + p0, on[0], on[1], on[2], on[3]);
             if constexpr (GM == kGCarryOut) {
                 float t[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) t[i] = uin[i] * wl[i];
-                if constexpr (VEC) {
-                    ntstore4(cr + p0, t[0], t[1], t[2], t[3]);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (x0 + i < nx) cr[p0 + i] = t[i];
-                }
+                ntstore4(cr + p0, t[0], t[1], t[2], t[3]);
             }
             if constexpr (GRW) {
                 const float tin[4] = {S.t.x, S.t.y, S.t.z, S.t.w};
@@ -366,7 +353,7 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
                     else
                         gn[i] = gold[i] + gscale * (double)uin[i] * (double)wl[i];
                 }
-                if constexpr (VEC) {
+                if constexpr (WHOLE) {
                     *reinterpret_cast<double2 *>(&G[p0g]) = make_double2(gn[0], gn[1]);
                     *reinterpret_cast<double2 *>(&G[p0g + 2]) = make_double2(gn[2], gn[3]);
                 } else {
@@ -674,12 +661,12 @@ void launch_timed(Kern kern, dim3 grid, hipStream_t s, LaunchEvents ev, Args... 
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, args...);
 }
 
-template <int K, int GM, bool VEC, int MODE>
+template <int K, int GM, bool WHOLE, int MODE>
 hipError_t launch3d(const Grid &g, const float *fin, const float *prev, float *fout, const float *w,
                     const float *uk, const float *xtra, const float *xtra2, double *G, float *cr, double gscale,
                     hipStream_t s, LaunchEvents ev)
 {
-    auto kern = stencil3d<K, GM, VEC, MODE>;
+    auto kern = stencil3d<K, GM, WHOLE, MODE>;
     const int tiles_x = (g.nx + 31) / 32, tiles_y = (g.ny + 31) / 32;
     // one resident round of workgroups: z chunks as long as possible (the 2K-plane
     // warm-up of each chunk re-reads the field), but enough of them to fill the GPU
