@@ -306,7 +306,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct Layout {
     size_t bk, U0, U1, L0, L1, W, Z, UB, DB, V, VU, CR;
-    size_t src_tab, rec_tab, tab_bytes;
+    size_t src_tab, rec_tab, tab_bytes, src_plane, src_pos, rec_plane, rec_pos;
     size_t res, dsim, partials, enc, offs, sizes, arena;
     size_t total;
     size_t arena_bytes;
@@ -325,6 +325,9 @@ struct Setup {
     long long Pf = 0;       // elements of one solver field array (rows pitched, see Grid)
     int ndim = 0, N[3] = {1, 1, 1};
     int src_nc = 4, rec_nc = 4;   // corners per source / receiver in the gather tables
+    // 3-D: planes of the scatter points, when the steps inject in their own launches (the
+    // points in at most kInjPlanes planes; sources: one entry a point)
+    std::vector<int> src_pz, rec_pz;
     // host tables, packed
     std::vector<int> src_gidx, rec_gidx, src_pts, src_start, src_col, rec_pts, rec_start, rec_col;
     std::vector<float> src_gwt, rec_gwt, src_swt, rec_swt;
@@ -677,6 +680,20 @@ int build_sparse(const wv_model *m, const Setup &su, int npt, const double *xyz,
     return WV_OK;
 }
 
+// The planes that hold a 3-D scatter table's points (sorted), none when over kInjPlanes.
+std::vector<int> scatter_planes(const Setup &su, const std::vector<int> &pts)
+{
+    std::vector<int> pz;
+    if (su.ndim != 3) return pz;
+    const int plane = su.g.px * su.g.ny;
+    for (const int p : pts) {
+        if (!pz.empty() && pz.back() == p / plane) continue;
+        if ((int)pz.size() == kInjPlanes) return {};
+        pz.push_back(p / plane);
+    }
+    return pz;
+}
+
 int prepare(const wv_model *m, const wv_geom *geo, Setup &su)
 {
     // the launch wrappers report hipGetLastError(); drop any error a previous,
@@ -689,8 +706,12 @@ int prepare(const wv_model *m, const wv_geom *geo, Setup &su)
     rc = build_sparse(m, su, geo->nsrc, geo->src_xyz, true, su.src_gidx, su.src_gwt, su.src_pts, su.src_start,
                       su.src_col, su.src_swt, su.src_nc);
     if (rc) return rc;
-    return build_sparse(m, su, geo->nrec, geo->rec_xyz, false, su.rec_gidx, su.rec_gwt, su.rec_pts, su.rec_start,
-                        su.rec_col, su.rec_swt, su.rec_nc);
+    rc = build_sparse(m, su, geo->nrec, geo->rec_xyz, false, su.rec_gidx, su.rec_gwt, su.rec_pts, su.rec_start,
+                      su.rec_col, su.rec_swt, su.rec_nc);
+    if (rc) return rc;
+    if (su.src_col.size() == su.src_pts.size()) su.src_pz = scatter_planes(su, su.src_pts);
+    su.rec_pz = scatter_planes(su, su.rec_pts);
+    return WV_OK;
 }
 
 size_t tab_bytes(const Setup &su, bool rec)
@@ -728,6 +749,17 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     if (ot4) L.V = take(fb);                    // OT4: v = w lap u (first pass of a step)
     L.src_tab = take(tab_bytes(su, false));
     L.rec_tab = take(tab_bytes(su, true));
+    // the values injected by the steps' own launches: the source points' weights, and the
+    // residual sums of two steps (one injected, the next being formed)
+    const size_t plane_bytes = (size_t)su.g.px * su.g.ny * 4;
+    if (!su.src_pz.empty()) {
+        L.src_plane = take(su.src_pz.size() * plane_bytes);
+        L.src_pos = take(su.src_pts.size() * 4);
+    }
+    if (op == WV_OP_GRADIENT && !su.rec_pz.empty()) {
+        L.rec_plane = take(2 * su.rec_pz.size() * plane_bytes);
+        L.rec_pos = take(su.rec_pts.size() * 4);
+    }
     const size_t data_bytes = (size_t)(m->nt + 1) * geo->nrec * 4;
     if (op == WV_OP_GRADIENT) {
         L.L0 = take(fb);
@@ -767,6 +799,7 @@ struct Dev {
     uint8_t *arena;
     float *res, *dsim;
     double *partials;
+    float *src_plane = nullptr, *rec_plane[2] = {nullptr, nullptr};
 };
 
 template <typename T>
@@ -800,6 +833,13 @@ int upload_tables(Dev &d, const Setup &su, hipStream_t s)
         sp.s_start = (const int *)put(start.data(), start.size() * 4);
         sp.s_col = (const int *)put(col.data(), col.size() * 4);
         sp.s_wt = (const float *)put(swt.data(), swt.size() * 4);
+        const size_t pos = rec ? d.L.rec_pos : d.L.src_pos;   // none: injected by a launch of its own
+        const std::vector<int> &pz = rec ? su.rec_pz : su.src_pz;
+        if (pos) {
+            sp.np = (int)pz.size();
+            std::copy(pz.begin(), pz.end(), sp.pz);
+            sp.s_pos = (int *)(d.base + pos);
+        }
     };
     place(d.L.src_tab, false, d.src);
     place(d.L.rec_tab, true, d.rec);
@@ -855,6 +895,15 @@ int start(Dev &d, const wv_model *m, const Setup &su, hipStream_t s)
     HIPCHK(launch_fill_u64(at<uint64_t>(d.base, d.L.bk), kBk / 8, 0, s));
     int rc = upload_tables(d, su, s);
     if (rc) return rc;
+    const size_t plane = (size_t)su.g.px * su.g.ny;
+    if (d.src.np) {
+        d.src_plane = at<float>(d.base, d.L.src_plane);
+        HIPCHK(launch_plane_setup(su.g, d.src, d.src_plane, 1, true, s));
+    }
+    if (d.rec.np) {
+        for (int i = 0; i < 2; ++i) d.rec_plane[i] = at<float>(d.base, d.L.rec_plane) + i * d.rec.np * plane;
+        HIPCHK(launch_plane_setup(su.g, d.rec, d.rec_plane[0], 2, false, s));
+    }
     HIPCHK(launch_setup_w(su.g, m->vel, d.W, m->dt, m->vmax, d.err, s));
     // every field array starts at zero: kernels write only the nx valid columns of a
     // pitched row, so the pad columns keep this zero for the whole call (and whole-array
@@ -873,37 +922,32 @@ int start(Dev &d, const wv_model *m, const Setup &su, hipStream_t s)
 // x_0, the checkpoint slot itself (uncompressed) or the decoded base pair
 // (compressed).  The next step reads it there and writes the working buffers, so a
 // restore moves no data.
-// Device timing with one event pair per timed region (a schedule action, or one stencil
-// launch), read after the final sync.
+// Device timing, read after the final sync: either by marks between schedule actions (an
+// action's time runs from the mark before it, so each takes one event; actions that enqueue
+// nothing take none), or by an event pair that a stencil launch records itself.
 struct ActionTimer {
     bool on = false;
     hipStream_t s = nullptr;
     std::vector<hipEvent_t> ev;
-    std::vector<int> kind;
+    std::vector<int> kind;      // per interval: [2i, 2i+1] of pairs, [i, i+1] of marks
     size_t used = 0;
+    bool marks = false;
     ~ActionTimer()
     {
         for (hipEvent_t e : ev) (void)hipEventDestroy(e);
     }
-    int begin(int k)
+    // the end of an action of kind k (k < 0: the start of the first)
+    int mark(int k)
     {
         if (!on) return WV_OK;
-        if (used + 2 > ev.size()) {
-            for (int i = 0; i < 2; ++i) {
-                hipEvent_t e;
-                HIPCHK(hipEventCreate(&e));
-                ev.push_back(e);
-            }
+        if (used + 1 > ev.size()) {
+            hipEvent_t e;
+            HIPCHK(hipEventCreate(&e));
+            ev.push_back(e);
         }
-        kind.push_back(k);
-        HIPCHK(hipEventRecord(ev[used], s));
-        return WV_OK;
-    }
-    int end()
-    {
-        if (!on) return WV_OK;
-        HIPCHK(hipEventRecord(ev[used + 1], s));
-        used += 2;
+        marks = true;
+        if (k >= 0) kind.push_back(k);
+        HIPCHK(hipEventRecord(ev[used++], s));
         return WV_OK;
     }
     // a fresh event pair of kind k for a launch that records it itself ({} when off)
@@ -927,9 +971,10 @@ struct ActionTimer {
     // after a sync: accumulate per-kind milliseconds (kinds 1..5 = action codes)
     int totals(double *ms)
     {
-        for (size_t i = 0; i < used / 2; ++i) {
+        for (size_t i = 0; i < kind.size(); ++i) {
             float t = 0.0f;
-            HIPCHK(hipEventElapsedTime(&t, ev[2 * i], ev[2 * i + 1]));
+            const size_t a = marks ? i : 2 * i;
+            HIPCHK(hipEventElapsedTime(&t, ev[a], ev[a + 1]));
             ms[kind[i]] += t;
         }
         return WV_OK;
@@ -947,7 +992,7 @@ struct Fwd {
     hipStream_t s;
     const float *u = nullptr, *up = nullptr;   // u^n, u^{n-1}
     ActionTimer *kt = nullptr;                  // optional per-launch timing of the stencil (kind 0)
-    // 2-D: the data row of u^n not gathered yet; the next step's launch gathers it, or
+    // the data row of u^n not gathered yet: the next step's launch gathers it, or
     // flush() after the last step of a run of steps
     float *pend = nullptr;
     void at(const float *cur, const float *prev)
@@ -962,25 +1007,36 @@ struct Fwd {
         int rc;
         LaunchEvents le;
         if (kt && (rc = kt->pair(0, &le))) return rc;
-        if (su.g.time_order == 4) {
-            HIPCHK(launch_lapw(su.g, u, d.V, d.W, s, le));
-            if (kt && (rc = kt->pair(0, &le))) return rc;
-            HIPCHK(launch_ot4_update(su.g, d.V, u, up, out, d.W, nullptr, nullptr, nullptr, 0.0, s, le));
-            HIPCHK(launch_inject_src(su.g, d.src, geo->wavelet, n, d.W, out, s));
-        } else if (su.ndim == 2) {
-            // the step's own launch injects the source sample and gathers the previous
-            // step's receivers
-            HIPCHK(launch_fwd_step(su.g, u, up, out, d.W, s, le, &d.src, geo->wavelet + n, pend ? &d.rec : nullptr,
-                                   pend));
-            pend = nullptr;
-        } else {
-            HIPCHK(launch_fwd_step(su.g, u, up, out, d.W, s, le));
-            HIPCHK(launch_inject_src(su.g, d.src, geo->wavelet, n, d.W, out, s));
+        // The step's launch injects the source sample and gathers the previous step's
+        // receivers: always in 2-D OT2, in 3-D where the source points lie in few planes
+        // (the gather then too; 2-D OT4 steps keep launches of their own for both).
+        const bool ot4 = su.g.time_order == 4;
+        const bool gfuse = su.ndim == 3 || !ot4, ifuse = su.ndim == 2 ? !ot4 : d.src.np > 0;
+        StepSide inj, gat;
+        if (ifuse) {
+            inj.inj = &d.src;
+            inj.vals = inj.scale = geo->wavelet + n;
+            inj.plane = d.src_plane;
         }
+        if (pend) {
+            gat.gat = &d.rec;
+            gat.row = pend;
+        }
+        if (ot4) {
+            HIPCHK(launch_lapw(su.g, u, d.V, d.W, s, le, gat));
+            if (kt && (rc = kt->pair(0, &le))) return rc;
+            HIPCHK(launch_ot4_update(su.g, d.V, u, up, out, d.W, nullptr, nullptr, nullptr, 0.0, s, le, inj));
+        } else {
+            inj.gat = gat.gat;
+            inj.row = gat.row;
+            HIPCHK(launch_fwd_step(su.g, u, up, out, d.W, s, le, inj));
+        }
+        pend = nullptr;
+        if (!ifuse) HIPCHK(launch_inject_src(su.g, d.src, geo->wavelet, n, d.W, out, s));
         up = u;
         u = out;
         if (data_row) {
-            if (su.ndim == 2 && su.g.time_order != 4) pend = data_row;
+            if (gfuse) pend = data_row;
             else HIPCHK(launch_gather(d.rec, u, data_row, s));
         }
         return WV_OK;
@@ -1252,9 +1308,10 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
     ktimer.on = stats && (stats->timing & 2);
     ktimer.s = s;
     if (ktimer.on) f.kt = &ktimer;
+    rc = timer.mark(-1);
     for (size_t i = 0; i < acts.size() / 3 && rc == WV_OK; ++i) {
         const int op = acts[3 * i], a = acts[3 * i + 1], b = acts[3 * i + 2];
-        if (op != FREE && (rc = timer.begin(op))) break;
+        bool work = op == ADVANCE || op == REVERSE;   // the action enqueues something
         switch (op) {
         case ADVANCE:
             if (!f.up) {   // advancing from a restore: the second level is needed now
@@ -1309,6 +1366,7 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
                 // u^k at offs[2b]; with both levels the increment u^k - u^{k-1} follows at
                 // offs[2b+1]; the next slot starts at offs[2b+2]
                 const bool skip = R.optimistic && R.arena_full && !profile_sample(N, a);
+                work = !skip;
                 if (skip) {
                     // the arena is full: this attempt will stop, and only the profile's
                     // samples are still measured
@@ -1327,10 +1385,14 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
             } else {
                 // copy only the levels the advance before did not write in place
                 uint8_t *slot = d.arena + (size_t)(b - 1) * R.S;
-                if ((const void *)f.u != (const void *)slot)
+                if ((const void *)f.u != (const void *)slot) {
                     HIPCHK(hipMemcpyAsync(slot, f.u, fb, hipMemcpyDeviceToDevice, s));
-                if (need2[i] && (const void *)f.up != (const void *)(slot + fb))
+                    work = true;
+                }
+                if (need2[i] && (const void *)f.up != (const void *)(slot + fb)) {
                     HIPCHK(hipMemcpyAsync(slot + fb, f.up, fb, hipMemcpyDeviceToDevice, s));
+                    work = true;
+                }
             }
             R.stores++;
             R.fields += need2[i] ? 2 : 1;
@@ -1347,6 +1409,7 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
                     hot_k = a;
                     hot_db = false;
                     R.decodes++;
+                    work = true;
                 }
                 // u^{k-1} is decoded by the advance that needs it
                 f.at(d.UB, nullptr);
@@ -1378,6 +1441,26 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
             const float *uk = R.G ? f.u : nullptr;
             LaunchEvents le;
             if ((rc = ktimer.pair(1, &le))) break;
+            // the step's own launch injects the residual row: always in 2-D OT2, in 3-D
+            // where the receivers' points lie in few planes
+            const bool fused = R.su.ndim == 2 ? R.su.g.time_order != 4 : d.rec.np > 0;
+            const float *r_row = res + (size_t)a * R.geo->nrec;
+            StepSide side;
+            if (fused) {
+                side.inj = &d.rec;
+                side.vals = r_row;
+                if (R.su.ndim == 3) {
+                    // reverse steps go through k = N..1 in order: each sums the next one's
+                    // residual samples, the first finds its own summed beforehand
+                    if (a == N) HIPCHK(launch_plane_sums(d.rec, r_row, d.rec_plane[a & 1], s));
+                    side.plane = d.rec_plane[a & 1];
+                    if (a > 1) {
+                        side.next = &d.rec;
+                        side.next_vals = r_row - R.geo->nrec;
+                        side.next_plane = d.rec_plane[(a - 1) & 1];
+                    }
+                }
+            }
             // lam^{k-1} overwrites lam^{k+1}
             if (R.su.g.time_order == 4) {
                 // v_u = w lap u^k; v = w lap lam^k; then the update, which adds both
@@ -1390,21 +1473,16 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
                 HIPCHK(launch_lapw(R.su.g, d.Lm[lc], d.V, d.W, s, le));
                 if ((rc = ktimer.pair(1, &le))) break;
                 HIPCHK(launch_ot4_update(R.su.g, d.V, d.Lm[lc], d.Lm[lc ^ 1], d.Lm[lc ^ 1], d.W, uk, uk ? d.VU : nullptr,
-                                         R.G, gscale, s, le));
+                                         R.G, gscale, s, le, side));
             } else {
                 // 3-D: the steps k = 2j and 2j - 1 update G once between them (the even
                 // step carries its term); an odd first step k = N adds its own
                 int gm = kGAdd;
                 if (uk && d.CR) gm = a % 2 == 0 ? kGCarryOut : (a < N ? kGCarryIn : kGAdd);
-                // 2-D: the step's own launch injects the residual row
-                const bool fused = R.su.ndim == 2;
                 HIPCHK(launch_adj_step(R.su.g, d.Lm[lc], d.Lm[lc ^ 1], d.Lm[lc ^ 1], d.W, uk, R.G, gscale, s, le,
-                                       d.CR, gm, fused ? &d.rec : nullptr,
-                                       fused ? res + (size_t)a * R.geo->nrec : nullptr));
+                                       d.CR, gm, side));
             }
-            if (R.su.g.time_order == 4 || R.su.ndim == 3)
-                HIPCHK(launch_inject_res(R.su.g, d.rec, res + (size_t)a * R.geo->nrec, d.W, d.Lm[lc ^ 1], uk, R.G,
-                                         gscale, s));
+            if (!fused) HIPCHK(launch_inject_res(R.su.g, d.rec, r_row, d.W, d.Lm[lc ^ 1], uk, R.G, gscale, s));
             lc ^= 1;
             if (R.src_adj) HIPCHK(launch_gather_sum(d.src, d.Lm[lc], R.src_adj + (a - 1), s));
             R.reverses++;
@@ -1413,7 +1491,7 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
         default:
             rc = WV_EINVAL;
         }
-        if (rc == WV_OK && op != FREE) rc = timer.end();
+        if (rc == WV_OK && work) rc = timer.mark(op);
     }
     if (rc) {
         (void)hipEventDestroy(e0);

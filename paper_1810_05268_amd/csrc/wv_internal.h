@@ -36,6 +36,9 @@ struct Grid {
 };
 
 // Sparse point operators (sources / receivers), built on the host.
+// A 3-D step injects in its own launch when the points lie in few grid planes (a surface
+// survey: one plane on the nodes, two between them); more planes take a launch of their own.
+constexpr int kInjPlanes = 4;
 //   gather:  out[r] = sum_c wt[r*nc + c] * f[idx[r*nc + c]]
 //   scatter: unique points pts[i], entries [start[i], start[i+1]) of (col, wt)
 struct Sparse {
@@ -45,6 +48,29 @@ struct Sparse {
     int npts;         // unique grid points touched
     const int *s_pts; const int *s_start;        // [npts], [npts+1]
     const int *s_col; const float *s_wt;         // [nnz]
+    // 3-D: the grid planes that hold scatter points, when they are at most kInjPlanes
+    // (np = 0 otherwise), ascending; s_pos[npts]: each unique point's place in an array of
+    // np pitched planes
+    int np; int pz[kInjPlanes];
+    int *s_pos;
+};
+
+// What a step's launch does beside the step.
+struct StepSide {
+    // injects into the level it writes.  2-D: the samples vals at the points of inj.  3-D
+    // (inj->np > 0): plane holds the points' values in np pitched planes, each multiplied by
+    // *scale when scale is set
+    const Sparse *inj = nullptr;
+    const float *vals = nullptr;
+    const float *plane = nullptr, *scale = nullptr;
+    // gathers the receivers of its input level into row
+    const Sparse *gat = nullptr;
+    float *row = nullptr;
+    // 3-D: sums the samples next_vals at the points of next into the planes next_plane (the
+    // values a later step injects; places of no point are not written)
+    const Sparse *next = nullptr;
+    const float *next_vals = nullptr;
+    float *next_plane = nullptr;
 };
 
 // ---------------------------------------------------------------- stencil launches (wv_stencil.hip)
@@ -54,13 +80,9 @@ struct LaunchEvents {
     hipEvent_t start = nullptr, stop = nullptr;
 };
 // Forward step: u_out = u_in + ((1-a)(u_in - u_prev) + w lap u_in)/(1+a).
-// u_out may equal u_prev (in place); it must differ from u_in.  2-D only: with src, the
-// same launch then injects sample q_n (a device pointer) at the table's points, as
-// launch_inject_src would; with rec and row_prev, it also gathers the receivers of u_in
-// (the previous step's level) into row_prev, as launch_gather would.
+// u_out may equal u_prev (in place); it must differ from u_in.
 hipError_t launch_fwd_step(const Grid &g, const float *u_in, const float *u_prev, float *u_out, const float *w,
-                           hipStream_t s, LaunchEvents ev = {}, const Sparse *src = nullptr,
-                           const float *q_n = nullptr, const Sparse *rec = nullptr, float *row_prev = nullptr);
+                           hipStream_t s, LaunchEvents ev = {}, const StepSide &side = {});
 // How an adjoint step's gradient term t = uk * (w lap lam_in) reaches G.  The carried
 // forms are for 3-D grids: a step with kGCarryOut leaves t, rounded to binary32, in a
 // field-sized array, and the next adjoint step (kGCarryIn) adds it with its own term,
@@ -69,21 +91,25 @@ constexpr int kGNone = 0, kGAdd = 1, kGCarryOut = 2, kGCarryIn = 3;
 // Adjoint step (lam_in = lam^k, lam_next = lam^{k+1}, lam_out = lam^{k-1}, may equal
 // lam_next): the same update, and (if G) G += gscale * uk * (w lap lam_in), or the
 // carried form gmode selects with the array carry (pitched like a field).
-// 2-D only: with rec, the same launch then injects the residual row r_row at the
-// receivers (and their gradient term), as launch_inject_res would.
+// An injection adds its gradient term too.
 hipError_t launch_adj_step(const Grid &g, const float *lam_in, const float *lam_next, float *lam_out,
                            const float *w, const float *uk, double *G, double gscale, hipStream_t s,
                            LaunchEvents ev = {}, float *carry = nullptr, int gmode = kGAdd,
-                           const Sparse *rec = nullptr, const float *r_row = nullptr);
-// OT4, first pass: v_out = w lap f.
+                           const StepSide &side = {});
+// OT4, first pass: v_out = w lap f (side: gather only, in 3-D).
 hipError_t launch_lapw(const Grid &g, const float *f, float *v_out, const float *w, hipStream_t s,
-                       LaunchEvents ev = {});
+                       LaunchEvents ev = {}, const StepSide &side = {});
 // OT4, second pass: u_out = u_in + ((1-a)(u_in - u_prev) + v + (w/12) lap v)/(1+a), v = w lap u_in
 // from the first pass; with G, G += gscale * (uk * (v + (w/12) lap v) + v * vu / 12), vu = w lap uk.
-// u_out may equal u_prev.
+// u_out may equal u_prev.  side: injection and next planes, in 3-D.
 hipError_t launch_ot4_update(const Grid &g, const float *v, const float *u_in, const float *u_prev, float *u_out,
                              const float *w, const float *uk, const float *vu, double *G, double gscale,
-                             hipStream_t s, LaunchEvents ev = {});
+                             hipStream_t s, LaunchEvents ev = {}, const StepSide &side = {});
+// 3-D tables with np > 0: fills sp.s_pos and zeroes planes (nplanes sets of np pitched planes);
+// with weights, the first set receives each point's weight (tables of one entry a point).
+hipError_t launch_plane_setup(const Grid &g, const Sparse &sp, float *planes, int nsets, bool weights, hipStream_t s);
+// The points' summed samples, at their places in one set of planes (as StepSide::next).
+hipError_t launch_plane_sums(const Sparse &sp, const float *vals, float *plane, hipStream_t s);
 // Source injection of sample q[n] (forward) at the unique source points of u_out.
 hipError_t launch_inject_src(const Grid &g, const Sparse &sp, const float *q, int n, const float *w,
                              float *u_out, hipStream_t s);

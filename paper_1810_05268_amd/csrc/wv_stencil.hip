@@ -35,6 +35,8 @@
 // a 32-wide tile row is then exactly one 128-byte line.  With a row length that is
 // not a multiple of 32 (e.g. 400), every other tile row straddles two lines, which
 // measured 10-15 % slower.  The binary64 gradient belongs to the caller and is dense.
+#include <algorithm>
+
 #include <hip/hip_ext.h>
 
 #include "wv_stencil_dev.h"
@@ -56,6 +58,38 @@ __device__ __forceinline__ void ntstore4(float *p, float a, float b, float c, fl
 {
     f4v t = {a, b, c, d};
     __builtin_nontemporal_store(t, reinterpret_cast<f4v *>(p));
+}
+
+// What a 3-D launch does beside the step (see StepSide).
+struct Side3d {
+    const float *plane, *scale;      // injected values: np planes, times *scale if set
+    int np, pz[kInjPlanes];
+    Sparse gat;                      // receiver gather of the input level into row
+    float *row;
+    Sparse next;                     // sums for a later step's injection
+    const float *next_vals;
+    float *next_plane;
+    int gat_wg, next_wg;             // workgroups of each
+};
+constexpr int kSidePerWg = 1024;     // points of a side workgroup
+
+__device__ __forceinline__ void side_work(const Side3d &S, const float *__restrict__ f, int b)
+{
+    const bool next = b >= S.gat_wg;
+    const int i0 = (next ? b - S.gat_wg : b) * kSidePerWg + (int)threadIdx.x;
+    if (!next) {
+#pragma unroll
+        for (int j = 0; j < kSidePerWg / 256; ++j) {
+            const int r = i0 + 256 * j;
+            if (r < S.gat.n) S.row[r] = gather_point(S.gat, r, f);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kSidePerWg / 256; ++j) {
+            const int i = i0 + 256 * j;
+            if (i < S.next.npts) S.next_plane[S.next.s_pos[i]] = scatter_sum(S.next, i, S.next_vals);
+        }
+    }
 }
 
 // 3-D step.  A workgroup owns a 32 x 32 tile of the x-y plane and marches down z
@@ -96,13 +130,23 @@ __device__ __forceinline__ void ntstore4(float *p, float a, float b, float c, fl
 //   kGCarryOut: cr = t rounded to binary32, G untouched;
 //   kGCarryIn:  G += gscale (t + cr), cr from the kGCarryOut step before.
 // A pair of adjoint steps thus reads and writes the binary64 gradient once.
+//
+// S is what the launch does beside the step, each formerly a launch of its own (4.4 and
+// 3.8 us of a 35 us step on 168^3 points at order 8 with 16384 receivers, and 3 us of gaps):
+//   * injection into the level it writes (and its gradient term), as inject_kernel would
+//     after it, with the same operations in the same order.  The points lie in few planes;
+//     a workgroup whose chunk holds one reads its tile of the plane's values before the
+//     march, into LDS, so that the march waits for nothing;
+//   * the receivers of `fin`, and the sums a later step injects, by further workgroups at
+//     the end of the grid.  Their chains of dependent loads then run beside the march; done
+//     by the marching workgroups themselves they cost 5-10 us a step.
 template <int K, int GM, bool WHOLE, int MODE>
 __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *__restrict__ fin,
                                                  const float *prev, float *fout, const float *__restrict__ w,
                                                  const float *__restrict__ uk, const float *__restrict__ xtra,
                                                  const float *__restrict__ xtra2, double *__restrict__ G,
                                                  float *__restrict__ cr, double gscale, int tiles_x, int tiles_y,
-                                                 int zchunks, int zlen)
+                                                 int zchunks, int zlen, const Side3d S3)
 {
     constexpr bool GRAD = GM != kGNone;                    // u^k is read
     constexpr bool GRW = GM == kGAdd || GM == kGCarryIn;    // G is read and written
@@ -119,9 +163,15 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     // planes between a stage's loads and its use: two where three stages fit in 256
     // registers without spilling (no gradient, not the OT4 update)
     constexpr int AHEAD = (!GRAD && MODE != kOT4) ? 2 : 1;
+    constexpr bool INJ = MODE != kLapW;                     // may inject
     __shared__ __align__(16) float tile[2][LY][LX];
+    __shared__ __align__(16) float s_inj[INJ ? kInjPlanes : 1][INJ ? 256 : 1][4];
 
     const int nwg = tiles_x * tiles_y * zchunks;
+    if ((int)blockIdx.x >= nwg) {
+        side_work(S3, fin, (int)blockIdx.x - nwg);
+        return;
+    }
     const int lid = xcd_remap(blockIdx.x, nwg);
     const int tix = lid % tiles_x;
     const int tiy = (lid / tiles_x) % tiles_y;
@@ -222,6 +272,18 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     for (int j = 0; j < 2 * K + 1; ++j) {
         const float4 v = load4(fin, z0 - K + j, y, x0, rowin);
         q[0][j] = v.x; q[1][j] = v.y; q[2][j] = v.z; q[3][j] = v.w;
+    }
+    if constexpr (INJ) {
+        for (int j = 0; j < S3.np; ++j) {
+            if (S3.pz[j] < z0 || S3.pz[j] >= z1) continue;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ptin) v = *reinterpret_cast<const float4 *>(S3.plane + j * sxy + rowoff + x0);
+            if (S3.scale) {
+                const float q = *S3.scale;
+                v = make_float4(v.x * q, v.y * q, v.z * q, v.w * q);
+            }
+            *reinterpret_cast<float4 *>(&s_inj[j][tid][0]) = v;
+        }
     }
     Stage A, B, C;
     fill(A, z0);
@@ -326,6 +388,29 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
                 on[i] = ctr + ((1.0f - a) * (ctr - pin[i]) + wl[i]) * r;
             }
         }
+        // injected values of this plane (0 where a point has none): w s and w s / (1+a)
+        float wi[4] = {0.f, 0.f, 0.f, 0.f};
+        bool inj = false;
+        if constexpr (INJ) {
+            {
+                int j = S3.np;
+#pragma unroll
+                for (int i = 0; i < kInjPlanes; ++i)
+                    if (i < S3.np && S3.pz[i] == z) j = i;
+                if (j < S3.np) {
+                    const float4 s4 = *reinterpret_cast<const float4 *>(&s_inj[j][tid][0]);   // the lane's own
+                    const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (sv[i] != 0.0f) {
+                            inj = true;
+                            wi[i] = win[i] * sv[i];
+                            on[i] += injected(g, x0 + i, y, z, wi[i]);
+                        }
+                    }
+                }
+            }
+        }
         if (ptin) {
             const long long p0 = (long long)z * sxy + rowoff + x0;
             const long long p0g = ((long long)z * ny + y) * nx + x0;   // dense gradient
@@ -339,6 +424,11 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) t[i] = uin[i] * wl[i];
                 ntstore4(cr + p0, t[0], t[1], t[2], t[3]);
+                if (inj) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (wi[i] != 0.0f) G[p0g + i] += gscale * (double)uin[i] * (double)wi[i];
+                }
             }
             if constexpr (GRW) {
                 const float tin[4] = {S.t.x, S.t.y, S.t.z, S.t.w};
@@ -352,6 +442,10 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
                         gn[i] = gold[i] + gscale * ((double)uin[i] * (double)wl[i] + (double)tin[i]);
                     else
                         gn[i] = gold[i] + gscale * (double)uin[i] * (double)wl[i];
+                }
+                if (inj) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) gn[i] += gscale * (double)uin[i] * (double)wi[i];
                 }
                 if constexpr (WHOLE) {
                     *reinterpret_cast<double2 *>(&G[p0g]) = make_double2(gn[0], gn[1]);
@@ -475,6 +569,26 @@ __global__ void inject_kernel(Grid g, Sparse sp, const float *__restrict__ vals,
     const int rem = (int)(p - z * sxy);
     const int y = rem / g.px, x = rem - (rem / g.px) * g.px;
     inject_point<GRAD>(g, sp, i, p, x, y, z, vals, w, fout, uk, G, ((long long)z * g.ny + y) * g.nx + x, gscale);
+}
+
+// each point's place in the planes of its table, and (with weights) its weight there
+__global__ void plane_setup_kernel(Sparse sp, int plane, float *__restrict__ weights)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < sp.npts; i += gridDim.x * blockDim.x) {
+        const int p = sp.s_pts[i];
+        const int z = p / plane;
+        int pos = p - z * plane;
+        for (int j = 0; j < sp.np; ++j)
+            if (sp.pz[j] == z) pos += j * plane;
+        sp.s_pos[i] = pos;
+        if (weights) weights[pos] = sp.s_wt[sp.s_start[i]];
+    }
+}
+
+__global__ void plane_sums_kernel(Sparse sp, const float *__restrict__ vals, float *__restrict__ plane)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < sp.npts; i += gridDim.x * blockDim.x)
+        plane[sp.s_pos[i]] = scatter_sum(sp, i, vals);
 }
 
 __global__ void gather_kernel(Sparse sp, const float *__restrict__ f, float *__restrict__ out)
@@ -664,7 +778,7 @@ void launch_timed(Kern kern, dim3 grid, hipStream_t s, LaunchEvents ev, Args... 
 template <int K, int GM, bool WHOLE, int MODE>
 hipError_t launch3d(const Grid &g, const float *fin, const float *prev, float *fout, const float *w,
                     const float *uk, const float *xtra, const float *xtra2, double *G, float *cr, double gscale,
-                    hipStream_t s, LaunchEvents ev)
+                    hipStream_t s, LaunchEvents ev, const StepSide &side)
 {
     auto kern = stencil3d<K, GM, WHOLE, MODE>;
     const int tiles_x = (g.nx + 31) / 32, tiles_y = (g.ny + 31) / 32;
@@ -673,21 +787,40 @@ hipError_t launch3d(const Grid &g, const float *fin, const float *prev, float *f
     int zchunks, zlen;
     choose_chunks((long long)tiles_x * tiles_y, g.nz, 4 * K, resident_workgroups(kern), zchunks, zlen);
     const int nwg = tiles_x * tiles_y * zchunks;
-    launch_timed(kern, dim3(nwg), s, ev, g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, tiles_x, tiles_y,
-                 zchunks, zlen);
+    Side3d S{};
+    if (side.inj) {
+        if (side.inj->np < 1 || !side.plane || MODE == kLapW) return hipErrorInvalidValue;
+        S.plane = side.plane;
+        S.scale = side.scale;
+        S.np = side.inj->np;
+        std::copy(side.inj->pz, side.inj->pz + S.np, S.pz);
+    }
+    if (side.gat && side.row) {
+        if (MODE == kOT4) return hipErrorInvalidValue;   // its input is not the wavefield
+        S.gat = *side.gat;
+        S.row = side.row;
+        S.gat_wg = (S.gat.n + kSidePerWg - 1) / kSidePerWg;
+    }
+    if (side.next) {
+        S.next = *side.next;
+        S.next_vals = side.next_vals;
+        S.next_plane = side.next_plane;
+        S.next_wg = (S.next.npts + kSidePerWg - 1) / kSidePerWg;
+    }
+    launch_timed(kern, dim3(nwg + S.gat_wg + S.next_wg), s, ev, g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale,
+                 tiles_x, tiles_y, zchunks, zlen, S);
     return hipGetLastError();
 }
 
 template <int K, int GM, int MODE>
 hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *fout, const float *w,
                     const float *uk, const float *xtra, const float *xtra2, double *G, float *cr, double gscale,
-                    hipStream_t s, LaunchEvents ev, const Sparse *inj, const float *inj_vals, const Sparse *gsp,
-                    const float *gin, float *gout)
+                    hipStream_t s, LaunchEvents ev, const StepSide &side)
 {
     if (g.ndim == 3) {
         if (g.nx % 4 == 0)
-            return launch3d<K, GM, true, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev);
-        return launch3d<K, GM, false, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev);
+            return launch3d<K, GM, true, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+        return launch3d<K, GM, false, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
     }
     if constexpr (GM == kGCarryOut || GM == kGCarryIn) {
         return hipErrorInvalidValue;   // 2-D steps add their gradient term directly
@@ -699,11 +832,12 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
     int zchunks, zlen;
     choose_chunks(tiles_x, g.nz, K, 2048, zchunks, zlen);
     const int nwg = tiles_x * zchunks;
-    const Sparse spv = inj ? *inj : Sparse{};
-    const Sparse gv = (gsp && gout) ? *gsp : Sparse{};
-    float *go = (gsp && gout) ? gout : nullptr;
+    if (side.next || (MODE != kOT2 && (side.inj || side.row))) return hipErrorInvalidValue;
+    const Sparse spv = side.inj ? *side.inj : Sparse{};
+    const Sparse gv = side.gat ? *side.gat : Sparse{};
+    float *go = side.gat ? side.row : nullptr;
     launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(nwg + (go ? 1 : 0)), s, ev, g, fin, prev, fout, w, uk, xtra,
-                 xtra2, G, gscale, tiles_x, zchunks, zlen, spv, inj ? inj_vals : (const float *)nullptr, gv, gin, go);
+                 xtra2, G, gscale, tiles_x, zchunks, zlen, spv, side.inj ? side.vals : nullptr, gv, fin, go);
     return hipGetLastError();
     }
 }
@@ -711,37 +845,17 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
 template <int GM, int MODE>
 hipError_t launch_any(const Grid &g, const float *fin, const float *prev, float *fout, const float *w,
                       const float *uk, const float *xtra, const float *xtra2, double *G, double gscale, hipStream_t s,
-                      LaunchEvents ev, float *cr = nullptr, const Sparse *inj = nullptr,
-                      const float *inj_vals = nullptr, const Sparse *gsp = nullptr, const float *gin = nullptr,
-                      float *gout = nullptr)
+                      LaunchEvents ev, const StepSide &side, float *cr = nullptr)
 {
-    if (gout && g.ndim != 2) return hipErrorInvalidValue;
-    if (inj && g.ndim != 2) return hipErrorInvalidValue;   // 3-D steps inject in a launch of their own
     switch (g.K) {
-    case 1:
-        return launch_k<1, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 2:
-        return launch_k<2, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 3:
-        return launch_k<3, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 4:
-        return launch_k<4, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 5:
-        return launch_k<5, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 6:
-        return launch_k<6, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 7:
-        return launch_k<7, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
-    case 8:
-        return launch_k<8, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, inj, inj_vals, gsp,
-                                       gin, gout);
+    case 1: return launch_k<1, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 2: return launch_k<2, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 3: return launch_k<3, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 4: return launch_k<4, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 5: return launch_k<5, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 6: return launch_k<6, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 7: return launch_k<7, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
+    case 8: return launch_k<8, GM, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
     default: return hipErrorInvalidValue;
     }
 }
@@ -749,45 +863,59 @@ hipError_t launch_any(const Grid &g, const float *fin, const float *prev, float 
 }  // namespace
 
 hipError_t launch_fwd_step(const Grid &g, const float *u_in, const float *u_prev, float *u_out, const float *w,
-                           hipStream_t s, LaunchEvents ev, const Sparse *src, const float *q_n, const Sparse *rec,
-                           float *row_prev)
+                           hipStream_t s, LaunchEvents ev, const StepSide &side)
 {
-    return launch_any<kGNone, kOT2>(g, u_in, u_prev, u_out, w, nullptr, nullptr, nullptr, nullptr, 0.0, s, ev,
-                                    nullptr, src, q_n, rec, u_in, row_prev);
+    return launch_any<kGNone, kOT2>(g, u_in, u_prev, u_out, w, nullptr, nullptr, nullptr, nullptr, 0.0, s, ev, side);
 }
 
 hipError_t launch_adj_step(const Grid &g, const float *lam_in, const float *lam_next, float *lam_out,
                            const float *w, const float *uk, double *G, double gscale, hipStream_t s,
-                           LaunchEvents ev, float *carry, int gmode, const Sparse *rec, const float *r_row)
+                           LaunchEvents ev, float *carry, int gmode, const StepSide &side)
 {
     if (!G) return launch_any<kGNone, kOT2>(g, lam_in, lam_next, lam_out, w, nullptr, nullptr, nullptr, nullptr, 0.0,
-                                            s, ev, nullptr, rec, r_row);
+                                            s, ev, side);
     if (gmode != kGAdd && (g.ndim != 3 || !carry)) return hipErrorInvalidValue;
     switch (gmode) {
     case kGAdd:
-        return launch_any<kGAdd, kOT2>(g, lam_in, lam_next, lam_out, w, uk, nullptr, nullptr, G, gscale, s, ev,
-                                       nullptr, rec, r_row);
+        return launch_any<kGAdd, kOT2>(g, lam_in, lam_next, lam_out, w, uk, nullptr, nullptr, G, gscale, s, ev, side);
     case kGCarryOut:
         return launch_any<kGCarryOut, kOT2>(g, lam_in, lam_next, lam_out, w, uk, nullptr, nullptr, G, gscale, s, ev,
-                                            carry);
+                                            side, carry);
     case kGCarryIn:
         return launch_any<kGCarryIn, kOT2>(g, lam_in, lam_next, lam_out, w, uk, nullptr, nullptr, G, gscale, s, ev,
-                                           carry);
+                                           side, carry);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_lapw(const Grid &g, const float *f, float *v_out, const float *w, hipStream_t s, LaunchEvents ev)
+hipError_t launch_lapw(const Grid &g, const float *f, float *v_out, const float *w, hipStream_t s, LaunchEvents ev,
+                       const StepSide &side)
 {
-    return launch_any<kGNone, kLapW>(g, f, nullptr, v_out, w, nullptr, nullptr, nullptr, nullptr, 0.0, s, ev);
+    return launch_any<kGNone, kLapW>(g, f, nullptr, v_out, w, nullptr, nullptr, nullptr, nullptr, 0.0, s, ev, side);
 }
 
 hipError_t launch_ot4_update(const Grid &g, const float *v, const float *u_in, const float *u_prev, float *u_out,
                              const float *w, const float *uk, const float *vu, double *G, double gscale, hipStream_t s,
-                             LaunchEvents ev)
+                             LaunchEvents ev, const StepSide &side)
 {
-    if (G) return launch_any<kGAdd, kOT4>(g, v, u_prev, u_out, w, uk, u_in, vu, G, gscale, s, ev);
-    return launch_any<kGNone, kOT4>(g, v, u_prev, u_out, w, nullptr, u_in, nullptr, nullptr, 0.0, s, ev);
+    if (G) return launch_any<kGAdd, kOT4>(g, v, u_prev, u_out, w, uk, u_in, vu, G, gscale, s, ev, side);
+    return launch_any<kGNone, kOT4>(g, v, u_prev, u_out, w, nullptr, u_in, nullptr, nullptr, 0.0, s, ev, side);
+}
+
+hipError_t launch_plane_setup(const Grid &g, const Sparse &sp, float *planes, int nsets, bool weights, hipStream_t s)
+{
+    const long long set = (long long)sp.np * g.px * g.ny;
+    hipLaunchKernelGGL((fill_kernel<float>), dim3(grid_for(nsets * set, 256)), dim3(256), 0, s, planes, nsets * set,
+                       0.0f);
+    hipLaunchKernelGGL(plane_setup_kernel, dim3(grid_for(sp.npts, 256)), dim3(256), 0, s, sp, g.px * g.ny,
+                       weights ? planes : nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_plane_sums(const Sparse &sp, const float *vals, float *plane, hipStream_t s)
+{
+    hipLaunchKernelGGL(plane_sums_kernel, dim3(grid_for(sp.npts, 256)), dim3(256), 0, s, sp, vals, plane);
+    return hipGetLastError();
 }
 
 hipError_t launch_inject_src(const Grid &g, const Sparse &sp, const float *q, int n, const float *w,

@@ -124,6 +124,21 @@ __device__ __forceinline__ void march2d(const Grid &g, const float *__restrict__
     }
 }
 
+// The weighted sum of the samples at unique point i of the scatter table.
+__device__ __forceinline__ float scatter_sum(const Sparse &sp, int i, const float *__restrict__ vals)
+{
+    float s = 0.0f;
+    for (int e = sp.s_start[i]; e < sp.s_start[i + 1]; ++e) s = fmaf(sp.s_wt[e], vals[sp.s_col[e]], s);
+    return s;
+}
+
+// What an injected term wi = w s adds to the level at (x, y, z).
+__device__ __forceinline__ float injected(const Grid &g, int x, int y, int z, float wi)
+{
+    const float a = damping(g, x, y, z);
+    return (a == 0.0f) ? wi : wi / (1.0f + a);
+}
+
 // Source (or residual) injection at one unique point p of the scatter table entry i:
 // fout[p] += w s / (1+a), s the weighted sum of its samples; GRAD adds the gradient term
 // of the injected value.  (x, y, z): the point's coordinates.
@@ -133,12 +148,8 @@ __device__ __forceinline__ void inject_point(const Grid &g, const Sparse &sp, in
                                              float *__restrict__ fout, const float *__restrict__ uk,
                                              double *__restrict__ G, long long pg, double gscale)
 {
-    float s = 0.0f;
-    for (int e = sp.s_start[i]; e < sp.s_start[i + 1]; ++e) s = fmaf(sp.s_wt[e], vals[sp.s_col[e]], s);
-    const float a = damping(g, x, y, z);
-    const float wi = w[p] * s;
-    const float inj = (a == 0.0f) ? wi : wi / (1.0f + a);
-    fout[p] += inj;
+    const float wi = w[p] * scatter_sum(sp, i, vals);
+    fout[p] += injected(g, x, y, z, wi);
     if constexpr (GRAD) G[pg] += gscale * (double)uk[p] * (double)wi;
 }
 
