@@ -12,7 +12,7 @@
 // injection, gather, codec block and reduction code, in the same order), so a shot
 // gives the same bits alone, in a solo call and in any batch.
 #include "wv_codec_dev.h"
-#include "wv_stencil_dev.h"
+#include "wv_tile2d_dev.h"
 
 namespace wv {
 
@@ -20,23 +20,22 @@ namespace {
 
 constexpr int kBatchParts = 1024;   // residual partial sums per shot (as the solo misfit)
 constexpr int kCopyItem = 65536;    // elements per copy or finiteness work item
+// Threads of a workgroup: a region of the steps takes all of them, one row of points a
+// lane; the codec's chunks and the reductions, shared with the solo path, take 256 lanes, so
+// the workgroup runs them as groups.
+constexpr int kBatchRows = 1, kBatchThreads = tile2d_threads(kBatchRows), kGroups = kBatchThreads / 256;
+static_assert(kBatchThreads % 256 == 0, "whole groups");
 
-__device__ __forceinline__ float *batch_buf(const BatchShot &S, int id, long long slot_elems, long long P)
+__device__ __forceinline__ float *batch_buf(const BatchArgs &A, const BatchShot &S, int id, long long P)
 {
-    switch (id) {
-    case kBufZ: return S.Z;
-    case kBufU0: return S.U[0];
-    case kBufU1: return S.U[1];
-    case kBufUB: return S.UB;
-    case kBufDB: return S.DB;
-    case kBufL0: return S.Lm[0];
-    case kBufL1: return S.Lm[1];
-    case kBufNone: return nullptr;
-    default: {
-        const int b = (id - kBufSlot) >> 1, l = (id - kBufSlot) & 1;
-        return reinterpret_cast<float *>(S.arena) + (long long)(b - 1) * slot_elems + (long long)l * P;
-    }
-    }
+    if (id < 0) return nullptr;
+    if (id >= kBufSlot)
+        return reinterpret_cast<float *>(S.arena) + (long long)((id - kBufSlot) / 2 - 1) * A.slot_elems +
+               (long long)(id & 1) * P;
+    if (id >= kBufUB) return S.UB + (id - kBufUB) * A.fstride;
+    if (id >= kBufU) return S.U + (id - kBufU) * A.fstride;
+    if (id >= kBufL) return S.Lm + (id - kBufL) * A.fstride;
+    return id == kBufDB ? S.DB : S.Z;
 }
 
 // Device-wide barrier of the persistent launch.  Two levels: workgroup b arrives at the
@@ -93,7 +92,7 @@ __device__ __forceinline__ bool grid_barrier(unsigned *bar, unsigned nwg, unsign
     return *s_flag != 0u;
 }
 
-// inclusive workgroup scan of v (s_scan: scratch for the wave totals); the trailing
+// inclusive scan of v over the group (s_scan: scratch for its wave totals); the trailing
 // barrier lets the caller reuse s_scan at once
 __device__ __forceinline__ unsigned block_scan(unsigned *s_scan, unsigned v, unsigned &total)
 {
@@ -102,16 +101,17 @@ __device__ __forceinline__ unsigned block_scan(unsigned *s_scan, unsigned v, uns
     return r;
 }
 
-// sum of w[0..n) by one workgroup (wave 0 does the adding), broadcast through *out
+// sum of w[0..n) by the group (its first wave does the adding), broadcast through *out
 __device__ __forceinline__ unsigned long long block_sum_words(const uint32_t *w, long long n,
                                                               unsigned long long *out)
 {
-    if (threadIdx.x < 64) {
+    const int tid = threadIdx.x & 255;
+    if (tid < 64) {
         unsigned long long s = 0;
-        for (long long i = threadIdx.x; i < n; i += 64) s += w[i];
+        for (long long i = tid; i < n; i += 64) s += w[i];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (threadIdx.x == 0) *out = s;
+        if (tid == 0) *out = s;
     }
     __syncthreads();
     const unsigned long long r = *out;
@@ -135,7 +135,6 @@ struct BatchCtx {
     const Grid &g;
     const CodecDims &cd;
     long long P;
-    int tiles_x, st_items;
     bool vec;
     long long nch;
 };
@@ -150,49 +149,65 @@ __device__ __forceinline__ void for_items(const BatchArgs &A, int per, Body body
     }
 }
 
-// One forward (GRAD false) or adjoint (GRAD true) step of every shot, injections fused.
-// Items [0, st_items) of a shot march one z-chunk of one 256-column tile, then add the
-// injections whose grid point lies in that chunk and tile: the source's sample n into
-// `out` (forward), or the residual's row n into `out` with its gradient term (adjoint).
-// Every point has one owner, and its value is the stencil's and then the injection's, as
-// in the solo solver.  Item st_items of a shot gathers the receivers of `gin` into data
-// row `grow` (if grow >= 0): the deferred gather of the previous step's output, which
-// nothing writes during this step.
+// A step or adjoint phase of one shot, as tile2d takes it.
+template <bool GRAD>
+struct ShotTile {
+    const BatchArgs &A;
+    const BatchShot &S;
+    const BatchOp &op;
+    long long P;
+    const float *u, *up, *w;
+    int ns;
+    const Sparse &inj;
+    const float *vals;
+    long long vstride;
+    const Sparse &gat;
+    float *rows;
+    unsigned gmask;
+    double *G;
+    double gscale;
+    __device__ ShotTile(const BatchArgs &A_, const BatchShot &S_, const BatchOp &op_, long long P_)
+        : A(A_), S(S_), op(op_), P(P_), u(batch_buf(A_, S_, op_.a, P_)), up(batch_buf(A_, S_, op_.b, P_)), w(S_.W),
+          ns(op_.ns), inj(GRAD ? S_.rec : S_.src),
+          vals(GRAD ? S_.res + (long long)op_.n * A_.nrec : S_.wavelet + op_.n), vstride(GRAD ? -A_.nrec : 1),
+          gat(S_.rec), rows(S_.dsim + (long long)op_.n * A_.nrec), gmask(GRAD ? 0u : (unsigned)op_.e), G(S_.G),
+          gscale(A_.gscale)
+    {
+    }
+    __device__ const float *level(int j) const { return batch_buf(A, S, op.c[j], P); }
+    __device__ float *dest(int j) const
+    {
+        if (!GRAD) return batch_buf(A, S, op.c[j], P);
+        return j == ns - 1 ? batch_buf(A, S, op.d[0], P) : (j == ns - 2 ? batch_buf(A, S, op.d[1], P) : nullptr);
+    }
+};
+
+// Forward (GRAD false) or adjoint (GRAD true) steps of every shot: one item per tile.
 template <int K, bool GRAD>
-__device__ __forceinline__ void phase_step(const BatchCtx &C, int fin, int prev, int out, int uk, int n, int gin,
-                                           int grow, float *s_row)
+__device__ __forceinline__ void phase_step(const BatchCtx &C, const BatchOp &op, Tile2dShared &S,
+                                           typename Tile2dShared::template Levels<K> &L)
 {
-    const BatchArgs &A = C.A;
-    const int tid = threadIdx.x, nx = C.g.nx;
-    for_items(A, C.st_items + 1, [&](const BatchShot &S, int j) {
-        if (j == C.st_items) {
-            if (grow >= 0) {
-                const float *f = batch_buf(S, gin, A.slot_elems, C.P);
-                for (int r = tid; r < A.nrec; r += 256) S.dsim[(long long)grow * A.nrec + r] = gather_point(S.rec, r, f);
-            }
-            return;
-        }
-        const int tix = j % C.tiles_x, zc = j / C.tiles_x;
-        const int z0 = zc * A.zlen, z1 = min(z0 + A.zlen, C.g.nz);
-        float *f = batch_buf(S, out, A.slot_elems, C.P);
-        const float *u = GRAD ? batch_buf(S, uk, A.slot_elems, C.P) : nullptr;
-        march2d<K, GRAD, kOT2>(C.g, batch_buf(S, fin, A.slot_elems, C.P), batch_buf(S, prev, A.slot_elems, C.P), f,
-                               S.W, u, nullptr, nullptr, GRAD ? S.G : nullptr, GRAD ? A.gscale : 0.0, tix, z0, z1,
-                               s_row);
-        __syncthreads();
-        const Sparse &sp = GRAD ? S.rec : S.src;
-        const int x0 = tix * 256, x1 = min(x0 + 256, nx);
-        for (int i = tid; i < sp.npts; i += 256) {
-            const int p = sp.s_pts[i];
-            const int z = p / nx, x = p - z * nx;
-            if (z < z0 || z >= z1 || x < x0 || x >= x1) continue;
-            if constexpr (GRAD)
-                inject_point<true>(C.g, sp, i, p, x, 0, z, S.res + (long long)n * A.nrec, S.W, f, u, S.G, p,
-                                   A.gscale);
-            else
-                inject_point<false>(C.g, sp, i, p, x, 0, z, S.wavelet + n, S.W, f, nullptr, nullptr, p, 0.0);
-        }
+    const int core = kTileRegion - 2 * tile2d_halo(K, op.ns);
+    const int tx = (C.g.nx + core - 1) / core, tz = (C.g.nz + core - 1) / core;
+    for_items(C.A, tx * tz, [&](const BatchShot &shot, int j) {
+        const ShotTile<GRAD> T(C.A, shot, op, C.P);
+        tile2d<K, GRAD, kBatchRows>(C.g, T, j % tx, j / tx, S, L);
+        __syncthreads();   // the next tile reuses the arrays
     });
+}
+
+// As for_items, an item for each group of 256 lanes; every group makes as many passes (the
+// items hold workgroup barriers), on is false in those it has no item for.
+template <typename Body>
+__device__ __forceinline__ void for_group_items(const BatchArgs &A, int per, Body body)
+{
+    const int items = per * A.nshots;
+    for (int i0 = blockIdx.x * kGroups; i0 < items; i0 += gridDim.x * kGroups) {
+        const int it = i0 + (int)(threadIdx.x >> 8);
+        const bool on = it < items;
+        const int si = on ? it / per : 0;
+        body(A.shots[si], on ? it - si * per : 0, on);
+    }
 }
 
 // One workgroup per shot: the receivers of `gin` into data row `grow`.
@@ -200,25 +215,26 @@ __device__ __forceinline__ void phase_gather(const BatchCtx &C, int gin, int gro
 {
     const BatchArgs &A = C.A;
     for_items(A, 1, [&](const BatchShot &S, int) {
-        const float *f = batch_buf(S, gin, A.slot_elems, C.P);
-        for (int r = threadIdx.x; r < A.nrec; r += 256) S.dsim[(long long)grow * A.nrec + r] = gather_point(S.rec, r, f);
+        const float *f = batch_buf(A, S, gin, C.P);
+        for (int r = threadIdx.x; r < A.nrec; r += kBatchThreads) S.dsim[(long long)grow * A.nrec + r] = gather_point(S.rec, r, f);
     });
 }
 
+// s_scan, s_words and s_one are the group's own.
 __device__ __forceinline__ void phase_encode(const BatchCtx &C, const BatchOp &op, bool emit, unsigned *s_scan,
                              unsigned long long *s_words, unsigned long long *s_one)
 {
     const BatchArgs &A = C.A;
     const CodecDims &cd = C.cd;
     const long long nch = C.nch;
-    const int tid = threadIdx.x;
-    for_items(A, (int)(op.b != kBufNone ? 2 * nch : nch), [&](const BatchShot &S, int j) {
+    const int tid = threadIdx.x & 255;
+    for_group_items(A, (int)(op.ns * nch), [&](const BatchShot &S, int j, bool on) {
         const int f = (int)(j / nch);
         const long long c = j - (long long)f * nch;
-        const float *field = batch_buf(S, op.a, A.slot_elems, C.P);
-        const float *sub = f == 1 ? batch_buf(S, op.b, A.slot_elems, C.P) : nullptr;
+        const float *field = batch_buf(A, S, op.c[f], C.P);
+        const float *sub = batch_buf(A, S, op.d[f], C.P);
         const long long b = c * kBlocksPerChunk + tid;
-        const bool valid = b < cd.nblocks;
+        const bool valid = on && b < cd.nblocks;
         float v[16];
         if (valid) {
             if (C.vec) load_block2<true>(field, sub, cd, b, v);
@@ -234,49 +250,49 @@ __device__ __forceinline__ void phase_encode(const BatchCtx &C, const BatchOp &o
         unsigned total_bits;
         const unsigned incl = block_scan(s_scan, nbits, total_bits);
         const uint32_t chunk_words = (total_bits + 63u) / 64u;
-        __syncthreads();
         if (!emit) {
-            if (!blk.finite) atomicOr(S.err, 2u);
-            if (tid == 0) S.chunk_words[(long long)f * nch + c] = chunk_words;
+            if (on && !blk.finite) atomicOr(S.err, 2u);
+            if (on && tid == 0) S.chunk_words[(long long)f * nch + c] = chunk_words;
             return;
         }
-        // the stream of field f starts at its base; the second field's base follows the
-        // first stream, rounded up to 256 bytes
-        const unsigned long long words0 = block_sum_words(S.chunk_words, nch, s_one);
-        uint64_t base = S.offs[op.d];
-        if (f == 1) base += (cd.prefix_bytes + 8ull * words0 + 255ull) & ~255ull;
+        // the first field's stream starts at its offset word, each other one where the one
+        // before it ends, rounded up to 256 bytes
+        uint64_t base = S.offs[op.x[0]];
+        unsigned long long fwords = 0;
+        for (int q = 0; q < op.ns; ++q) {
+            const unsigned long long words = block_sum_words(S.chunk_words + q * nch, nch, s_one);
+            if (q < f) base += (cd.prefix_bytes + 8ull * words + 255ull) & ~255ull;
+            if (q == f) fwords = words;
+        }
         const unsigned long long excl = block_sum_words(S.chunk_words + (long long)f * nch, c, s_one);
-        const unsigned long long fwords = f == 0 ? words0 : block_sum_words(S.chunk_words + nch, nch, s_one);
         const uint64_t cap = S.arena_bytes;
-        const bool prefix_fits = base + (uint64_t)cd.prefix_bytes <= cap;
+        const bool prefix_fits = on && base + (uint64_t)cd.prefix_bytes <= cap;
         const bool fits = prefix_fits && base + (uint64_t)cd.prefix_bytes + (excl + chunk_words) * 8ull <= cap;
         uint8_t *hdr = S.arena + base;
         uint64_t *chunk_off = (uint64_t *)(hdr + 64);
         uint16_t *lens = (uint16_t *)(hdr + 64 + 8 * nch);
         if (valid && prefix_fits) lens[b] = (uint16_t)nbits;
         if (tid == 0 && prefix_fits) chunk_off[c] = excl;
-        if (tid == 0 && !fits) atomicOr(S.err, 4u);
+        if (on && tid == 0 && !fits) atomicOr(S.err, 4u);
         unsigned long long *data = (unsigned long long *)(hdr + cd.prefix_bytes) + excl;
         const unsigned excl_bits = incl - nbits;
-        if (fits && chunk_words <= (uint32_t)kLdsWords) {
-            for (uint32_t q = tid; q < chunk_words; q += 256) s_words[q] = 0ull;
-            __syncthreads();
-            if (valid) {
-                auto sink = [&](long long w, unsigned long long bits) { atomicOr(&s_words[w], bits); };
-                blk.emit((long long)excl_bits, sink, m_lo, m_hi);
-            }
-            __syncthreads();
-            for (uint32_t q = tid; q < chunk_words; q += 256) data[q] = s_words[q];
-        } else if (fits) {
-            for (uint32_t q = tid; q < chunk_words; q += 256) data[q] = 0ull;
-            __syncthreads();
-            if (valid) {
-                auto sink = [&](long long w, unsigned long long bits) { atomicOr(&data[w], bits); };
-                blk.emit((long long)excl_bits, sink, m_lo, m_hi);
-            }
+        const bool staged = fits && chunk_words <= (uint32_t)kLdsWords;
+        unsigned long long *words = staged ? s_words : data;
+        if (fits)
+            for (uint32_t q = tid; q < chunk_words; q += 256) words[q] = 0ull;
+        __syncthreads();
+        if (valid && staged) {
+            auto sink = [&](long long w, unsigned long long bits) { atomicOr(&s_words[w], bits); };
+            blk.emit((long long)excl_bits, sink, m_lo, m_hi);
+        } else if (valid && fits) {
+            auto sink = [&](long long w, unsigned long long bits) { atomicOr(&data[w], bits); };
+            blk.emit((long long)excl_bits, sink, m_lo, m_hi);
         }
         __syncthreads();
-        if (c == nch - 1 && tid == 0) {
+        if (staged)
+            for (uint32_t q = tid; q < chunk_words; q += 256) data[q] = s_words[q];
+        __syncthreads();
+        if (on && c == nch - 1 && tid == 0) {
             const unsigned long long total = (unsigned long long)cd.prefix_bytes + 8ull * fwords;
             if (prefix_fits) {
                 uint32_t *h32 = (uint32_t *)hdr;
@@ -297,9 +313,8 @@ __device__ __forceinline__ void phase_encode(const BatchCtx &C, const BatchOp &o
                 for (long long q = lb; q < cd.prefix_bytes; ++q) hdr[q] = 0;
             }
             const unsigned long long nxt = base + ((total + 255ull) & ~255ull);
-            // next offset: after a single field at d+2; of two, the first ends at d+1
-            S.offs[op.d + ((op.b != kBufNone && f == 0) ? 1 : 2)] = nxt;
-            if (f == 0 && op.n >= 0) S.sizes[op.n] = total;
+            S.offs[f + 1 < op.ns ? op.x[f + 1] : op.n] = nxt;
+            if (op.y[f] >= 0) S.sizes[op.y[f]] = total;
             atomicAdd(&S.stats[0], total);
             atomicMax(&S.stats[1], nxt);
         }
@@ -311,43 +326,37 @@ __device__ __forceinline__ void phase_decode(const BatchCtx &C, const BatchOp &o
     const BatchArgs &A = C.A;
     const CodecDims &cd = C.cd;
     const long long nch = C.nch;
-    const int tid = threadIdx.x;
-    for_items(A, (int)nch, [&](const BatchShot &S, int j) {
-        float *field = batch_buf(S, op.a, A.slot_elems, C.P);
-        const float *sub = op.b != kBufNone ? batch_buf(S, op.b, A.slot_elems, C.P) : nullptr;
-        const long long c = j;
+    const int tid = threadIdx.x & 255;
+    for_group_items(A, (int)(op.ns * nch), [&](const BatchShot &S, int j, bool on) {
+        const int f = (int)(j / nch);
+        float *field = batch_buf(A, S, op.c[f], C.P);
+        const float *sub = batch_buf(A, S, op.d[f], C.P);
+        const long long c = j - (long long)f * nch;
         const long long b = c * kBlocksPerChunk + tid;
-        const bool valid = b < cd.nblocks;
-        const uint64_t boff = S.offs[op.d];
+        const bool valid = on && b < cd.nblocks;
+        const uint64_t boff = S.offs[op.x[f]];
         const uint64_t cap = S.arena_bytes;
-        if (boff + (uint64_t)cd.prefix_bytes > cap) {
-            // a stream outside the arena (an overflowed store) decodes to zeros, as in the
-            // solo decoder
-            if (valid) {
-                float zero[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) zero[q] = 0.0f;
-                if (C.vec) store_block<2, true>(field, sub, cd.dims, cd.pitch, cd.nb, b, zero);
-                else store_block<2, false>(field, sub, cd.dims, cd.pitch, cd.nb, b, zero);
-            }
-            return;
-        }
-        const uint8_t *hdr = S.arena + boff;
+        // a stream outside the arena (an overflowed store) decodes to zeros, as in the solo decoder
+        const bool fits = boff + (uint64_t)cd.prefix_bytes <= cap;
+        const uint8_t *hdr = S.arena + (fits ? boff : 0);
         const uint64_t *chunk_off = (const uint64_t *)(hdr + 64);
         const uint16_t *lens = (const uint16_t *)(hdr + 64 + 8 * nch);
         const unsigned long long *data = (const unsigned long long *)(hdr + cd.prefix_bytes);
-        long long nwords = (long long)*(const unsigned long long *)(hdr + 48);
-        const long long maxw = (long long)((cap - boff - (uint64_t)cd.prefix_bytes) / 8);
-        nwords = nwords < maxw ? nwords : maxw;
-        const double tol = *(const double *)(hdr + 24);
-        int te;
-        frexp(tol, &te);
-        const int minexp = te - 1;
-        const unsigned nbits = valid ? lens[b] : 0u;
+        long long nwords = 0, cbase = 0;
+        int minexp = 0;
+        if (fits) {
+            nwords = (long long)*(const unsigned long long *)(hdr + 48);
+            const long long maxw = (long long)((cap - boff - (uint64_t)cd.prefix_bytes) / 8);
+            nwords = nwords < maxw ? nwords : maxw;
+            int te;
+            frexp(*(const double *)(hdr + 24), &te);
+            minexp = te - 1;
+            cbase = (long long)chunk_off[c];
+            cbase = cbase < 0 ? 0 : (cbase > nwords ? nwords : cbase);
+        }
+        const unsigned nbits = valid && fits ? lens[b] : 0u;
         unsigned total_bits;
         const unsigned incl = block_scan(s_scan, nbits, total_bits);
-        long long cbase = (long long)chunk_off[c];
-        cbase = cbase < 0 ? 0 : (cbase > nwords ? nwords : cbase);
         const long long cw = ((long long)total_bits + 63) / 64 + 1;
         const bool staged = cw <= kDecLdsWords;
         if (staged) {
@@ -358,11 +367,17 @@ __device__ __forceinline__ void phase_decode(const BatchCtx &C, const BatchOp &o
         }
         __syncthreads();
         if (valid) {
-            const long long rel = (long long)(incl - nbits);
-            BitReader rd = staged ? BitReader{s_words, cw, 0, 0ull, 0ull, 0} : BitReader{data, nwords, 0, 0ull, 0ull, 0};
-            rd.init(staged ? rel : cbase * 64 + rel);
             float out[16];
-            decode_block<2>(rd, minexp, out);
+            if (fits) {
+                const long long rel = (long long)(incl - nbits);
+                BitReader rd = staged ? BitReader{s_words, cw, 0, 0ull, 0ull, 0}
+                                      : BitReader{data, nwords, 0, 0ull, 0ull, 0};
+                rd.init(staged ? rel : cbase * 64 + rel);
+                decode_block<2>(rd, minexp, out);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 16; ++q) out[q] = 0.0f;
+            }
             if (C.vec) store_block<2, true>(field, sub, cd.dims, cd.pitch, cd.nb, b, out);
             else store_block<2, false>(field, sub, cd.dims, cd.pitch, cd.nb, b, out);
         }
@@ -372,15 +387,17 @@ __device__ __forceinline__ void phase_decode(const BatchCtx &C, const BatchOp &o
 
 // residual r = d_sim - d_obs and its partial sums of r^2 (the solo misfit's blocks and
 // order), plus the finiteness check of the last forward state (field a)
+// s_red is the group's own.
 __device__ __forceinline__ void phase_residual(const BatchCtx &C, int ufield, double *s_red)
 {
     const BatchArgs &A = C.A;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 255;
     const int nfin = (int)((C.P + kCopyItem - 1) / kCopyItem);
-    for_items(A, kBatchParts + nfin, [&](const BatchShot &S, int j) {
-        if (j < kBatchParts) {
+    for_group_items(A, kBatchParts + nfin, [&](const BatchShot &S, int j, bool on) {
+        const bool part = on && j < kBatchParts;
+        double acc = 0.0;
+        if (part) {
             const long long n = (long long)(A.nt + 1) * A.nrec;
-            double acc = 0.0;
             for (long long e = (long long)j * 256 + tid; e < n; e += (long long)kBatchParts * 256) {
                 if (e < A.nrec) {
                     S.res[e] = 0.0f;
@@ -390,38 +407,39 @@ __device__ __forceinline__ void phase_residual(const BatchCtx &C, int ufield, do
                 S.res[e] = (float)r;
                 acc += r * r;
             }
-            s_red[tid] = acc;
-            __syncthreads();
-            for (int sft = 128; sft > 0; sft >>= 1) {
-                if (tid < sft) s_red[tid] += s_red[tid + sft];
-                __syncthreads();
-            }
-            if (tid == 0) S.partials[j] = s_red[0];
-            __syncthreads();
-        } else {
-            const float *u = batch_buf(S, ufield, A.slot_elems, C.P);
+        } else if (on) {
+            const float *u = batch_buf(A, S, ufield, C.P);
             const long long e0 = (long long)(j - kBatchParts) * kCopyItem, e1 = min(e0 + kCopyItem, C.P);
             bool bad = false;
             for (long long e = e0 + tid; e < e1; e += 256) bad |= !isfinite(u[e]);
             if (bad) atomicOr(S.err, 8u);
         }
-    });
-}
-
-// phi = 1/2 sum of the partials (the solo final sum's order)
-__device__ __forceinline__ void phase_misfit(const BatchCtx &C, double *s_red)
-{
-    const int tid = threadIdx.x;
-    for_items(C.A, 1, [&](const BatchShot &S, int) {
-        double acc = 0.0;
-        for (int q = tid; q < kBatchParts; q += 256) acc += S.partials[q];
         s_red[tid] = acc;
         __syncthreads();
         for (int sft = 128; sft > 0; sft >>= 1) {
             if (tid < sft) s_red[tid] += s_red[tid + sft];
             __syncthreads();
         }
-        if (tid == 0) S.misfit[0] = 0.5 * s_red[0];
+        if (part && tid == 0) S.partials[j] = s_red[0];
+        __syncthreads();
+    });
+}
+
+// phi = 1/2 sum of the partials (the solo final sum's order)
+__device__ __forceinline__ void phase_misfit(const BatchCtx &C, double *s_red)
+{
+    const int tid = threadIdx.x & 255;
+    for_group_items(C.A, 1, [&](const BatchShot &S, int, bool on) {
+        double acc = 0.0;
+        if (on)
+            for (int q = tid; q < kBatchParts; q += 256) acc += S.partials[q];
+        s_red[tid] = acc;
+        __syncthreads();
+        for (int sft = 128; sft > 0; sft >>= 1) {
+            if (tid < sft) s_red[tid] += s_red[tid + sft];
+            __syncthreads();
+        }
+        if (on && tid == 0) S.misfit[0] = 0.5 * s_red[0];
         __syncthreads();
     });
 }
@@ -430,60 +448,54 @@ __device__ __forceinline__ void phase_copy(const BatchCtx &C, int src, int dst)
 {
     const BatchArgs &A = C.A;
     for_items(A, (int)((C.P + kCopyItem - 1) / kCopyItem), [&](const BatchShot &S, int j) {
-        const float *a = batch_buf(S, src, A.slot_elems, C.P);
-        float *b = batch_buf(S, dst, A.slot_elems, C.P);
+        const float *a = batch_buf(A, S, src, C.P);
+        float *b = batch_buf(A, S, dst, C.P);
         const long long e0 = (long long)j * kCopyItem, e1 = min(e0 + kCopyItem, C.P);
-        for (long long e = e0 + threadIdx.x; e < e1; e += 256) b[e] = a[e];
+        for (long long e = e0 + threadIdx.x; e < e1; e += kBatchThreads) b[e] = a[e];
     });
 }
 
 template <int K>
-__global__ __launch_bounds__(256) void batch2d_kernel(BatchArgs A)
+__global__ __launch_bounds__(kBatchThreads) void batch2d_kernel(BatchArgs A)
 {
-    __shared__ unsigned s_scan[4];
-    __shared__ unsigned long long s_words[kDecLdsWords];
-    __shared__ unsigned long long s_one;
-    __shared__ float s_row[256 + 2 * K];
-    __shared__ double s_red[256];
-    const int tiles_x = (A.g.nx + 255) / 256;
-    const BatchCtx C{A, A.g, A.cd, A.g.P, tiles_x, tiles_x * ((A.g.nz + A.zlen - 1) / A.zlen),
-                     A.cd.dims[0] % 4 == 0 && A.cd.pitch % 4 == 0, A.cd.nchunks};
+    // the tile's levels and the codec's words are never live together (a barrier lies between)
+    using Levels = typename Tile2dShared::template Levels<K>;
+    constexpr size_t kCodec = 8 * kDecLdsWords * kGroups;
+    constexpr size_t kPool = sizeof(Levels) > kCodec ? sizeof(Levels) : kCodec;
+    __shared__ __align__(16) unsigned char s_pool[kPool];
+    __shared__ __align__(16) Tile2dShared s_tile;
+    Levels &s_levels = *reinterpret_cast<Levels *>(s_pool);
+    const int grp = threadIdx.x >> 8;
+    unsigned long long *s_words = reinterpret_cast<unsigned long long *>(s_pool) + grp * kDecLdsWords;
+    __shared__ unsigned s_scan_[kGroups][4];
+    __shared__ unsigned long long s_one[kGroups];
+    __shared__ double s_red_[kGroups][256];
+    unsigned *s_scan = s_scan_[grp];
+    double *s_red = s_red_[grp];
+    const BatchCtx C{A, A.g, A.cd, A.g.P, A.cd.dims[0] % 4 == 0 && A.cd.pitch % 4 == 0, A.cd.nchunks};
     __shared__ unsigned s_flag;
     unsigned *err0 = A.shots[0].err;
     auto barrier = [&]() { return grid_barrier(A.bar, (unsigned)A.nwg, A.spin_limit, err0, &s_flag); };
 
     for (int oi = 0; oi < A.nops; ++oi) {
-        const BatchOp op = A.ops[oi];
+        const BatchOp &op = A.ops[oi];
         switch (op.kind) {
-        case kOpFwd: {
-            // step n writes u^{n+1}; its gather (n >= op.e) runs in the next step's phase,
-            // or in a phase of its own after the last step
-            int fin = op.a, prev = op.b, grow = -1, gin = kBufNone;
-            for (int n = op.n; n < op.d; ++n) {
-                const int out = fin == kBufU0 ? kBufU1 : kBufU0;
-                phase_step<K, false>(C, fin, prev, out, kBufNone, n, gin, grow, s_row);
-                if (!barrier()) return;
-                grow = n >= op.e ? n + 1 : -1;
-                gin = out;
-                prev = fin;
-                fin = out;
-            }
-            if (grow >= 0) {
-                phase_gather(C, gin, grow);
-                if (!barrier()) return;
-            }
+        case kOpStep:
+            phase_step<K, false>(C, op, s_tile, s_levels);
+            if (!barrier()) return;
             break;
-        }
         case kOpAdj:
-            phase_step<K, true>(C, op.a, op.b, op.b, op.c, op.n, kBufNone, -1, s_row);
+            phase_step<K, true>(C, op, s_tile, s_levels);
             if (!barrier()) return;
             break;
-        case kOpEncCount:
-            phase_encode(C, op, false, s_scan, s_words, &s_one);
+        case kOpGather:
+            phase_gather(C, op.a, op.n);
             if (!barrier()) return;
             break;
-        case kOpEncEmit:
-            phase_encode(C, op, true, s_scan, s_words, &s_one);
+        case kOpEnc:
+            phase_encode(C, op, false, s_scan, s_words, &s_one[grp]);
+            if (!barrier()) return;
+            phase_encode(C, op, true, s_scan, s_words, &s_one[grp]);
             if (!barrier()) return;
             break;
         case kOpDec:
@@ -514,7 +526,7 @@ int resident_of()
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch2d_kernel<K>, 256, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch2d_kernel<K>, kBatchThreads, 0) != hipSuccess) return 0;
     return cus * per_cu;
 }
 
@@ -523,7 +535,7 @@ int resident_of()
 template <int K>
 hipError_t launch_of(const BatchArgs &A, hipStream_t s)
 {
-    hipLaunchKernelGGL(batch2d_kernel<K>, dim3(A.nwg), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(batch2d_kernel<K>, dim3(A.nwg), dim3(kBatchThreads), 0, s, A);
     return hipGetLastError();
 }
 

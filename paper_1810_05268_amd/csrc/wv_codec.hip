@@ -19,6 +19,8 @@
 //   * chunks start at 64-bit word boundaries and record their word offsets, so the
 //     decoder needs only a per-chunk scan of the 16-bit block lengths and every
 //     block decodes independently.
+#include <algorithm>
+
 #include "wv_codec_dev.h"
 
 namespace wv {
@@ -26,8 +28,8 @@ namespace wv {
 namespace {
 
 struct EncArgs {
-    const float *field;
-    const float *sub;        // nullable: encode field - sub
+    EncJob job[kEncJobs];    // the fields of the launch
+    bool chain[kEncJobs];    // job e starts where job e - 1 ends
     int dims[3];
     int pitch;               // elements between rows of field and sub
     int nb[3];
@@ -37,13 +39,12 @@ struct EncArgs {
     double tol;
     uint8_t *out;
     uint64_t cap;
-    const uint64_t *base;
-    uint64_t *next;
-    uint32_t *words;         // per chunk: its stream words
-    uint64_t *offs;          // per chunk: its first word in the data area
-    unsigned long long *staging;   // nullable: slot_words words per chunk
+    uint32_t *words;         // per job and chunk: its stream words
+    uint64_t *offs;          // per job and chunk: its first word in the data area
+    unsigned long long *staging;   // nullable: slot_words words per job and chunk
+    uint16_t *lens;          // with staging: per job and block, its length (the stream's place for
+                             // them is known after the scan)
     int slot_words;
-    uint64_t *size_out;      // nullable: receives the stream's size in bytes
     unsigned *err;
     unsigned long long *stats;
 };
@@ -53,7 +54,7 @@ struct EncArgs {
 // the caller's local arrays (inside a struct they would be placed in scratch).  Every
 // lane of the workgroup calls it.
 template <int ND, bool VEC>
-__device__ __forceinline__ bool chunk_prepare(const EncArgs &A, long long c, BlockEnc<ND> &blk,
+__device__ __forceinline__ bool chunk_prepare(const EncArgs &A, int job, long long c, BlockEnc<ND> &blk,
                                               uint32_t (&m_lo)[32], uint32_t (&m_hi)[32], unsigned &nbits,
                                               unsigned &excl_bits, unsigned &total_bits, unsigned *s_scan)
 {
@@ -65,7 +66,7 @@ __device__ __forceinline__ bool chunk_prepare(const EncArgs &A, long long c, Blo
         const int bx = (int)(b % A.nb[0]);
         const int by = (int)((b / A.nb[0]) % A.nb[1]);
         const int bz = (int)(b / ((long long)A.nb[0] * A.nb[1]));
-        load_block<ND, VEC>(A.field, A.sub, A.dims, A.pitch, bx, by, bz, v);
+        load_block<ND, VEC>(A.job[job].field, A.job[job].sub, A.dims, A.pitch, bx, by, bz, v);
     } else {
 #pragma unroll
         for (int i = 0; i < S; ++i) v[i] = 0.0f;
@@ -76,19 +77,44 @@ __device__ __forceinline__ bool chunk_prepare(const EncArgs &A, long long c, Blo
     return valid;
 }
 
-// Exclusive scan of the chunk word counts into offs (and the stream's chunk offsets),
+// Sum of w[0..n) over the workgroup's lanes.
+__device__ __forceinline__ unsigned long long wg_total(const uint32_t *w, long long n, unsigned long long *s_scan)
+{
+    unsigned long long v = 0, total;
+    for (long long i = threadIdx.x; i < n; i += 256) v += w[i];
+    (void)wg_scan256(v, s_scan, total);
+    __syncthreads();
+    return total;
+}
+
+// Where job e's stream starts: its own offset word, or the end of the jobs it follows.
+__device__ __forceinline__ uint64_t job_base(const EncArgs &A, int e, unsigned long long *s_scan)
+{
+    int f = e;
+    while (f > 0 && A.chain[f]) --f;
+    uint64_t base = *A.job[f].base;
+    for (; f < e; ++f) {
+        const unsigned long long words = wg_total(A.words + f * A.nchunks, A.nchunks, s_scan);
+        base += ((uint64_t)A.prefix_bytes + 8ull * words + 255ull) & ~255ull;
+    }
+    return base;
+}
+
+// Exclusive scan of job e's chunk word counts into offs (and the stream's chunk offsets),
 // then the header, the stream size and the next free offset; one workgroup.  Each lane
 // sums a run of up to 16 counts held in registers.
-__device__ __forceinline__ void scan_chunks(const EncArgs &A, unsigned long long *s_scan)
+__device__ __forceinline__ void scan_chunks(const EncArgs &A, int e, unsigned long long *s_scan)
 {
     const int tid = threadIdx.x;
     const long long n = A.nchunks;
+    const uint64_t base = job_base(A, e, s_scan);
+    uint64_t *__restrict__ offs = A.offs + e * n;
     const long long per = (n + 1023) / 1024 * 4;   // a multiple of 4: whole uint4 loads
     const long long i0 = min((long long)tid * per, n), i1 = min(i0 + per, n);
-    const uint32_t *__restrict__ words = A.words;
+    const uint32_t *__restrict__ words = A.words + e * n;
     constexpr int kReg = 16;
     uint32_t wr[kReg];
-    const bool in_reg = per <= kReg && i1 - i0 == per;
+    const bool in_reg = per <= kReg && i1 - i0 == per && (e * n) % 4 == 0;
     unsigned long long part = 0;
     if (in_reg) {
         const uint4 *w4 = reinterpret_cast<const uint4 *>(words + i0);   // 16-byte aligned
@@ -107,7 +133,6 @@ __device__ __forceinline__ void scan_chunks(const EncArgs &A, unsigned long long
     }
     unsigned long long data_words;
     unsigned long long run = wg_scan256(part, s_scan, data_words) - part;
-    const uint64_t base = *A.base;
     const bool prefix_fits = base + (uint64_t)A.prefix_bytes <= A.cap;
     uint8_t *hdr = A.out + base;
     uint64_t *chunk_off = (uint64_t *)(hdr + kHdr);
@@ -115,13 +140,13 @@ __device__ __forceinline__ void scan_chunks(const EncArgs &A, unsigned long long
 #pragma unroll
         for (int k = 0; k < kReg; ++k)
             if (k < per) {
-                A.offs[i0 + k] = run;
+                offs[i0 + k] = run;
                 if (prefix_fits) chunk_off[i0 + k] = run;
                 run += wr[k];
             }
     } else {
         for (long long i = i0; i < i1; ++i) {
-            A.offs[i] = run;
+            offs[i] = run;
             if (prefix_fits) chunk_off[i] = run;
             run += words[i];
         }
@@ -149,14 +174,13 @@ __device__ __forceinline__ void scan_chunks(const EncArgs &A, unsigned long long
         for (long long i = lb; i < A.prefix_bytes; ++i) hdr[i] = 0;
     }
     const unsigned long long nxt = base + ((total + 255ull) & ~255ull);
-    *A.next = nxt;
-    if (A.size_out) *A.size_out = total;
+    *A.job[e].next = nxt;
+    if (A.job[e].size_out) *A.job[e].size_out = total;
     atomicAdd(&A.stats[0], total);
     atomicMax(&A.stats[1], nxt);
 }
 
-// Pass 1, one workgroup per chunk: the block lengths (into the stream's prefix), the
-// chunk's word count, and, when it fits a staging slot, the chunk's bits, assembled in
+// Pass 1, one workgroup per chunk (and field): the block lengths, the chunk's word count, and, when it fits a staging slot, the chunk's bits, assembled in
 // LDS at chunk-local positions.  Chunks are independent: no workgroup waits for another.
 template <int ND, bool VEC>
 __global__ __launch_bounds__(256, 4) void encode_count_kernel(EncArgs A)
@@ -165,20 +189,22 @@ __global__ __launch_bounds__(256, 4) void encode_count_kernel(EncArgs A)
     __shared__ unsigned long long s_bits[kLdsWords];
     const int tid = threadIdx.x;
     const long long c = blockIdx.x;
-    const uint64_t base = *A.base;
-    const bool prefix_fits = base + (uint64_t)A.prefix_bytes <= A.cap;
+    const int e = blockIdx.y;
     BlockEnc<ND> blk;
     uint32_t m_lo[32], m_hi[32];
     unsigned nbits, excl_bits, total_bits;
-    const bool valid = chunk_prepare<ND, VEC>(A, c, blk, m_lo, m_hi, nbits, excl_bits, total_bits, s_scan);
+    const bool valid = chunk_prepare<ND, VEC>(A, e, c, blk, m_lo, m_hi, nbits, excl_bits, total_bits, s_scan);
     if (!blk.finite) atomicOr(A.err, 2u);
     const long long b = c * kBlocksPerChunk + tid;
-    if (valid && prefix_fits) {
-        uint16_t *lens = (uint16_t *)(A.out + base + kHdr + 8 * A.nchunks);
-        lens[b] = (uint16_t)nbits;
+    if (valid && A.staging) {
+        A.lens[e * A.nblocks + b] = (uint16_t)nbits;
+    } else if (valid) {   // a single field, whose place is known
+        const uint64_t base = *A.job[0].base;
+        if (base + (uint64_t)A.prefix_bytes <= A.cap)
+            ((uint16_t *)(A.out + base + kHdr + 8 * A.nchunks))[b] = (uint16_t)nbits;
     }
     const uint32_t cw = (total_bits + 63u) / 64u;
-    if (tid == 0) A.words[c] = cw;
+    if (tid == 0) A.words[e * A.nchunks + c] = cw;
     if (A.staging && cw <= (uint32_t)A.slot_words) {   // else encoded again by pass 3
         for (uint32_t i = tid; i < cw; i += 256) s_bits[i] = 0ull;
         __syncthreads();
@@ -187,18 +213,18 @@ __global__ __launch_bounds__(256, 4) void encode_count_kernel(EncArgs A)
             blk.emit((long long)excl_bits, sink, m_lo, m_hi);
         }
         __syncthreads();
-        unsigned long long *slot = A.staging + c * (long long)A.slot_words;
+        unsigned long long *slot = A.staging + (e * A.nchunks + c) * (long long)A.slot_words;
         for (uint32_t i = tid; i < cw; i += 256) slot[i] = s_bits[i];
     }
 }
 
-// Pass 2, one workgroup: the offsets scan (a kernel of its own: finishing pass 1 with a
+// Pass 2, one workgroup per field: the offsets scan (a kernel of its own: finishing pass 1 with a
 // last-workgroup scan needs an agent-scope release in every workgroup, each an L2
 // write-back, which cost more than this launch).
 __global__ __launch_bounds__(256) void encode_scan_kernel(EncArgs A)
 {
     __shared__ unsigned long long s_scan64[4];
-    scan_chunks(A, s_scan64);
+    scan_chunks(A, blockIdx.x, s_scan64);
 }
 
 // Pass 3, one workgroup per chunk: a staged chunk is copied to its offset; a chunk too
@@ -209,20 +235,25 @@ __global__ __launch_bounds__(256) void encode_place_kernel(EncArgs A)
     __shared__ unsigned s_scan[4];
     const int tid = threadIdx.x;
     const long long c = blockIdx.x;
-    const uint64_t base = *A.base;
-    const uint32_t cw = A.words[c];
-    const unsigned long long off = A.offs[c];
+    const int e = blockIdx.y;
+    const uint64_t base = *A.job[e].base;   // pass 2 has written the bases that follow another field
+    const uint32_t cw = A.words[e * A.nchunks + c];
+    const unsigned long long off = A.offs[e * A.nchunks + c];
+    if (A.staging && base + (uint64_t)A.prefix_bytes <= A.cap) {
+        const long long b = c * kBlocksPerChunk + tid;
+        if (b < A.nblocks) ((uint16_t *)(A.out + base + kHdr + 8 * A.nchunks))[b] = A.lens[e * A.nblocks + b];
+    }
     if (base + (uint64_t)A.prefix_bytes + (off + cw) * 8ull > A.cap) return;   // flagged by pass 2
     unsigned long long *data = (unsigned long long *)(A.out + base + A.prefix_bytes) + off;
     if (A.staging && cw <= (uint32_t)A.slot_words) {
-        const unsigned long long *slot = A.staging + c * (long long)A.slot_words;
+        const unsigned long long *slot = A.staging + (e * A.nchunks + c) * (long long)A.slot_words;
         for (uint32_t i = tid; i < cw; i += 256) data[i] = slot[i];
         return;
     }
     BlockEnc<ND> blk;
     uint32_t m_lo[32], m_hi[32];
     unsigned nbits, excl_bits, total_bits;
-    const bool valid = chunk_prepare<ND, VEC>(A, c, blk, m_lo, m_hi, nbits, excl_bits, total_bits, s_scan);
+    const bool valid = chunk_prepare<ND, VEC>(A, e, c, blk, m_lo, m_hi, nbits, excl_bits, total_bits, s_scan);
     for (uint32_t i = tid; i < cw; i += 256) data[i] = 0ull;
     __syncthreads();
     if (valid) {
@@ -232,11 +263,9 @@ __global__ __launch_bounds__(256) void encode_place_kernel(EncArgs A)
 }
 
 struct DecArgs {
-    const float *sub;        // nullable: store sub - decoded
+    DecJob job[kEncJobs];
     const uint8_t *in;
-    const uint64_t *base;
     uint64_t cap;        // bytes readable from `in`
-    float *field;
     int dims[3];
     int pitch;           // elements between rows of the field
     int nb[3];
@@ -253,7 +282,9 @@ __global__ __launch_bounds__(256) void decode_kernel(DecArgs A)
     const long long c = blockIdx.x;
     const long long b = c * kBlocksPerChunk + tid;
     const bool valid = b < A.nblocks;
-    const uint64_t boff = A.base ? *A.base : 0ull;
+    const float *sub = A.job[blockIdx.y].sub;
+    float *field = A.job[blockIdx.y].field;
+    const uint64_t boff = A.job[blockIdx.y].base ? *A.job[blockIdx.y].base : 0ull;
     if (boff + (uint64_t)A.prefix_bytes > A.cap) {
         // stream outside the readable range (an overflowed store): decode zeros
         if (valid) {
@@ -267,7 +298,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecArgs A)
                         const int x = 4 * bx + i, y = 4 * by + j, z = 4 * bz + k;
                         if (x < A.dims[0] && y < A.dims[1] && z < nzz) {
                             const long long p = ((long long)z * A.dims[1] + y) * A.pitch + x;
-                            A.field[p] = A.sub ? A.sub[p] : 0.0f;
+                            field[p] = sub ? sub[p] : 0.0f;
                         }
                     }
         }
@@ -310,7 +341,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecArgs A)
     rd.init(staged ? rel : cbase * 64 + rel);
     float out[S];
     decode_block<ND>(rd, minexp, out);
-    store_block<ND, VEC>(A.field, A.sub, A.dims, A.pitch, A.nb, b, out);
+    store_block<ND, VEC>(field, sub, A.dims, A.pitch, A.nb, b, out);
 }
 
 }  // namespace
@@ -339,21 +370,29 @@ size_t codec_max_bytes(const CodecDims &cd)
     return (size_t)(cd.prefix_bytes + 8 * words);
 }
 
-size_t encode_work_bytes(const CodecDims &cd, bool staged)
+namespace {
+
+size_t pad256(size_t v) { return (v + 255) / 256 * 256; }
+
+}  // namespace
+
+size_t encode_work_bytes(const CodecDims &cd, bool staged, int jobs)
 {
-    const size_t n = (size_t)cd.nchunks;
-    size_t b = (n * 4 + 255) / 256 * 256 + (n * 8 + 255) / 256 * 256;
-    if (staged) b += n * (size_t)kLdsWords * 8;
+    const size_t n = (size_t)cd.nchunks * jobs;
+    size_t b = pad256(n * 4) + pad256(n * 8);
+    if (staged) b += n * (size_t)kLdsWords * 8 + pad256((size_t)cd.nblocks * jobs * 2);
     return b;
 }
 
-hipError_t launch_encode(const CodecDims &cd, const float *field, const float *sub, double tol, uint8_t *out,
-                         uint64_t cap, const uint64_t *base, uint64_t *next, uint8_t *work, bool staged,
-                         unsigned *err, unsigned long long *stats, hipStream_t s, uint64_t *size_out)
+hipError_t launch_encode(const CodecDims &cd, const EncJob *jobs, int njobs, double tol, uint8_t *out, uint64_t cap,
+                         uint8_t *work, bool staged, unsigned *err, unsigned long long *stats, hipStream_t s)
 {
+    if (njobs < 1 || njobs > kEncJobs || (!staged && njobs != 1)) return hipErrorInvalidValue;
     EncArgs A{};
-    A.field = field;
-    A.sub = sub;
+    for (int e = 0; e < njobs; ++e) {
+        A.job[e] = jobs[e];
+        A.chain[e] = e > 0 && jobs[e].base == jobs[e - 1].next;
+    }
     for (int a = 0; a < 3; ++a) {
         A.dims[a] = cd.dims[a];
         A.nb[a] = cd.nb[a];
@@ -369,20 +408,19 @@ hipError_t launch_encode(const CodecDims &cd, const float *field, const float *s
     A.tol = tol;
     A.out = out;
     A.cap = cap;
-    A.base = base;
-    A.next = next;
-    const size_t n = (size_t)cd.nchunks;
+    const size_t n = (size_t)cd.nchunks * njobs;
     A.words = reinterpret_cast<uint32_t *>(work);
-    A.offs = reinterpret_cast<uint64_t *>(work + (n * 4 + 255) / 256 * 256);
-    A.staging = staged ? reinterpret_cast<unsigned long long *>(work + (n * 4 + 255) / 256 * 256 +
-                                                                 (n * 8 + 255) / 256 * 256)
-                       : nullptr;
-    A.slot_words = staged ? kLdsWords : 0;
-    A.size_out = size_out;
+    A.offs = reinterpret_cast<uint64_t *>(work + pad256(n * 4));
+    if (staged) {
+        uint8_t *slots = work + pad256(n * 4) + pad256(n * 8);
+        A.staging = reinterpret_cast<unsigned long long *>(slots);
+        A.lens = reinterpret_cast<uint16_t *>(slots + n * (size_t)kLdsWords * 8);
+        A.slot_words = kLdsWords;
+    }
     A.err = err;
     A.stats = stats;
     const bool vec = cd.dims[0] % 4 == 0 && cd.pitch % 4 == 0;
-    const dim3 grid((unsigned)cd.nchunks);
+    const dim3 grid((unsigned)cd.nchunks, (unsigned)njobs);
     if (cd.ndim == 3) {
         if (vec) hipLaunchKernelGGL((encode_count_kernel<3, true>), grid, dim3(256), 0, s, A);
         else hipLaunchKernelGGL((encode_count_kernel<3, false>), grid, dim3(256), 0, s, A);
@@ -390,7 +428,7 @@ hipError_t launch_encode(const CodecDims &cd, const float *field, const float *s
         if (vec) hipLaunchKernelGGL((encode_count_kernel<2, true>), grid, dim3(256), 0, s, A);
         else hipLaunchKernelGGL((encode_count_kernel<2, false>), grid, dim3(256), 0, s, A);
     }
-    hipLaunchKernelGGL(encode_scan_kernel, dim3(1), dim3(256), 0, s, A);
+    hipLaunchKernelGGL(encode_scan_kernel, dim3((unsigned)njobs), dim3(256), 0, s, A);
     if (cd.ndim == 3) {
         if (vec) hipLaunchKernelGGL((encode_place_kernel<3, true>), grid, dim3(256), 0, s, A);
         else hipLaunchKernelGGL((encode_place_kernel<3, false>), grid, dim3(256), 0, s, A);
@@ -401,15 +439,14 @@ hipError_t launch_encode(const CodecDims &cd, const float *field, const float *s
     return hipGetLastError();
 }
 
-hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const uint64_t *base, uint64_t cap, float *field,
-                         const float *sub, hipStream_t s)
+hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const DecJob *jobs, int njobs, uint64_t cap,
+                         hipStream_t s)
 {
+    if (njobs < 1 || njobs > kEncJobs) return hipErrorInvalidValue;
     DecArgs A{};
-    A.sub = sub;
+    std::copy(jobs, jobs + njobs, A.job);
     A.in = in;
-    A.base = base;
     A.cap = cap;
-    A.field = field;
     for (int a = 0; a < 3; ++a) {
         A.dims[a] = cd.dims[a];
         A.nb[a] = cd.nb[a];
@@ -419,7 +456,7 @@ hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const uint64_t 
     A.nchunks = cd.nchunks;
     A.prefix_bytes = cd.prefix_bytes;
     const bool vec = cd.dims[0] % 4 == 0 && cd.pitch % 4 == 0;
-    const dim3 grid((unsigned)cd.nchunks);
+    const dim3 grid((unsigned)cd.nchunks, (unsigned)njobs);
     if (cd.ndim == 3) {
         if (vec) hipLaunchKernelGGL((decode_kernel<3, true>), grid, dim3(256), 0, s, A);
         else hipLaunchKernelGGL((decode_kernel<3, false>), grid, dim3(256), 0, s, A);

@@ -208,14 +208,15 @@ struct BitReader {
     }
 };
 
-// Inclusive scan of v over a 256-lane workgroup: shuffles inside each wave, then one
-// exchange of the four wave totals through s_w[0..3].  Returns the lane's inclusive sum
-// and sets total to the workgroup's sum.  Every lane calls it; it holds one barrier, and
-// s_w may be written again only after another barrier of the caller.
+// Inclusive scan of v over 256 lanes (a workgroup, or one of its groups of 256, each with an
+// s_w of its own): shuffles inside each wave, then one exchange of the four wave totals
+// through s_w[0..3].  Returns the lane's inclusive sum and sets total to the group's sum.
+// Every lane of the workgroup calls it; it holds one barrier, and s_w may be written again
+// only after another barrier of the caller.
 template <typename T>
 __device__ __forceinline__ T wg_scan256(T v, T *s_w, T &total)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
     T x = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {

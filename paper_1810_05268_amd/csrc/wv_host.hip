@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "wv_internal.h"
+#include "wv_prog2d.h"
 
 using namespace wv;
 
@@ -310,6 +311,7 @@ struct Layout {
     size_t res, dsim, partials, enc, offs, sizes, arena;
     size_t total;
     size_t arena_bytes;
+    size_t fstride;          // bytes from one array of a ring to the next
     long long nchunks_max;
     int offs_n;
 };
@@ -324,6 +326,8 @@ struct Setup {
     long long P = 0;        // grid points (the caller's dense arrays)
     long long Pf = 0;       // elements of one solver field array (rows pitched, see Grid)
     int ndim = 0, N[3] = {1, 1, 1};
+    // steps run in groups by a program (2-D OT2), not one by one
+    bool prog2d() const { return ndim == 2 && g.time_order != 4; }
     int src_nc = 4, rec_nc = 4;   // corners per source / receiver in the gather tables
     // 3-D: planes of the scatter points, when the steps inject in their own launches (the
     // points in at most kInjPlanes planes; sources: one entry a point)
@@ -740,9 +744,14 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
         return o;
     };
     const size_t fb = (size_t)su.Pf * 4;
+    // 2-D OT2 runs keep rings of levels and of decoded checkpoints (see Prog2d)
+    const bool prog = su.prog2d();
+    const int K = su.g.K;
+    L.fstride = align_up(fb, 256);
     L.bk = take(kBk);
-    L.U0 = take(fb);
-    L.U1 = take(fb);
+    L.U0 = take(prog ? tile2d_ring(K) * L.fstride : fb);
+    if (prog) L.U1 = L.U0 + L.fstride;
+    else L.U1 = take(fb);
     L.W = take(fb);
     L.Z = take(fb);
     const bool ot4 = su.g.time_order == 4;
@@ -762,9 +771,10 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     }
     const size_t data_bytes = (size_t)(m->nt + 1) * geo->nrec * 4;
     if (op == WV_OP_GRADIENT) {
-        L.L0 = take(fb);
-        L.L1 = take(fb);
-        L.UB = take(fb);
+        L.L0 = take(prog ? 4 * L.fstride : fb);
+        if (prog) L.L1 = L.L0 + L.fstride;
+        else L.L1 = take(fb);
+        L.UB = take(prog ? tile2d_decoded(K) * L.fstride : fb);
         L.DB = take(fb);
         if (ot4) L.VU = take(fb);               // OT4 adjoint: w lap u^k for the gradient term
         // 3-D OT2 adjoint: the gradient term an even step carries to the next one
@@ -775,14 +785,16 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
         const int cdims[3] = {su.g.nx, su.ndim == 3 ? su.g.ny : su.g.nz, su.ndim == 3 ? su.g.nz : 1};
         const CodecDims cd = codec_dims(su.ndim, cdims, su.g.px);
         L.nchunks_max = cd.nchunks;
-        L.enc = take(encode_work_bytes(cd, true));   // the encoder's chunk counts, offsets, slots
+        // the encoder's chunk counts, offsets, block lengths and slots
+        L.enc = take(encode_work_bytes(cd, true, prog ? tile2d_jobs(K) : 1));
         L.offs_n = 2 * (m->nt + 3);
         L.offs = take((size_t)L.offs_n * 8);
         L.sizes = take((size_t)(m->nt + 1) * 8);   // stream bytes of u^k for each stored state k
         L.arena_bytes = align_up(budget, 256);
         L.arena = take(L.arena_bytes);
     }
-    L.total = off;
+    // 2-D tiles read up to three values past an array, the last of which may be the arena's
+    L.total = prog ? off + 256 : off;
     return L;
 }
 
@@ -908,9 +920,11 @@ int start(Dev &d, const wv_model *m, const Setup &su, hipStream_t s)
     // every field array starts at zero: kernels write only the nx valid columns of a
     // pitched row, so the pad columns keep this zero for the whole call (and whole-array
     // scans such as the finiteness check read no stale workspace bytes)
+    // (2-D rows have no pad columns, and a program writes every array before it reads it,
+    // but for the zero field)
     float *const fields[] = {d.Z, d.U[0], d.U[1], d.Lm[0], d.Lm[1], d.UB, d.DB, d.V, d.VU};
     for (float *f : fields)
-        if (f) HIPCHK(launch_fill_f32(f, su.Pf, 0.0f, s));
+        if (f && (f == d.Z || !su.prog2d())) HIPCHK(launch_fill_f32(f, su.Pf, 0.0f, s));
     unsigned e = 0;
     rc = read_err(d, s, &e);
     if (rc) return rc;
@@ -1007,15 +1021,15 @@ struct Fwd {
         int rc;
         LaunchEvents le;
         if (kt && (rc = kt->pair(0, &le))) return rc;
-        // The step's launch injects the source sample and gathers the previous step's
-        // receivers: always in 2-D OT2, in 3-D where the source points lie in few planes
-        // (the gather then too; 2-D OT4 steps keep launches of their own for both).
+        // 3-D: the step's launch gathers the previous step's receivers, and injects the
+        // source sample where its points lie in few planes (2-D OT4 steps keep launches of
+        // their own for both)
         const bool ot4 = su.g.time_order == 4;
-        const bool gfuse = su.ndim == 3 || !ot4, ifuse = su.ndim == 2 ? !ot4 : d.src.np > 0;
+        const bool gfuse = su.ndim == 3, ifuse = d.src.np > 0;
         StepSide inj, gat;
         if (ifuse) {
             inj.inj = &d.src;
-            inj.vals = inj.scale = geo->wavelet + n;
+            inj.scale = geo->wavelet + n;
             inj.plane = d.src_plane;
         }
         if (pend) {
@@ -1051,6 +1065,119 @@ struct Fwd {
 };
 
 double gradient_scale(const wv_model *m) { return -1.0 / (m->dt * m->dt); }
+
+// Runs the steps of a 2-D OT2 program by launches for one shot.
+struct Run2d {
+    Dev &d;
+    const Setup &su;
+    const wv_geom *geo;
+    hipStream_t s;
+    float *data = nullptr;              // d_sim rows (forward steps gather into it)
+    const float *res = nullptr;         // residual rows (adjoint steps inject them)
+    double *G = nullptr;
+    double gscale = 0.0;
+    size_t slot_elems = 0;              // elements of one uncompressed checkpoint
+    const CodecDims *cd = nullptr;
+    double tol = 0.0;
+    ActionTimer *kt = nullptr;          // optional per-launch timing of the stencils
+
+    float *ptr(int id) const
+    {
+        const size_t fs = d.L.fstride / 4;
+        if (id < 0) return nullptr;
+        if (id == kBufZ) return d.Z;
+        if (id == kBufDB) return d.DB;
+        if (id >= kBufSlot)
+            return reinterpret_cast<float *>(d.arena) + (size_t)((id - kBufSlot) / 2 - 1) * slot_elems +
+                   (size_t)(id & 1) * su.Pf;
+        if (id >= kBufUB) return d.UB + (size_t)(id - kBufUB) * fs;
+        if (id >= kBufU) return d.U[0] + (size_t)(id - kBufU) * fs;
+        return d.Lm[0] + (size_t)(id - kBufL) * fs;
+    }
+    int forward(const BatchOp &op)
+    {
+        Tile2dArgs A{};
+        A.u = ptr(op.a);
+        A.up = ptr(op.b);
+        A.w = d.W;
+        A.ns = op.ns;
+        for (int j = 0; j < op.ns; ++j) A.out[j] = ptr(op.c[j]);
+        A.inj = d.src;
+        A.vals = geo->wavelet + op.n;
+        A.vstride = 1;
+        A.gat = d.rec;
+        if (op.e && !data) return WV_EINVAL;   // a program without rows gathers none
+        A.gmask = (unsigned)op.e;
+        A.rows = data ? data + (size_t)op.n * geo->nrec : nullptr;
+        return launch(A, 0);
+    }
+    int adjoint(const BatchOp &op)
+    {
+        Tile2dArgs A{};
+        A.u = ptr(op.a);
+        A.up = ptr(op.b);
+        A.w = d.W;
+        A.ns = op.ns;
+        A.out[op.ns - 1] = ptr(op.d[0]);
+        if (op.ns > 1) A.out[op.ns - 2] = ptr(op.d[1]);
+        for (int j = 0; j < op.ns; ++j) A.uk[j] = ptr(op.c[j]);
+        A.inj = d.rec;
+        A.vals = res + (size_t)op.n * geo->nrec;
+        A.vstride = -(long long)geo->nrec;
+        A.G = G;
+        A.gscale = gscale;
+        return launch(A, 1);
+    }
+    int launch(const Tile2dArgs &A, int kind)
+    {
+        LaunchEvents le;
+        int rc;
+        if (kt && (rc = kt->pair(kind, &le))) return rc;
+        HIPCHK(launch_tile2d(su.g, A, s, le));
+        return WV_OK;
+    }
+    // steps, gathers, copies, encodes and decodes (the misfit is the caller's)
+    int run(const BatchOp &op)
+    {
+        switch (op.kind) {
+        case kOpStep: return forward(op);
+        case kOpAdj: return adjoint(op);
+        case kOpGather:
+            if (!data) return WV_EINVAL;
+            HIPCHK(launch_gather(d.rec, ptr(op.a), data + (size_t)op.n * geo->nrec, s)); return WV_OK;
+        case kOpCopy:
+            HIPCHK(hipMemcpyAsync(ptr(op.b), ptr(op.a), (size_t)su.Pf * 4, hipMemcpyDeviceToDevice, s));
+            return WV_OK;
+        case kOpEnc: {
+            EncJob jobs[kEncJobs];
+            int nj = 0;
+            for (int j = 0; j < op.ns; ++j)
+                if (op.c[j] != kBufNone)
+                    jobs[nj++] = {ptr(op.c[j]), ptr(op.d[j]), d.offs + op.x[j],
+                                  d.offs + (j + 1 < op.ns ? op.x[j + 1] : op.n), op.y[j] >= 0 ? d.sizes + op.y[j] : nullptr};
+            if (nj)
+                HIPCHK(launch_encode(*cd, jobs, nj, tol, d.arena, d.L.arena_bytes, d.enc, true, d.err, d.stats, s));
+            return WV_OK;
+        }
+        case kOpDec: {
+            DecJob jobs[kEncJobs];
+            for (int j = 0; j < op.ns; ++j) jobs[j] = {d.offs + op.x[j], ptr(op.c[j]), ptr(op.d[j])};
+            HIPCHK(launch_decode(*cd, d.arena, jobs, op.ns, d.L.arena_bytes, s));
+            return WV_OK;
+        }
+        default: return WV_EINVAL;
+        }
+    }
+    // the steps a program has collected since the last call
+    int drain(Prog2d &p)
+    {
+        int rc = WV_OK;
+        for (const BatchOp &op : p.ops)
+            if ((rc = run(op))) break;
+        p.ops.clear();
+        return rc;
+    }
+};
 
 }  // namespace
 
@@ -1202,9 +1329,21 @@ int wv_forward(const wv_model *m, const wv_geom *geo, float *data, float *state_
     HIPCHK(launch_fill_f32(data, geo->nrec, 0.0f, s));
     Fwd f{d, su, geo, s};
     f.at(d.Z, d.Z);
-    for (int n = 0; n < m->nt; ++n)
-        if ((rc = f.step(n, data + (size_t)(n + 1) * geo->nrec))) return rc;
-    if ((rc = f.flush())) return rc;
+    if (su.prog2d()) {
+        Prog2d p(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, 1));
+        Run2d run{d, su, geo, s, data};
+        for (int n = 0; n < m->nt; ++n) {
+            p.step(n, true);
+            if ((rc = run.drain(p))) return rc;
+        }
+        p.flush_rows(m->nt);
+        if ((rc = run.drain(p))) return rc;
+        f.at(run.ptr(p.u), run.ptr(p.up));
+    } else {
+        for (int n = 0; n < m->nt; ++n)
+            if ((rc = f.step(n, data + (size_t)(n + 1) * geo->nrec))) return rc;
+        if ((rc = f.flush())) return rc;
+    }
     if (state_out) {
         // pitched solver rows to the caller's dense layout
         const size_t row = (size_t)su.g.nx * 4, pitch = (size_t)su.g.px * 4, rows = (size_t)su.g.ny * su.g.nz;
@@ -1254,11 +1393,103 @@ struct GradRun {
     // size_out (nullable) the stream's bytes
     int encode_field(const float *f, const float *sub, uint64_t *base, uint64_t *next, uint64_t *size_out = nullptr)
     {
-        HIPCHK(launch_encode(cd, f, sub, tol, d.arena, d.L.arena_bytes, base, next, d.enc, true, d.err, d.stats, s,
-                             size_out));
+        const EncJob job{f, sub, base, next, size_out};
+        HIPCHK(launch_encode(cd, &job, 1, tol, d.arena, d.L.arena_bytes, d.enc, true, d.err, d.stats, s));
         return WV_OK;
     }
 };
+
+// The action codes of a schedule, for Prog2d.
+struct ActionCodes {
+    int advance = ADVANCE, store = STORE, restore = RESTORE, reverse = REVERSE;
+};
+
+// A 2-D OT2 reversal: the schedule's program, launch by launch.
+int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const std::vector<char> &need2, int M,
+                ActionTimer &timer)
+{
+    Dev &d = R.d;
+    const int N = R.m->nt;
+    const long long nrec = R.geo->nrec;
+    const bool comp = R.tol > 0;
+    Prog2d p(R.su.g.K, tile2d_choose(R.su.g.K, R.su.g.nx, R.su.g.nz, 1));
+    p.schedule(acts, need2, M, comp, run.data != nullptr, ActionCodes{});
+    if (!p.valid) return WV_EINVAL;
+    R.advances = p.advances;
+    R.stores = p.stores;
+    R.fields = p.fields;
+    R.restores = p.restores;
+    R.reverses = p.reverses;
+    R.decodes = p.decodes;
+    R.max_depth = p.max_depth;
+    int rc = WV_OK;
+    for (BatchOp &op : p.ops) {
+        int kind = ADVANCE;
+        switch (op.kind) {
+        case kOpResid:
+            if (R.optimistic) {
+                unsigned e = 0;
+                if ((rc = read_err(d, run.s, &e))) return rc;
+                if (e & 4u) return WV_EARENA;   // not every state fits: the caller plans from the sizes
+            }
+            if (!R.misfit_mode) continue;
+            HIPCHK(launch_check_finite(run.ptr(op.a), R.su.Pf, d.err, run.s));
+            HIPCHK(launch_residual_misfit(run.data, R.dobs, d.res, (long long)(N + 1) * nrec, nrec, d.partials, kParts,
+                                          d.misfit, run.s));
+            kind = REVERSE;
+            break;
+        case kOpMisfit: continue;
+        case kOpEnc:
+            if (R.optimistic && R.arena_full) {
+                // this attempt will stop: only the profile's samples are still measured
+                for (int j = 0; j < op.ns; ++j)
+                    if (!profile_sample(N, op.y[j])) op.c[j] = kBufNone;
+            }
+            if ((rc = run.run(op))) return rc;
+            if (R.optimistic && !R.arena_full) {
+                const long before = R.opt_stores;
+                R.opt_stores += op.ns;
+                if (R.opt_stores / 128 != before / 128) {
+                    unsigned e = 0;
+                    if ((rc = read_err(d, run.s, &e))) return rc;
+                    if (e & 4u) R.arena_full = true;
+                }
+            }
+            kind = STORE;
+            break;
+        default:
+            if ((rc = run.run(op))) return rc;
+            kind = op.kind == kOpAdj ? REVERSE : (op.kind == kOpDec ? RESTORE : (op.kind == kOpCopy ? STORE : ADVANCE));
+        }
+        if ((rc = timer.mark(kind))) return rc;
+    }
+    return WV_OK;
+}
+
+// The 2-D adjoint of the source path: reverse steps one by one, each level sampled at the sources.
+int run_adjoint_src(GradRun &R, Run2d &run)
+{
+    run.G = nullptr;
+    int lam = 0, lamp = 1, out = 2;
+    for (int k = R.m->nt; k >= 1; --k) {
+        BatchOp op{};
+        op.n = k;
+        op.ns = 1;
+        op.a = kBufL + lam;
+        op.b = kBufL + lamp;
+        op.c[0] = kBufNone;
+        op.d[0] = kBufL + out;
+        int rc = run.adjoint(op);
+        if (rc) return rc;
+        HIPCHK(launch_gather_sum(R.d.src, run.ptr(kBufL + out), R.src_adj + (k - 1), run.s));
+        const int next = 3 - lam - out;
+        lamp = lam;
+        lam = out;
+        out = next;
+        R.reverses++;
+    }
+    return WV_OK;
+}
 
 int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, double *misfit_out)
 {
@@ -1309,6 +1540,12 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
     ktimer.s = s;
     if (ktimer.on) f.kt = &ktimer;
     rc = timer.mark(-1);
+    if (R.su.prog2d()) {
+        Run2d run{d, R.su, R.geo, s, data, res, R.G, gscale, R.S / 4, &R.cd, R.tol, f.kt};
+        if (R.src_adj_mode) rc = run_adjoint_src(R, run);
+        else rc = run_program(R, run, acts, need2, M, timer);
+        acts.clear();
+    }
     for (size_t i = 0; i < acts.size() / 3 && rc == WV_OK; ++i) {
         const int op = acts[3 * i], a = acts[3 * i + 1], b = acts[3 * i + 2];
         bool work = op == ADVANCE || op == REVERSE;   // the action enqueues something
@@ -1321,8 +1558,8 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
                 }
                 if (!hot_db) {
                     // u^{k-1} = u^k - (u^k - u^{k-1})
-                    HIPCHK(launch_decode(R.cd, d.arena, d.offs + 2 * pend_slot + 1, d.L.arena_bytes, d.DB, d.UB,
-                                         s));
+                    const DecJob job{d.offs + 2 * pend_slot + 1, d.DB, d.UB};
+                    HIPCHK(launch_decode(R.cd, d.arena, &job, 1, d.L.arena_bytes, s));
                     hot_db = true;
                     R.decodes++;
                 }
@@ -1404,7 +1641,8 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
                 f.at(d.Z, d.Z);
             } else if (comp) {
                 if (hot_slot != b || hot_k != a) {
-                    HIPCHK(launch_decode(R.cd, d.arena, d.offs + 2 * b, d.L.arena_bytes, d.UB, nullptr, s));
+                    const DecJob job{d.offs + 2 * b, d.UB, nullptr};
+                    HIPCHK(launch_decode(R.cd, d.arena, &job, 1, d.L.arena_bytes, s));
                     hot_slot = b;
                     hot_k = a;
                     hot_db = false;
@@ -1441,24 +1679,21 @@ int run_gradient(GradRun &R, int M, double ratio_planned, wv_stats *stats, doubl
             const float *uk = R.G ? f.u : nullptr;
             LaunchEvents le;
             if ((rc = ktimer.pair(1, &le))) break;
-            // the step's own launch injects the residual row: always in 2-D OT2, in 3-D
-            // where the receivers' points lie in few planes
-            const bool fused = R.su.ndim == 2 ? R.su.g.time_order != 4 : d.rec.np > 0;
+            // 3-D: the step's own launch injects the residual row where the receivers'
+            // points lie in few planes
+            const bool fused = d.rec.np > 0;
             const float *r_row = res + (size_t)a * R.geo->nrec;
             StepSide side;
             if (fused) {
+                // reverse steps go through k = N..1 in order: each sums the next one's
+                // residual samples, the first finds its own summed beforehand
+                if (a == N) HIPCHK(launch_plane_sums(d.rec, r_row, d.rec_plane[a & 1], s));
                 side.inj = &d.rec;
-                side.vals = r_row;
-                if (R.su.ndim == 3) {
-                    // reverse steps go through k = N..1 in order: each sums the next one's
-                    // residual samples, the first finds its own summed beforehand
-                    if (a == N) HIPCHK(launch_plane_sums(d.rec, r_row, d.rec_plane[a & 1], s));
-                    side.plane = d.rec_plane[a & 1];
-                    if (a > 1) {
-                        side.next = &d.rec;
-                        side.next_vals = r_row - R.geo->nrec;
-                        side.next_plane = d.rec_plane[(a - 1) & 1];
-                    }
+                side.plane = d.rec_plane[a & 1];
+                if (a > 1) {
+                    side.next = &d.rec;
+                    side.next_vals = r_row - R.geo->nrec;
+                    side.next_plane = d.rec_plane[(a - 1) & 1];
                 }
             }
             // lam^{k-1} overwrites lam^{k+1}
@@ -1570,8 +1805,20 @@ int probe_ratio(GradRun &R, double *ratio, double *prof)
     HIPCHK(launch_fill_u64(at<uint64_t>(d.base, d.L.bk + kStats), 2, 0, s));
     int rc;
     int next_sample = 1;
+    Prog2d p(R.su.g.K, tile2d_choose(R.su.g.K, R.su.g.nx, R.su.g.nz, 1));
+    Run2d run{d, R.su, R.geo, s};
+    // u^{n+1}; in memory when a sample needs it
+    auto step = [&](int n, bool want) -> int {
+        if (!R.su.prog2d()) return f.step(n, nullptr);
+        p.step(n, false);
+        if (want) p.flush();
+        const int r = run.drain(p);
+        f.at(run.ptr(p.u), run.ptr(p.up));
+        return r;
+    };
     for (int n = 0; n < N; ++n) {
-        if ((rc = f.step(n, nullptr))) return rc;
+        const bool want = n + 1 == N || profile_sample(N, n + 1);
+        if ((rc = step(n, want))) return rc;
         while (next_sample < kProfile && profile_step(N, next_sample) < n + 1) ++next_sample;
         if (next_sample < kProfile && profile_step(N, next_sample) == n + 1) {
             // u^{n+1} at the start of the arena, for its size only
@@ -1703,114 +1950,6 @@ namespace {
 
 constexpr size_t kBatchHdr = 16384;   // barrier counters of the persistent launch, bytes
 
-// program steps for the schedule acts, with the solo executor's bookkeeping (which
-// buffer holds each level, when the second level is decoded, which data rows the first
-// sweep gathers); every shot of the batch runs the same steps
-struct BatchPlan {
-    std::vector<BatchOp> ops;
-    bool valid = true;
-    long advances = 0, stores = 0, restores = 0, reverses = 0, decodes = 0, fields = 0;
-    int max_depth = 0;
-};
-
-BatchPlan build_batch_program(const std::vector<int32_t> &acts, int M, bool comp)
-{
-    BatchPlan B;
-    auto op = [&](int kind, int n, int a, int b, int c, int d, int e) {
-        B.ops.push_back(BatchOp{kind, n, a, b, c, d, e});
-    };
-    const std::vector<char> need2 = second_level_needed(acts, M);
-    std::vector<char> slot2((size_t)M + 2, 0);
-    int u = kBufZ, up = kBufZ;            // buffers of u^n and u^{n-1} (kBufNone: not decoded yet)
-    int hot_slot = -1, hot_k = -1, pend_slot = -1;
-    bool up_pending = false, hot_db = false, residual_ready = false;
-    int gathered = 0, lc = 0;
-    for (size_t i = 0; i < acts.size() / 3; ++i) {
-        const int a = acts[3 * i + 1], b = acts[3 * i + 2];
-        switch (acts[3 * i]) {
-        case ADVANCE:
-            if (up == kBufNone) {   // advancing from a restore: decode the second level now
-                if (!up_pending) {      // cannot happen: the scan above marks these checkpoints
-                    B.ops.clear();
-                    B.valid = false;
-                    return B;
-                }
-                if (!hot_db) {
-                    op(kOpDec, -1, kBufDB, kBufUB, 0, 2 * pend_slot + 1, 0);
-                    hot_db = true;
-                    B.decodes++;
-                }
-                up = kBufDB;
-                up_pending = false;
-            }
-            op(kOpFwd, a, u, up, 0, b, std::max(a, gathered));
-            gathered = std::max(gathered, b);
-            for (int n = a; n < b; ++n) {   // the buffers the steps leave behind
-                const int out = u == kBufU0 ? kBufU1 : kBufU0;
-                up = u;
-                u = out;
-            }
-            B.advances += b - a;
-            break;
-        case STORE:
-            slot2[b] = need2[i];
-            if (need2[i] && up == kBufNone) {   // cannot happen either
-                B.ops.clear();
-                B.valid = false;
-                return B;
-            }
-            if (comp) {
-                op(kOpEncCount, a, u, need2[i] ? up : kBufNone, 0, 2 * b, 0);
-                op(kOpEncEmit, a, u, need2[i] ? up : kBufNone, 0, 2 * b, 0);
-                if (hot_slot == b) hot_slot = -1;
-            } else {
-                op(kOpCopy, -1, u, kBufSlot + 2 * b, 0, 0, 0);
-                if (need2[i]) op(kOpCopy, -1, up, kBufSlot + 2 * b + 1, 0, 0, 0);
-            }
-            B.stores++;
-            B.fields += need2[i] ? 2 : 1;
-            B.max_depth = std::max(B.max_depth, b);
-            break;
-        case RESTORE:
-            up_pending = false;
-            if (b == 0) {
-                u = up = kBufZ;
-            } else if (comp) {
-                if (hot_slot != b || hot_k != a) {
-                    op(kOpDec, -1, kBufUB, kBufNone, 0, 2 * b, 0);
-                    hot_slot = b;
-                    hot_k = a;
-                    hot_db = false;
-                    B.decodes++;
-                }
-                u = kBufUB;
-                up = kBufNone;
-                up_pending = slot2[b] != 0;
-                pend_slot = b;
-            } else {
-                u = kBufSlot + 2 * b;
-                up = slot2[b] ? kBufSlot + 2 * b + 1 : kBufNone;
-            }
-            B.restores++;
-            break;
-        case REVERSE:
-            if (!residual_ready) {
-                op(kOpResid, -1, u, 0, 0, 0, 0);
-                op(kOpMisfit, -1, 0, 0, 0, 0, 0);
-                residual_ready = true;
-            }
-            // lam^{k-1} overwrites lam^{k+1}
-            op(kOpAdj, a, lc ? kBufL1 : kBufL0, lc ? kBufL0 : kBufL1, u, 0, 0);
-            lc ^= 1;
-            B.reverses++;
-            break;
-        default:
-            break;
-        }
-    }
-    return B;
-}
-
 struct BatchShape {
     size_t hdr, desc, ops, shot0, shot_bytes, chunk_off;
     int max_ops;
@@ -1845,7 +1984,7 @@ int batch_setup(int nshots, const wv_model *ms, const wv_geom *gs, size_t budget
     size_t lay = 0;
     for (int i = 0; i < nshots; ++i) lay = std::max(lay, L[i].total);
     B.chunk_off = align_up(lay, 256);
-    B.shot_bytes = align_up(B.chunk_off + (size_t)2 * cd.nchunks * 4, 256);
+    B.shot_bytes = align_up(B.chunk_off + (size_t)tile2d_jobs(su[0].g.K) * cd.nchunks * 4, 256);
     B.total = B.shot0 + (size_t)nshots * B.shot_bytes;
     return WV_OK;
 }
@@ -1896,12 +2035,10 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         if ((rc = start(dv[i], &models[i], su[i], s))) return rc;
         Dev &d = dv[i];
         BatchShot &S = shots[i];
-        S.U[0] = d.U[0];
-        S.U[1] = d.U[1];
+        S.U = d.U[0];
         S.UB = d.UB;
         S.DB = d.DB;
-        S.Lm[0] = d.Lm[0];
-        S.Lm[1] = d.Lm[1];
+        S.Lm = d.Lm[0];
         S.Z = d.Z;
         S.W = d.W;
         S.wavelet = geoms[i].wavelet;
@@ -1966,22 +2103,16 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
     A.nt = N;
     // Launch shape.  Every workgroup takes part in every grid barrier, whose cost grows
     // with the number of arrivals, so the grid is no larger than the widest phase needs:
-    // a step phase takes one item per z-chunk of a 256-column tile (16 rows, halved down
-    // to 4 while the batch has fewer chunks than twice the CU count) plus one gather item
-    // per shot, and the codec phases one item per 256-block chunk and field.  Phases
-    // with more items loop over them.
+    // a step phase takes one item per tile, the codec phases one per 256-block chunk and
+    // field.  Phases with more items loop over them.
+    const int steps = tile2d_choose(g.K, g.nx, g.nz, nshots);
     {
-        int cus = 0, dev = 0;
-        HIPCHK(hipGetDevice(&dev));
-        HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        const long long tiles_x = (g.nx + 255) / 256;
-        auto chunks = [&](int zl) { return (long long)nshots * tiles_x * ((g.nz + zl - 1) / zl); };
-        int zl = 16;
-        while (zl > 4 && chunks(zl) < 2LL * cus) zl /= 2;
-        A.zlen = zl;
-        const long long widest = std::max(chunks(zl) + nshots, (long long)nshots * 2 * cd.nchunks);
+        const int K = g.K, core = kTileRegion - 2 * tile2d_halo(K, steps);
+        const long long tiles = (long long)((g.nx + core - 1) / core) * ((g.nz + core - 1) / core);
+        const long long widest = nshots * std::max(tiles, tol > 0 ? tile2d_jobs(K) * cd.nchunks / 2 : 1LL);
         A.nwg = (int)std::min<long long>(nwg, std::max<long long>(widest, 8));
     }
+    A.fstride = (long long)(L[0].fstride / 4);
     A.slot_elems = (long long)su[0].Pf * 2;
     A.bar = reinterpret_cast<unsigned *>(base + B.hdr);
     // WV_BATCH_SPIN_LIMIT (for tests of the fallback) lowers the barrier's poll bound
@@ -1998,7 +2129,8 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         if (M < 1) return WV_EBUDGET;
         std::vector<int32_t> acts;
         make_schedule(N, M, !(tol > 0), acts);
-        const BatchPlan plan = build_batch_program(acts, M, tol > 0);
+        Prog2d plan(g.K, steps);
+        plan.schedule(acts, second_level_needed(acts, M), M, tol > 0, true, ActionCodes{});
         // cannot happen: the program is bounded by the action count, and the executor's
         // bookkeeping always has the levels a step reads
         if (!plan.valid || (int)plan.ops.size() > B.max_ops) return WV_EINVAL;
@@ -2164,8 +2296,17 @@ int wv_compressibility(const wv_model *m, const wv_geom *geo, double tol, int st
     Fwd f{d, su, geo, s};
     f.at(d.Z, d.Z);
     int k = 0;
+    Prog2d p(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, 1));
+    Run2d run{d, su, geo, s};
     for (int n = 0; n < m->nt; ++n) {
-        if ((rc = f.step(n, nullptr))) return rc;
+        if (su.prog2d()) {
+            p.step(n, false);
+            if ((n + 1) % stride == 0) p.flush();
+            if ((rc = run.drain(p))) return rc;
+            f.at(run.ptr(p.u), run.ptr(p.up));
+        } else if ((rc = f.step(n, nullptr))) {
+            return rc;
+        }
         if ((n + 1) % stride == 0) {
             // encode u^{n+1} at the start of the arena; its header holds the stream size
             HIPCHK(launch_fill_u64(d.offs, 2, 0, s));
@@ -2250,8 +2391,8 @@ int encode_one(const float *field, int ndim, const int *dims, double tol, void *
     uint64_t *next = (uint64_t *)(b + 136);
     unsigned long long *st = (unsigned long long *)(b + 192);
     HIPCHK(launch_fill_u64((uint64_t *)b, kCodecBk / 8, 0, s));
-    HIPCHK(launch_encode(cd, field, nullptr, tol, (uint8_t *)out, cap, base, next, b + kCodecBk, staged, err, st,
-                         s));
+    const EncJob job{field, nullptr, base, next, nullptr};
+    HIPCHK(launch_encode(cd, &job, 1, tol, (uint8_t *)out, cap, b + kCodecBk, staged, err, st, s));
     unsigned e = 0;
     unsigned long long tot[2] = {0, 0};
     HIPCHK(hipMemcpyAsync(&e, err, 4, hipMemcpyDeviceToHost, s));
@@ -2354,7 +2495,8 @@ int wv_zfpk_decode(const void *in, size_t nbytes, int ndim, const int *dims, flo
     ok = ok && data_words <= (uint64_t)(nbytes - (size_t)cd.prefix_bytes) / 8 &&
          total == (uint64_t)cd.prefix_bytes + 8 * data_words && total <= (uint64_t)nbytes;
     if (!ok) return WV_EINVAL;
-    HIPCHK(launch_decode(cd, (const uint8_t *)in, nullptr, (uint64_t)total, field, nullptr, s));
+    const DecJob job{nullptr, field, nullptr};
+    HIPCHK(launch_decode(cd, (const uint8_t *)in, &job, 1, (uint64_t)total, s));
     return WV_OK;
 }
 

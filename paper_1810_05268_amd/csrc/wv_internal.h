@@ -55,18 +55,16 @@ struct Sparse {
     int *s_pos;
 };
 
-// What a step's launch does beside the step.
+// What a 3-D step's launch does beside the step.
 struct StepSide {
-    // injects into the level it writes.  2-D: the samples vals at the points of inj.  3-D
-    // (inj->np > 0): plane holds the points' values in np pitched planes, each multiplied by
-    // *scale when scale is set
+    // injects into the level it writes at the points of inj (np > 0): plane holds their
+    // values in np pitched planes, each multiplied by *scale when scale is set
     const Sparse *inj = nullptr;
-    const float *vals = nullptr;
     const float *plane = nullptr, *scale = nullptr;
     // gathers the receivers of its input level into row
     const Sparse *gat = nullptr;
     float *row = nullptr;
-    // 3-D: sums the samples next_vals at the points of next into the planes next_plane (the
+    // sums the samples next_vals at the points of next into the planes next_plane (the
     // values a later step injects; places of no point are not written)
     const Sparse *next = nullptr;
     const float *next_vals = nullptr;
@@ -90,7 +88,8 @@ hipError_t launch_fwd_step(const Grid &g, const float *u_in, const float *u_prev
 constexpr int kGNone = 0, kGAdd = 1, kGCarryOut = 2, kGCarryIn = 3;
 // Adjoint step (lam_in = lam^k, lam_next = lam^{k+1}, lam_out = lam^{k-1}, may equal
 // lam_next): the same update, and (if G) G += gscale * uk * (w lap lam_in), or the
-// carried form gmode selects with the array carry (pitched like a field).
+// carried form gmode selects with the array carry (pitched like a field).  Single OT2 steps
+// are for 3-D grids; 2-D grids take launch_tile2d.
 // An injection adds its gradient term too.
 hipError_t launch_adj_step(const Grid &g, const float *lam_in, const float *lam_next, float *lam_out,
                            const float *w, const float *uk, double *G, double gscale, hipStream_t s,
@@ -110,6 +109,40 @@ hipError_t launch_ot4_update(const Grid &g, const float *v, const float *u_in, c
 hipError_t launch_plane_setup(const Grid &g, const Sparse &sp, float *planes, int nsets, bool weights, hipStream_t s);
 // The points' summed samples, at their places in one set of planes (as StepSide::next).
 hipError_t launch_plane_sums(const Sparse &sp, const float *vals, float *plane, hipStream_t s);
+// 2-D OT2 steps of one shot in one launch: forward steps from u^n, or adjoint steps from
+// lam^k, ns of them (at most tile2d_steps).
+constexpr int kTileSteps = 8, kTileRegion = 64;   // a workgroup holds 64 x 64 points
+constexpr int tile2d_steps(int K) { return K <= 2 ? 8 : (K == 8 ? 2 : 16 / K); }
+// rim of a region that ns steps make invalid, in whole lanes' blocks
+constexpr int tile2d_halo(int K, int ns) { return (K * ns + 3) & ~3; }
+// Fields of one encode or decode of a 2-D OT2 run (a field of a few hundred points a side is a
+// few dozen chunks, which leave the chip idle: the more together the better), and its field
+// arrays: forward levels (as many waiting to be encoded or read by reverse steps, a group's
+// steps and its base) and decoded checkpoints.
+constexpr int tile2d_jobs(int K) { return tile2d_steps(K) > 4 ? tile2d_steps(K) : 4; }
+constexpr int tile2d_ring(int K) { return 2 * tile2d_jobs(K) + 3; }
+constexpr int tile2d_decoded(int K) { return tile2d_jobs(K) + 2; }
+struct Tile2dArgs {
+    const float *u, *up, *w;        // u^n, u^{n-1} (lam^k, lam^{k+1}); w
+    float *out[kTileSteps];         // where step j's level goes (null: it is not kept)
+    int ns;
+    Sparse inj;                     // injection of step j: samples vals + j vstride
+    const float *vals;
+    long long vstride;
+    Sparse gat;                     // bit j of gmask: the receivers of u^{n+j} go to rows + j gat.n
+    float *rows;
+    unsigned gmask;
+    const float *uk[kTileSteps];    // with G: u^k of step j, and the gradient (dense)
+    double *G;
+    double gscale;
+    __host__ __device__ const float *level(int j) const { return uk[j]; }
+    __host__ __device__ float *dest(int j) const { return out[j]; }
+};
+hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev = {});
+int device_cus();
+// steps per group for a grid, nshots shots advancing together
+int tile2d_choose(int K, int nx, int nz, int nshots);
+
 // Source injection of sample q[n] (forward) at the unique source points of u_out.
 hipError_t launch_inject_src(const Grid &g, const Sparse &sp, const float *q, int n, const float *w,
                              float *u_out, hipStream_t s);
@@ -148,23 +181,35 @@ struct CodecDims {
 // pitch 0: dense rows (pitch = dims[0])
 CodecDims codec_dims(int ndim, const int *dims, int pitch = 0);
 size_t codec_max_bytes(const CodecDims &cd);
-// Encode field (or field - sub, in binary32, when sub is not null) into out + *base
-// (device offset), capacity cap bytes from `out`.
-// Writes *next = *base + stream bytes rounded up to 256.  work: encode_work_bytes(cd,
-// staged) bytes, 256-byte aligned, any contents (chunk word counts, offsets and, when
-// staged, a kLdsWords-word slot per chunk; without staging every chunk is encoded twice).
-// size_out (nullable) receives the stream's size in bytes.
+// Encode fields of one geometry in three launches, job by job into out + *base (device
+// offset), capacity cap bytes from `out`; *next = *base + stream bytes rounded up to 256.  A
+// job whose base is the word the job before it writes as its next starts where that ends.
+// work: encode_work_bytes(cd, staged, jobs) bytes, 256-byte aligned, any contents (chunk
+// word counts, offsets and, when staged, block lengths and a kLdsWords-word slot per chunk;
+// without staging every chunk is encoded twice, and there is one job).
 // err: bit 2 = capacity overflow, bit 1 = non-finite input.
 // stats[0] += stream bytes, stats[1] = max(stats[1], *next).
-size_t encode_work_bytes(const CodecDims &cd, bool staged);
-hipError_t launch_encode(const CodecDims &cd, const float *field, const float *sub, double tol, uint8_t *out,
-                         uint64_t cap, const uint64_t *base, uint64_t *next, uint8_t *work, bool staged,
-                         unsigned *err, unsigned long long *stats, hipStream_t s, uint64_t *size_out = nullptr);
-// Decode the stream at in + *base (base == nullptr: offset 0) into field, or, when sub
+constexpr int kEncJobs = 8;
+struct EncJob {
+    const float *field;
+    const float *sub;        // nullable: field - sub, in binary32
+    const uint64_t *base;
+    uint64_t *next;
+    uint64_t *size_out;      // nullable: receives the stream's size in bytes
+};
+size_t encode_work_bytes(const CodecDims &cd, bool staged, int jobs = 1);
+hipError_t launch_encode(const CodecDims &cd, const EncJob *jobs, int njobs, double tol, uint8_t *out, uint64_t cap,
+                         uint8_t *work, bool staged, unsigned *err, unsigned long long *stats, hipStream_t s);
+// Decode the streams at in + *base (base == nullptr: offset 0) into field, or, when sub
 // is not null, store sub - decoded; cap bytes are readable from `in` (a stream that
 // does not fit decodes to zeros).
-hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const uint64_t *base, uint64_t cap, float *field,
-                         const float *sub, hipStream_t s);
+struct DecJob {
+    const uint64_t *base;
+    float *field;
+    const float *sub;
+};
+hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const DecJob *jobs, int njobs, uint64_t cap,
+                         hipStream_t s);
 
 // ---------------------------------------------------------------- batched 2-D solver (wv_batch.hip)
 // Several 2-D shots of one grid, order, step count and schedule advanced together by
@@ -172,7 +217,7 @@ hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const uint64_t 
 // device-wide barrier between phases.  Each shot keeps the buffers of a solo call
 // (field arrays dense in 2-D).
 struct BatchShot {
-    float *U[2], *UB, *DB, *Lm[2], *Z, *W;
+    float *U, *UB, *DB, *Lm, *Z, *W;   // rings of field arrays, BatchArgs::fstride elements apart
     const float *wavelet;     // [nt]
     const float *dobs;        // [nt+1][nrec]
     float *dsim, *res;        // [nt+1][nrec]
@@ -183,34 +228,39 @@ struct BatchShot {
     uint64_t arena_bytes;
     uint64_t *offs;           // stream offsets (as the solo executor's)
     uint64_t *sizes;          // stream bytes of u^k per stored k
-    uint32_t *chunk_words;    // [2][nchunks]: words per chunk of the two fields of a store
+    uint32_t *chunk_words;    // [jobs][nchunks]: words per chunk of the fields of an encode
     unsigned *err;            // bit 1: velocity, 2: non-finite input to the codec, 4: arena overflow,
                               // 8: non-finite wavefield, 16: barrier timeout
     unsigned long long *stats;  // [0] stream bytes stored, [1] peak arena offset
     Sparse src, rec;
 };
 
-// Buffers of a program step, by id: the shot's own arrays, or level l of checkpoint
-// slot b (uncompressed) as kBufSlot + 2 b + l.
-enum BatchBuf { kBufZ = 0, kBufU0, kBufU1, kBufUB, kBufDB, kBufL0, kBufL1, kBufNone = 15, kBufSlot = 16 };
-// Program steps.  Every shot executes each one; a device-wide barrier follows each.
-//   kOpFwd:      forward steps n .. d-1 from u^n in a and u^{n-1} in b, each a stencil phase and
-//                a phase that injects the source sample and (for steps s >= e) gathers data row
-//                s+1; the output of each step is the work buffer (kBufU0 / kBufU1) that does not
-//                hold its input, as in the solo executor
-//   kOpAdj:      adjoint step k = n, a = lam^k, b = lam^{k+1} (the output, in place), c = u^k: a
-//                stencil phase with the gradient term, then the residual injection of row k
-//   kOpEncCount: bit counts of the chunks of a store: a = u^k, b = u^{k-1} (kBufNone: one field)
-//   kOpEncEmit:  the store's streams at offs[d] (and offs[d+1] for the second field), next offset at
-//                offs[d+2] (one field) or offs[d+1], offs[d+2]; n = k (stream size recorded), -1 none
-//   kOpDec:      decode the stream at offs[d] into a (b != kBufNone: a = b - decoded)
-//   kOpCopy:     copy field a into b
-//   kOpResid:    residual r = d_sim - d_obs, partial sums of r^2, finiteness of field a
-//   kOpMisfit:   phi = 1/2 sum of the partials
-enum BatchOpKind { kOpNop = 0, kOpFwd, kOpAdj, kOpEncCount, kOpEncEmit, kOpDec, kOpCopy, kOpResid, kOpMisfit };
+// Buffers of a program step, by id: the shot's own arrays (member i of a ring as its first
+// id + i), or level l of checkpoint slot b (uncompressed) as kBufSlot + 2 b + l.
+enum BatchBuf { kBufNone = -1, kBufZ = 0, kBufDB = 1, kBufL = 2, kBufU = 8, kBufUB = 32, kBufSlot = 48 };
+static_assert(kBufU + tile2d_ring(1) <= kBufUB && kBufUB + tile2d_decoded(1) <= kBufSlot, "buffer ids");
+// Steps of a 2-D OT2 program (built by Prog2d).  Run by launches for a lone shot; in a batch
+// every shot executes each one, and a device-wide barrier follows each.
+//   kOpStep:   ns forward steps from u^n in a and u^{n-1} in b; step j's level goes to c[j]
+//              (kBufNone: not kept) with the source sample n + j injected; bit j of e: data row
+//              n + j from the level u^{n+j}
+//   kOpAdj:    ns adjoint steps from lam^k in a and lam^{k+1} in b, k = n; step j reads u^{k-j}
+//              in c[j] and injects the residual row k - j; the last level goes to d[0], the one
+//              before it to d[1]
+//   kOpGather: data row n from field a
+//   kOpEnc:    ns fields into their streams: field c[j], less d[j] (kBufNone: whole), at
+//              offs[x[j]]; the end of the last goes to offs[n], of the others to the next one's
+//              offs word; y[j]: k of the stored u^k (its size is recorded), -1 none
+//   kOpDec:    ns streams, at offs[x[j]], into c[j] (d[j] != kBufNone: d[j] - decoded)
+//   kOpCopy:   copy field a into b
+//   kOpResid:  residual r = d_sim - d_obs, partial sums of r^2, finiteness of field a
+//   kOpMisfit: phi = 1/2 sum of the partials
+enum BatchOpKind { kOpNop = 0, kOpStep, kOpAdj, kOpGather, kOpEnc, kOpDec, kOpCopy, kOpResid, kOpMisfit };
 struct BatchOp {
-    int32_t kind, n, a, b, c, d, e;
+    int32_t kind, n, ns, a, b, e;
+    int32_t c[kTileSteps], d[kTileSteps], x[kTileSteps], y[kTileSteps];
 };
+static_assert(kEncJobs >= kTileSteps, "an encode or decode step is one launch");
 
 struct BatchArgs {
     Grid g;
@@ -225,7 +275,7 @@ struct BatchArgs {
     int nrec;                 // receivers per shot (every shot of a batch has as many)
     int src_pts, rec_pts;     // largest scatter-table size over the shots (sources, receivers)
     int nt;
-    int zlen;                 // rows per stencil work item
+    long long fstride;        // elements from one array of a ring to the next
     long long slot_elems;     // elements of one uncompressed checkpoint slot (two fields)
     unsigned *bar;            // device-wide barrier words: group counters, top, generation, abort (zero at launch)
     int nwg;                  // workgroups of the launch (at most what the device holds at once)

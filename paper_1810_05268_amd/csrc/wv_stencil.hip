@@ -513,46 +513,22 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     }
 }
 
-// 2-D: a workgroup owns 256 consecutive x and marches down z (the second axis).
-// `prev` and `fout` may be the same array (read, then written, by the same lane).
-// MODE as for the 3-D kernel.
-// With inj_vals set (an OT2 step), the workgroup then injects the scatter table's points
-// inside its strip and rows into the level it has just written, as the separate injection
-// kernel would after the step (the same arithmetic in the same order): a 2-D step is
-// short, and a launch saved is a good part of it.  With gout set, one workgroup more
-// gathers the receivers of gin (the level the previous step wrote) into gout.
+// 2-D OT4 (OT2 runs in tiles, see wv_tile2d_dev.h): a workgroup owns 256 consecutive x and
+// marches down z (the second axis).  `prev` and `fout` may be the same array (read, then
+// written, by the same lane).  MODE as for the 3-D kernel.
 template <int K, bool GRAD, int MODE>
 __global__ __launch_bounds__(256) void stencil2d(Grid g, const float *__restrict__ fin, const float *prev,
                                                  float *fout, const float *__restrict__ w,
                                                  const float *__restrict__ uk, const float *__restrict__ xtra,
                                                  const float *__restrict__ xtra2, double *__restrict__ G,
-                                                 double gscale, int tiles_x, int zchunks, int zlen, Sparse sp,
-                                                 const float *__restrict__ inj_vals, Sparse gsp,
-                                                 const float *__restrict__ gin, float *__restrict__ gout)
+                                                 double gscale, int tiles_x, int zchunks, int zlen)
 {
-    static_assert(!(GRAD && MODE == kLapW), "the w lap pass carries no gradient term");
+    static_assert(MODE == kOT4 || (MODE == kLapW && !GRAD), "the OT4 passes; w lap carries no gradient term");
     __shared__ float row[256 + 2 * K];
-    const int nwg = tiles_x * zchunks;
-    if (gout && (int)blockIdx.x == nwg) {
-        for (int r = threadIdx.x; r < gsp.n; r += 256) gout[r] = gather_point(gsp, r, gin);
-        return;
-    }
-    const int lid = xcd_remap(blockIdx.x, nwg);
+    const int lid = xcd_remap(blockIdx.x, tiles_x * zchunks);
     const int tix = lid % tiles_x, zc = lid / tiles_x;
     const int z0 = zc * zlen, z1 = min(z0 + zlen, g.nz);
     march2d<K, GRAD, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, gscale, tix, z0, z1, row);
-    if constexpr (MODE == kOT2) {
-        if (inj_vals) {
-            __syncthreads();
-            const int nx = g.nx, x0 = tix * 256, x1 = min(x0 + 256, nx);
-            for (int i = threadIdx.x; i < sp.npts; i += 256) {
-                const int p = sp.s_pts[i];
-                const int z = p / nx, x = p - z * nx;
-                if (z < z0 || z >= z1 || x < x0 || x >= x1) continue;
-                inject_point<GRAD>(g, sp, i, p, x, 0, z, inj_vals, w, fout, uk, G, p, gscale);
-            }
-        }
-    }
 }
 
 // Adds w s / (1+a) at the source (or receiver) points of the level just written.
@@ -845,8 +821,8 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
             return launch3d<K, GM, true, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
         return launch3d<K, GM, false, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
     }
-    if constexpr (GM == kGCarryOut || GM == kGCarryIn) {
-        return hipErrorInvalidValue;   // 2-D steps add their gradient term directly
+    if constexpr (MODE == kOT2) {
+        return hipErrorInvalidValue;   // 2-D OT2 steps run in tiles
     } else {
     // 2-D grids are small (a few MB): a step is bound by the latency of each workgroup's
     // plane-by-plane march, not by bandwidth, so chunks are short (down to K planes, whose
@@ -854,13 +830,9 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
     const int tiles_x = (g.nx + 255) / 256;
     int zchunks, zlen;
     choose_chunks(tiles_x, g.nz, K, 2048, zchunks, zlen);
-    const int nwg = tiles_x * zchunks;
-    if (side.next || (MODE != kOT2 && (side.inj || side.row))) return hipErrorInvalidValue;
-    const Sparse spv = side.inj ? *side.inj : Sparse{};
-    const Sparse gv = side.gat ? *side.gat : Sparse{};
-    float *go = side.gat ? side.row : nullptr;
-    launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(nwg + (go ? 1 : 0)), s, ev, g, fin, prev, fout, w, uk, xtra,
-                 xtra2, G, gscale, tiles_x, zchunks, zlen, spv, side.inj ? side.vals : nullptr, gv, fin, go);
+    if (side.inj || side.row || side.next) return hipErrorInvalidValue;
+    launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(tiles_x * zchunks), s, ev, g, fin, prev, fout, w, uk, xtra,
+                 xtra2, G, gscale, tiles_x, zchunks, zlen);
     return hipGetLastError();
     }
 }

@@ -30,18 +30,17 @@ __device__ __forceinline__ float damping(const Grid &g, int x, int y, int z)
     int dx = layer_depth(x, g.ix0[0], g.ix1[0]);
     int dy = layer_depth(y, g.ix0[1], g.ix1[1]);
     int dz = layer_depth(z, g.ix0[2], g.ix1[2]);
-    return g.dampx * (float)(dx * dx) + g.dampy * (float)(dy * dy) + g.dampz * (float)(dz * dz);
+    // the order is fixed, so that every kernel rounds it alike
+    return fmaf(g.dampz, (float)(dz * dz), fmaf(g.dampx, (float)(dx * dx), g.dampy * (float)(dy * dy)));
 }
 
 // what a stencil launch does with the Laplacian (see stencil3d)
 constexpr int kOT2 = 0, kLapW = 1, kOT4 = 2;
 
-// One point (x, z) of the 2-D step, p its index.  q: the 2K+1 values of the marched
+// One point (x, z) of a 2-D OT4 pass, p its index.  q: the 2K+1 values of the marched
 // field's column around z (q[K] the point itself); rowc: the point in the field's row z,
 // staged with its K neighbours on either side (rowc[-K..K]).  MODE as for stencil3d:
-//   kOT2: fout = c + ((1-a)(c - prev) + w L)/(1+a), in binary32 with the damping
-//         division skipped where a = 0; GRAD adds gscale u^k (w L) to G in binary64;
-//   kLapW: fout = w L;  kOT4: the second pass of an OT4 step.
+//   kLapW: fout = w L;  kOT4: the second pass, with the damping division skipped where a = 0.
 // The Laplacian takes the k = 1 term from differences and the far terms as a plain sum
 // folded once against the centre.
 template <int K, bool GRAD, int MODE>
@@ -50,6 +49,7 @@ __device__ __forceinline__ void point2d(const Grid &g, const float *q, const flo
                                         const float *__restrict__ uk, const float *__restrict__ xtra,
                                         const float *__restrict__ xtra2, double *__restrict__ G, double gscale)
 {
+    static_assert(MODE == kLapW || MODE == kOT4, "2-D OT2 steps run in tiles");
     const float c = q[K];
     float sx = g.cx[1] * ((rowc[1] - c) + (rowc[-1] - c));
     float sz = g.cz[1] * ((q[K + 1] - c) + (q[K - 1] - c));
@@ -68,17 +68,15 @@ __device__ __forceinline__ void point2d(const Grid &g, const float *q, const flo
     if constexpr (MODE == kLapW) {
         __builtin_nontemporal_store(wp * lap, &fout[p]);
     } else {
-        const float ctr = MODE == kOT4 ? __builtin_nontemporal_load(&xtra[p]) : c;
-        const float wl = MODE == kOT4 ? fmaf(wp * (1.0f / 12.0f), lap, c) : wp * lap;
+        const float ctr = __builtin_nontemporal_load(&xtra[p]);
+        const float wl = fmaf(wp * (1.0f / 12.0f), lap, c);
         const float a = damping(g, x, 0, z);
         const float d = ctr - __builtin_nontemporal_load(&prev[p]);
         const float dn = (a == 0.0f) ? d + wl : ((1.0f - a) * d + wl) / (1.0f + a);
         __builtin_nontemporal_store(ctr + dn, &fout[p]);
-        if constexpr (GRAD && MODE == kOT4)
+        if constexpr (GRAD)
             G[p] += gscale * ((double)__builtin_nontemporal_load(&uk[p]) * (double)wl +
                               (double)c * (double)__builtin_nontemporal_load(&xtra2[p]) * (1.0 / 12.0));
-        else if constexpr (GRAD)
-            G[p] += gscale * (double)__builtin_nontemporal_load(&uk[p]) * (double)wl;
     }
 }
 

@@ -1,0 +1,378 @@
+// Several 2-D OT2 steps in one pass over a tile, shared by the solo launches and the
+// batched solver (one definition, so that a shot gives the same bits either way).
+//
+// A 2-D field is a few MB, so a step launched by itself is bound by latency: the launch, a
+// workgroup's first loads and its march down the rows (7.1 us a forward step on 552^2 points
+// at order 8, 0.7 us of which its bytes need; 8.7 us an adjoint step).  Three steps in tiles
+// take 9.1 and 9.8 us, two thirds of it arithmetic.  Here a workgroup takes a 64 x 64 region of
+// the grid into LDS and its registers and advances it by up to kTileSteps(K) steps; each
+// step makes K more rows and columns at the region's rim invalid, and the core that is left
+// is written.  The rim is computed by the neighbouring workgroups too (with 4 steps of order
+// 8 a core of 32 x 32: twice the arithmetic), which costs less than a launch per step.
+//   * A lane owns R rows of 4 points: the two levels are in LDS (a step overwrites the older
+//     one, each lane its own points: one barrier a step), w and the damping in registers; a step reads
+//     R + 2K rows of 16 bytes for the z neighbours of its points and 2 ceil(K/4) more per
+//     row for the x neighbours.
+//   * Injected samples are summed before the steps, for all of them; each step's go to an LDS
+//     plane of the region, and the owner of a point adds its own in the step's order (the
+//     binary64 gradient too), so results do not depend on how steps are grouped.
+//   * Divisions by 1 + a (in the absorbing layer) multiply by the reciprocal, formed once a
+//     region, and correct twice, which rounds as the division does (5 operations for 13);
+//     waves whose points all lie outside the layer have none.
+//   * Points outside the grid hold zeros and have w = 0, so they stay zero (but for a field that
+//     is no longer finite, which the caller refuses).
+//   * Receivers are read from the LDS level: those whose first corner lies in the core.
+#pragma once
+
+#include "wv_stencil_dev.h"
+
+namespace wv {
+
+namespace {
+
+constexpr int kTileEX = kTileRegion, kTileEY = kTileRegion;
+constexpr int tile2d_threads(int R) { return 16 * (kTileRegion / R); }
+constexpr int kTileCap = 256;                // injected points and receivers of a region kept in LDS
+
+struct Tile2dShared {
+    // two levels of the region with a guard rim for the lanes at its edge, whose results
+    // are not used (sized for K = 8)
+    template <int K>
+    struct Levels {
+        float u[2][kTileEY + 2 * K][kTileEX + 2 * ((K + 3) & ~3)];
+    };
+    float inj[kTileEY][kTileEX];             // a step's summed samples, 0 where there is no point
+    int ent[kTileCap], rec[kTileCap];
+    int n, nrec;
+};
+
+// Which products are fused with a sum is written out here (and contraction is off), so that
+// every instance rounds alike whatever surrounds it.
+// The Laplacian of a point from its column q[0..2K] (q[K] the point) and row x[0..2K].
+template <int K>
+__device__ __forceinline__ float lap2d(const Grid &g, const float *q, const float *x)
+{
+#pragma clang fp contract(off)
+    const float c = q[K];
+    const float tx = (x[K + 1] - c) + (x[K - 1] - c);
+    const float tz = (q[K + 1] - c) + (q[K - 1] - c);
+    if constexpr (K == 1) {
+        return fmaf(g.cz[1], tz, g.cx[1] * tx);
+    } else {
+        float fx = 0.0f, fz = 0.0f;
+#pragma unroll
+        for (int k = 2; k <= K; ++k) {
+            fx = fmaf(g.cx[k], x[K + k] + x[K - k], fx);
+            fz = fmaf(g.cz[k], q[K + k] + q[K - k], fz);
+        }
+        return fmaf(g.cx[1], tx, fmaf(-g.cf2[0], c, fx)) + fmaf(g.cz[1], tz, fmaf(-g.cf2[2], c, fz));
+    }
+}
+
+// n[i] / b[i], r the binary32 reciprocals of b (1 <= b < 4).  The first correction leaves less
+// than an ulp and the second rounds correctly, as long as the remainders are exact: below
+// 2^-100 they are not, and a wave with such a value divides (a long run is sensitive to a
+// single bit: the smallest values are those ahead of a wavefront, which grow by many orders).
+__device__ __forceinline__ void div4(const float *n, const float *b, const float *r, float *q)
+{
+#pragma clang fp contract(off)
+    unsigned least = ~0u;      // of the magnitudes, 0 taken as the largest
+#pragma unroll
+    for (int i = 0; i < 4; ++i) least = min(least, (__float_as_uint(n[i]) << 1) - 1u);
+    if (__any(least < (__float_as_uint(0x1p-100f) << 1) - 1u)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = n[i] / b[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float t = n[i] * r[i];
+            t = fmaf(fmaf(-t, b[i], n[i]), r[i], t);
+            q[i] = fmaf(fmaf(-t, b[i], n[i]), r[i], t);
+        }
+    }
+}
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of any length: 4-byte aligned
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// 4 values of row gz from column gx on, from a clamped address and without a branch, so that
+// all loads of a lane are in flight together; the caller zeroes what lies outside the grid.
+// gx is a multiple of 4, so only a row's last lane straddles its end; it reads on into the
+// next row (after the last row, into the workspace behind the array, which is padded).
+__device__ __forceinline__ f4u tile_load4(const Grid &g, const float *f, int gx, int gz)
+{
+    const int z = min(max(gz, 0), g.nz - 1), x = min(max(gx, 0), (g.nx - 1) & ~3);
+    return *reinterpret_cast<const f4u *>(f + (long long)z * g.nx + x);
+}
+
+// As tile_load4 for the caller's gradient, behind which nothing may be read: the last lane
+// of a row reads its last four values and moves them down (grids under 4 wide: one by one).
+__device__ __forceinline__ void tile_load_grad(const Grid &g, const double *f, int gx, int gz, double *v)
+{
+    const int z = min(max(gz, 0), g.nz - 1);
+    const double *row = f + (long long)z * g.nx;
+    if (g.nx < 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = row[min(max(gx, 0) + i, g.nx - 1)];
+        return;
+    }
+    const int x = min(max(gx, 0), g.nx - 4), sh = gx - x;
+    const d2u a = *reinterpret_cast<const d2u *>(row + x), b = *reinterpret_cast<const d2u *>(row + x + 2);
+    const double t0 = sh & 1 ? a.y : a.x, t1 = sh & 1 ? b.x : a.y, t2 = sh & 1 ? b.y : b.x, t3 = b.y;
+    v[0] = sh & 2 ? t2 : t0;
+    v[1] = sh & 2 ? t3 : t1;
+    v[2] = t2;
+    v[3] = t3;
+}
+
+// Tile (tix, tiz) of the launch or phase A describes (a Tile2dArgs, or a view of a batched
+// shot with the same members); every lane of the tile2d_threads(R)
+// calls it; a lane owns R rows of 4 points.
+template <int K, bool GRAD, int R, typename Args>
+__device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, int tiz, Tile2dShared &S,
+                                       typename Tile2dShared::template Levels<K> &L)
+{
+#pragma clang fp contract(off)
+    constexpr int HXK = (K + 3) & ~3;
+    constexpr int NXV = 1 + 2 * (HXK / 4);
+    constexpr int NT = tile2d_threads(R);
+    static_assert(NT >= kTileCap, "a lane per listed point");
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int nx = g.nx, nz = g.nz, ns = A.ns;
+    const int H = tile2d_halo(K, ns), C = kTileEX - 2 * H;     // rim and core (both axes)
+    const int gx0 = tix * C - H, gz0 = tiz * C - H;
+    const int gx = gx0 + 4 * tx, gz = gz0 + R * ty;
+    const bool core = tx >= H / 4 && tx < (H + C) / 4 && R * ty >= H && R * ty < H + C;
+
+    // the lane's points: u^n (to LDS), u^{n-1}, w, damping, gradient
+    f4u un[R], pl[R], wl4[R];
+    float wr[R][4], am[R][4], ap[R][4], rp[R][4];   // 1 - a, 1 + a, 1 / (1 + a)
+    double G[GRAD ? R : 1][4];
+    bool damp = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        un[r] = tile_load4(g, A.u, gx, gz + r);
+        pl[r] = tile_load4(g, A.up, gx, gz + r);
+        wl4[r] = tile_load4(g, A.w, gx, gz + r);
+        if constexpr (GRAD) tile_load_grad(g, A.G, gx, gz + r, G[r]);
+    }
+    if (tid == 0) S.n = S.nrec = 0;
+    __syncthreads();
+    // injected points of the region and receivers of the core
+    for (int i = tid; i < A.inj.npts; i += NT) {
+        const int p = A.inj.s_pts[i];
+        const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
+        if (lx < 0 || lx >= kTileEX || lz < 0 || lz >= kTileEY) continue;
+        const int e = atomicAdd(&S.n, 1);
+        if (e < kTileCap) S.ent[e] = i;
+    }
+    if (!GRAD && A.gmask) {
+        for (int i = tid; i < A.gat.n; i += NT) {
+            const int p = A.gat.g_idx[i * A.gat.nc];
+            const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
+            if (lx < H || lx >= H + C || lz < H || lz >= H + C) continue;
+            const int e = atomicAdd(&S.nrec, 1);
+            if (e < kTileCap) S.rec[e] = i;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int x = gx + i, z = gz + r;
+            const bool in = x >= 0 && x < nx && z >= 0 && z < nz;
+            un[r][i] = in ? un[r][i] : 0.0f;
+            pl[r][i] = in ? pl[r][i] : 0.0f;
+            wr[r][i] = in ? wl4[r][i] : 0.0f;
+            const float a = in ? damping(g, x, 0, z) : 0.0f;
+            damp |= a != 0.0f;
+            am[r][i] = 1.0f - a;
+            ap[r][i] = 1.0f + a;
+        }
+        *reinterpret_cast<float4 *>(&L.u[0][R * ty + r + K][4 * tx + HXK]) =
+            make_float4(un[r][0], un[r][1], un[r][2], un[r][3]);
+        *reinterpret_cast<float4 *>(&L.u[1][R * ty + r + K][4 * tx + HXK]) =
+            make_float4(pl[r][0], pl[r][1], pl[r][2], pl[r][3]);
+    }
+    __syncthreads();
+    const int ninj = S.n, nrec = S.nrec;
+    const bool damped = __any(damp);
+    // thread e < ninj sums the samples of entry e for every step
+    const bool listed = ninj <= kTileCap;
+    int iloc = -1;
+    float ival[tile2d_steps(K)];
+    if (ninj) {
+        for (int i = tid; i < kTileEX * kTileEY; i += NT) (&S.inj[0][0])[i] = 0.0f;
+        if (listed && tid < ninj) {
+            const int i = S.ent[tid], p = A.inj.s_pts[i], z = p / nx;
+            iloc = (z - gz0) * kTileEX + p - z * nx - gx0;
+#pragma unroll
+            for (int j = 0; j < tile2d_steps(K); ++j) ival[j] = 0.0f;
+            for (int q = A.inj.s_start[i]; q < A.inj.s_start[i + 1]; ++q) {   // as scatter_sum, all steps at once
+                const float wt = A.inj.s_wt[q];
+                const float *v = A.vals + A.inj.s_col[q];
+#pragma unroll
+                for (int j = 0; j < tile2d_steps(K); ++j) ival[j] = fmaf(wt, v[min(j, ns - 1) * A.vstride], ival[j]);
+            }
+        }
+        __syncthreads();
+    }
+    if (damped) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rp[r][i] = 1.0f / ap[r][i];
+    }
+    // the lane's receiver: its corners' places in the region and their weights
+    int goff[4] = {0, 0, 0, 0};
+    float gwt[4] = {0.f, 0.f, 0.f, 0.f};
+    const int rr = (!GRAD && nrec <= kTileCap && tid < nrec) ? S.rec[tid] : -1;
+    if (rr >= 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c < A.gat.nc) {
+                const int p = A.gat.g_idx[rr * A.gat.nc + c];
+                const int z = p / nx;
+                goff[c] = (z - gz0 + K) * (kTileEX + 2 * HXK) + p - z * nx - gx0 + HXK;
+                gwt[c] = A.gat.g_wt[rr * A.gat.nc + c];
+            }
+    }
+
+#pragma unroll 1
+    for (int j = 0; j < ns; ++j) {
+        const int cur = j & 1;
+        if (ninj) {       // this step's samples
+            if (listed) {
+                float v = ival[0];
+#pragma unroll
+                for (int q = 1; q < tile2d_steps(K); ++q) v = q == j ? ival[q] : v;
+                if (iloc >= 0) (&S.inj[0][0])[iloc] = v;
+            } else {
+                for (int i = tid; i < A.inj.npts; i += NT) {
+                    const int p = A.inj.s_pts[i];
+                    const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
+                    if (lx >= 0 && lx < kTileEX && lz >= 0 && lz < kTileEY)
+                        S.inj[lz][lx] = scatter_sum(A.inj, i, A.vals + j * A.vstride);
+                }
+            }
+            __syncthreads();
+        }
+        if (!GRAD && (A.gmask >> j & 1)) {
+            const float *lev = &L.u[cur][0][0];
+            float *row = A.rows + (long long)j * A.gat.n;
+            if (nrec <= kTileCap) {
+                if (rr >= 0) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (c < A.gat.nc) s = fmaf(gwt[c], lev[goff[c]], s);
+                    row[rr] = s;
+                }
+            } else {
+                for (int i = tid; i < A.gat.n; i += NT) {
+                    const int p0 = A.gat.g_idx[i * A.gat.nc];
+                    const int z0 = p0 / nx, lx0 = p0 - z0 * nx - gx0, lz0 = z0 - gz0;
+                    if (lx0 < H || lx0 >= H + C || lz0 < H || lz0 >= H + C) continue;
+                    float s = 0.0f;
+                    for (int c = 0; c < A.gat.nc; ++c) {
+                        const int p = A.gat.g_idx[i * A.gat.nc + c];
+                        const int z = p / nx;
+                        s = fmaf(A.gat.g_wt[i * A.gat.nc + c], L.u[cur][z - gz0 + K][p - z * nx - gx0 + HXK], s);
+                    }
+                    row[i] = s;
+                }
+            }
+        }
+        const int m = K * (j + 1);     // the rim that is invalid after this step
+        if (R * ty + R > m && R * ty < kTileEY - m && 4 * tx + 4 > m && 4 * tx < kTileEX - m) {
+            f4u uk[R];   // read in the core only by what is stored
+            if constexpr (GRAD) {
+                const float *lev = A.level(j);
+#pragma unroll
+                for (int r = 0; r < R; ++r) uk[r] = tile_load4(g, lev, gx, gz + r);
+            }
+            float q[4][R + 2 * K];
+#pragma unroll
+            for (int r = 0; r < R + 2 * K; ++r) {
+                const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][R * ty + r][4 * tx + HXK]);
+                q[0][r] = t.x; q[1][r] = t.y; q[2][r] = t.z; q[3][r] = t.w;
+            }
+            float *const out = A.dest(j);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float xr[4 * NXV];
+#pragma unroll
+                for (int v = 0; v < NXV; ++v) {
+                    if (v == HXK / 4) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) xr[4 * v + i] = q[i][r + K];
+                    } else {
+                        const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][R * ty + r + K][4 * tx + 4 * v]);
+                        xr[4 * v] = t.x; xr[4 * v + 1] = t.y; xr[4 * v + 2] = t.z; xr[4 * v + 3] = t.w;
+                    }
+                }
+                // the level before is the lane's own in the other buffer, about to be overwritten
+                const float4 p4 = *reinterpret_cast<const float4 *>(&L.u[cur ^ 1][R * ty + r + K][4 * tx + HXK]);
+                const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
+                float on[4], num[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float c = q[i][r + K];
+                    const float lap = lap2d<K>(g, &q[i][r], &xr[HXK + i - K]);
+                    const float wl = wr[r][i] * lap;
+                    const float d = c - pv[i];
+                    num[i] = damped ? fmaf(am[r][i], d, wl) : d + wl;   // (1 - 0) d + wl rounds as d + wl
+                    if constexpr (GRAD) G[r][i] = fma(A.gscale * (double)uk[r][i], (double)wl, G[r][i]);
+                }
+                if (damped) div4(num, ap[r], rp[r], num);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) on[i] = q[i][r + K] + num[i];
+                if (ninj) {
+                    const float4 s4 = *reinterpret_cast<const float4 *>(&S.inj[R * ty + r][4 * tx]);
+                    const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (sv[i] != 0.0f) {
+                            const float wi = wr[r][i] * sv[i];
+                            on[i] += damped ? wi / ap[r][i] : wi;
+                            if constexpr (GRAD) G[r][i] = fma(A.gscale * (double)uk[r][i], (double)wi, G[r][i]);
+                        }
+                }
+                *reinterpret_cast<float4 *>(&L.u[cur ^ 1][R * ty + r + K][4 * tx + HXK]) =
+                    make_float4(on[0], on[1], on[2], on[3]);
+                if (core && out && gz + r < nz) {
+                    float *p = out + (long long)(gz + r) * nx + gx;
+                    if (gx + 3 < nx) {
+                        const f4u t = {on[0], on[1], on[2], on[3]};
+                        *reinterpret_cast<f4u *>(p) = t;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+                            if (gx + i < nx) p[i] = on[i];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (GRAD) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!core || gz + r >= nz || gx >= nx) continue;
+            double *p = A.G + (long long)(gz + r) * nx + gx;
+            if (gx + 3 < nx) {
+                const d2u a = {G[r][0], G[r][1]}, b = {G[r][2], G[r][3]};
+                *reinterpret_cast<d2u *>(p) = a;
+                *reinterpret_cast<d2u *>(p + 2) = b;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (gx + i < nx) p[i] = G[r][i];
+            }
+        }
+    }
+}
+
+}  // namespace
+
+}  // namespace wv
