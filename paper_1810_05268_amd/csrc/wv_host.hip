@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <vector>
 
@@ -588,99 +589,136 @@ int validate_model(const wv_model *m, Setup &su)
     return WV_OK;
 }
 
-// Multilinear weights of one position (metres from the first interior point).
-int point_weights(const wv_model *m, const Setup &su, const double *xyz, int *idx, float *wt)
+// Corners of a point of nonzero weight, in corner order (axis 0's bit lowest): appends their
+// places in the pitched field arrays and their weights, and returns corner 0's place in
+// *first.  The weight is the product of the axes' factors, formed in binary64.
+int point_corners(const wv_model *m, const Setup &su, const double *xyz, std::vector<int> &idx,
+                  std::vector<float> &wt, int *first)
 {
-    int i0[3] = {0, 0, 0};
-    double fr[3] = {0, 0, 0};
+    int off[3][2] = {{0, 0}, {0, 0}, {0, 0}};
+    double f[3][2] = {{1, 0}, {1, 0}, {1, 0}};
+    long long stride = 1;
     for (int d = 0; d < m->ndim; ++d) {
         const double gpos = xyz[d] / m->h[d] + (double)m->nbl;
         if (!(gpos >= 0.0) || gpos > (double)(su.N[d] - 1)) return WV_EINVAL;
-        int i = (int)std::floor(gpos);
+        int i = (int)gpos;   // gpos >= 0: its floor
         if (i > su.N[d] - 2) i = su.N[d] - 2;
         if (i < 0) i = 0;
-        i0[d] = i;
-        fr[d] = gpos - i;
+        const double fr = gpos - i;
+        off[d][0] = (int)(i * stride);
+        off[d][1] = (int)(std::min(i + 1, su.N[d] - 1) * stride);
+        f[d][0] = 1.0 - fr;
+        f[d][1] = fr;
+        stride *= d == 0 ? su.g.px : su.N[d];
     }
-    const int nc = m->ndim == 3 ? 8 : 4;
-    for (int c = 0; c < nc; ++c) {
-        long long p = 0, stride = 1;
-        double w = 1.0;
-        for (int d = 0; d < m->ndim; ++d) {
-            const int bit = (c >> d) & 1;
-            const int ii = std::min(i0[d] + bit, su.N[d] - 1);
-            p += (long long)ii * stride;
-            stride *= d == 0 ? su.g.px : su.N[d];   // pitched field arrays
-            w *= bit ? fr[d] : 1.0 - fr[d];
+    *first = off[0][0] + off[1][0] + off[2][0];
+    for (int z = 0; z < 2; ++z) {
+        if (f[2][z] == 0.0) continue;
+        for (int y = 0; y < 2; ++y) {
+            if (f[1][y] == 0.0) continue;
+            for (int x = 0; x < 2; ++x) {
+                const float w = (float)(f[0][x] * f[1][y] * f[2][z]);
+                if (w == 0.0f) continue;
+                idx.push_back(off[0][x] + off[1][y] + off[2][z]);
+                wt.push_back(w);
+            }
         }
-        idx[c] = (int)p;
-        wt[c] = (float)w;
     }
     return WV_OK;
 }
 
-// gather tables plus the transposed (scatter) table with unique points
+// Gather tables plus the transposed (scatter) table with unique points.  A survey of tens of
+// thousands of receivers is set up on every call (twice: its workspace size is asked for
+// first), so this is linear: the corners of nonzero weight only, and the transposition by a
+// stable counting sort on the points, which leaves each point's entries in column and corner
+// order, or by none where the points already ascend (receivers on the nodes, in grid order).
+// 13,677 receivers between nodes: 10.3 -> 1.8 ms; 102,400 on them: 9.3 -> 2.5 ms.
 int build_sparse(const wv_model *m, const Setup &su, int npt, const double *xyz, bool shared_col,
                  std::vector<int> &gidx, std::vector<float> &gwt, std::vector<int> &pts, std::vector<int> &start,
                  std::vector<int> &col, std::vector<float> &swt, int &nc_out)
 {
-    const int nc_all = m->ndim == 3 ? 8 : 4;
-    std::vector<int> gi((size_t)npt * nc_all, 0);
-    std::vector<float> gw((size_t)npt * nc_all, 0.0f);
-    for (int r = 0; r < npt; ++r) {
-        const int rc = point_weights(m, su, xyz + (size_t)r * m->ndim, &gi[(size_t)r * nc_all], &gw[(size_t)r * nc_all]);
-        if (rc) return rc;
-    }
+    std::vector<int> idx, first((size_t)npt), end((size_t)npt);
+    std::vector<float> wt;
+    idx.reserve((size_t)npt * 2);
+    wt.reserve((size_t)npt * 2);
     // A corner of weight zero (a point on a grid line or node) adds nothing to a gather
     // or a scatter: the tables keep the others, in corner order, each point padded to the
     // largest count with zero weights at its first corner (so a sum takes the same
     // values in the same order, without the zero terms).
-    int nc = 1;
+    size_t nc = 1;
     for (int r = 0; r < npt; ++r) {
-        int k = 0;
-        for (int c = 0; c < nc_all; ++c) k += gw[(size_t)r * nc_all + c] != 0.0f;
-        nc = std::max(nc, k);
+        const size_t n0 = idx.size();
+        const int rc = point_corners(m, su, xyz + (size_t)r * m->ndim, idx, wt, &first[r]);
+        if (rc) return rc;
+        end[r] = (int)idx.size();
+        nc = std::max(nc, idx.size() - n0);
     }
-    gidx.assign((size_t)npt * nc, 0);
-    gwt.assign((size_t)npt * nc, 0.0f);
-    for (int r = 0; r < npt; ++r) {
-        int j = 0;
-        for (int c = 0; c < nc_all; ++c) {
-            const size_t a = (size_t)r * nc_all + c;
-            if (gw[a] == 0.0f) continue;
-            gidx[(size_t)r * nc + j] = gi[a];
-            gwt[(size_t)r * nc + j] = gw[a];
-            ++j;
+    const size_t ne = idx.size();
+    nc_out = (int)nc;
+    col.resize(ne);
+    for (int r = 0, e = 0; r < npt; ++r)
+        for (; e < end[r]; ++e) col[e] = shared_col ? 0 : r;
+    if (ne == nc * (size_t)npt) {
+        gidx = idx;
+        gwt = wt;
+    } else {
+        gidx.resize((size_t)npt * nc);
+        gwt.assign((size_t)npt * nc, 0.0f);
+        for (int r = 0, e = 0; r < npt; ++r) {
+            size_t a = (size_t)r * nc;
+            for (; e < end[r]; ++e, ++a) {
+                gidx[a] = idx[e];
+                gwt[a] = wt[e];
+            }
+            for (; a < (size_t)(r + 1) * nc; ++a) gidx[a] = first[r];
         }
-        for (; j < nc; ++j) gidx[(size_t)r * nc + j] = gi[(size_t)r * nc_all];
     }
-    nc_out = nc;
     // entries sorted by (point, column, corner) for a fixed summation order
-    struct E { int p, col, c; float w; };
-    std::vector<E> es;
-    es.reserve((size_t)npt * nc);
-    for (int r = 0; r < npt; ++r)
-        for (int c = 0; c < nc; ++c)
-            if (gwt[(size_t)r * nc + c] != 0.0f)
-                es.push_back({gidx[(size_t)r * nc + c], shared_col ? 0 : r, c, gwt[(size_t)r * nc + c]});
-    std::sort(es.begin(), es.end(), [](const E &a, const E &b) {
-        if (a.p != b.p) return a.p < b.p;
-        if (a.col != b.col) return a.col < b.col;
-        return a.c < b.c;
-    });
+    const bool ascending = shared_col ? std::adjacent_find(idx.begin(), idx.end(), std::greater_equal<int>()) == idx.end()
+                                      : std::is_sorted(idx.begin(), idx.end());
+    if (!ascending) {
+        std::vector<int> perm(ne), tmp(ne);
+        for (size_t e = 0; e < ne; ++e) perm[e] = (int)e;
+        if (shared_col) {
+            // one column: a point's entries in the order of their corners
+            std::vector<int> corner(ne);
+            for (int r = 0, e = 0; r < npt; ++r)
+                for (int c = 0; e < end[r]; ++e, ++c) corner[e] = c;
+            std::stable_sort(perm.begin(), perm.end(), [&](int a, int b) {
+                return idx[a] != idx[b] ? idx[a] < idx[b] : corner[a] < corner[b];
+            });
+        } else {
+            constexpr int kBits = 11, kBuckets = 1 << kBits;
+            for (int shift = 0; shift < 32 && (su.Pf - 1) >> shift; shift += kBits) {
+                std::vector<int> at(kBuckets + 1, 0);
+                for (size_t e = 0; e < ne; ++e) ++at[((idx[perm[e]] >> shift) & (kBuckets - 1)) + 1];
+                for (int k = 0; k < kBuckets; ++k) at[k + 1] += at[k];
+                for (size_t e = 0; e < ne; ++e) tmp[at[(idx[perm[e]] >> shift) & (kBuckets - 1)]++] = perm[e];
+                perm.swap(tmp);
+            }
+        }
+        std::vector<int> idx2(ne), col2(ne);
+        swt.resize(ne);
+        for (size_t e = 0; e < ne; ++e) {
+            idx2[e] = idx[perm[e]];
+            col2[e] = col[perm[e]];
+            swt[e] = wt[perm[e]];
+        }
+        idx.swap(idx2);
+        col.swap(col2);
+    } else {
+        swt.swap(wt);
+    }
     pts.clear();
     start.clear();
-    col.clear();
-    swt.clear();
-    for (size_t i = 0; i < es.size(); ++i) {
-        if (i == 0 || es[i].p != es[i - 1].p) {
-            pts.push_back(es[i].p);
-            start.push_back((int)col.size());
+    pts.reserve(ne);
+    start.reserve(ne + 1);
+    for (size_t e = 0; e < ne; ++e)
+        if (e == 0 || idx[e] != idx[e - 1]) {
+            pts.push_back(idx[e]);
+            start.push_back((int)e);
         }
-        col.push_back(es[i].col);
-        swt.push_back(es[i].w);
-    }
-    start.push_back((int)col.size());
+    start.push_back((int)ne);
     return WV_OK;
 }
 
