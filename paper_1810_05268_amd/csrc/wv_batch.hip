@@ -360,9 +360,9 @@ __device__ __forceinline__ void phase_decode(const BatchCtx &C, const BatchOp &o
         const long long cw = ((long long)total_bits + 63) / 64 + 1;
         const bool staged = cw <= kDecLdsWords;
         if (staged) {
-            for (long long q = tid; q < cw; q += 256) {
+            for (long long q = tid; q < cw + kDecPad; q += 256) {
                 const long long jw = cbase + q;
-                s_words[q] = (jw >= 0 && jw < nwords) ? data[jw] : 0ull;
+                s_words[q] = (q < cw && jw >= 0 && jw < nwords) ? data[jw] : 0ull;
             }
         }
         __syncthreads();
@@ -370,10 +370,14 @@ __device__ __forceinline__ void phase_decode(const BatchCtx &C, const BatchOp &o
             float out[16];
             if (fits) {
                 const long long rel = (long long)(incl - nbits);
-                BitReader rd = staged ? BitReader{s_words, cw, 0, 0ull, 0ull, 0}
-                                      : BitReader{data, nwords, 0, 0ull, 0ull, 0};
-                rd.init(staged ? rel : cbase * 64 + rel);
-                decode_block<2>(rd, minexp, out);
+                if (staged) {
+                    LdsReader rd{reinterpret_cast<const uint32_t *>(s_words), 2 * (int)cw, (int)rel};
+                    decode_block<2>(rd, minexp, out);
+                } else {
+                    GlobalReader rd{data, nwords, 0, 0ull, 0ull, 0};
+                    rd.init(cbase * 64 + rel);
+                    decode_block<2>(rd, minexp, out);
+                }
             } else {
 #pragma unroll
                 for (int q = 0; q < 16; ++q) out[q] = 0.0f;
@@ -460,13 +464,13 @@ __global__ __launch_bounds__(kBatchThreads) void batch2d_kernel(BatchArgs A)
 {
     // the tile's levels and the codec's words are never live together (a barrier lies between)
     using Levels = typename Tile2dShared::template Levels<K>;
-    constexpr size_t kCodec = 8 * kDecLdsWords * kGroups;
+    constexpr size_t kCodec = 8 * (kDecLdsWords + kDecPad) * kGroups;
     constexpr size_t kPool = sizeof(Levels) > kCodec ? sizeof(Levels) : kCodec;
     __shared__ __align__(16) unsigned char s_pool[kPool];
     __shared__ __align__(16) Tile2dShared s_tile;
     Levels &s_levels = *reinterpret_cast<Levels *>(s_pool);
     const int grp = threadIdx.x >> 8;
-    unsigned long long *s_words = reinterpret_cast<unsigned long long *>(s_pool) + grp * kDecLdsWords;
+    unsigned long long *s_words = reinterpret_cast<unsigned long long *>(s_pool) + grp * (kDecLdsWords + kDecPad);
     __shared__ unsigned s_scan_[kGroups][4];
     __shared__ unsigned long long s_one[kGroups];
     __shared__ double s_red_[kGroups][256];

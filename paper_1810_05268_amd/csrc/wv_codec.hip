@@ -10,9 +10,10 @@
 //   * one lane encodes one block, so a 256-lane workgroup encodes a chunk of 256
 //     blocks; a block's bit length has a closed form per bit plane, so each lane
 //     first counts its bits and the workgroup scans them;
-//   * three launches place the chunks: every chunk counts its words and assembles
+//   * up to three launches place the chunks: every chunk counts its words and assembles
 //     its bits at chunk-local positions in a staging slot; one workgroup scans the
-//     word counts into offsets; every chunk copies its slot to its offset (a chunk
+//     word counts into offsets (in fields of few chunks each chunk sums the counts before
+//     it instead); every chunk copies its slot to its offset (a chunk
 //     longer than a slot, or every chunk without staging, is encoded again there).
 //     No workgroup waits for another: a single pass with a look-back over the
 //     preceding chunks spent most of its time in those waits, each a trip to memory;
@@ -100,6 +101,39 @@ __device__ __forceinline__ uint64_t job_base(const EncArgs &A, int e, unsigned l
     return base;
 }
 
+// Job e's header, stream size and next free offset (one lane).
+__device__ __forceinline__ void write_header(const EncArgs &A, int e, uint64_t base, unsigned long long data_words)
+{
+    const bool prefix_fits = base + (uint64_t)A.prefix_bytes <= A.cap;
+    uint8_t *hdr = A.out + base;
+    const unsigned long long total = (unsigned long long)A.prefix_bytes + 8ull * data_words;
+    if (!prefix_fits || base + total > A.cap) atomicOr(A.err, 4u);
+    if (prefix_fits) {
+        uint32_t *h32 = (uint32_t *)hdr;
+        h32[0] = kMagic;
+        h32[1] = kVersion;
+        h32[2] = (uint32_t)A.ndim;
+        h32[3] = (uint32_t)A.dims[0];
+        h32[4] = (uint32_t)A.dims[1];
+        h32[5] = (uint32_t)A.dims[2];
+        *(double *)(hdr + 24) = A.tol;
+        h32[8] = (uint32_t)A.nblocks;
+        h32[9] = (uint32_t)A.nchunks;
+        h32[10] = kBlocksPerChunk;
+        h32[11] = 0;
+        *(unsigned long long *)(hdr + 48) = data_words;
+        *(unsigned long long *)(hdr + 56) = total;
+        // zero the padding after the block lengths
+        const long long lb = kHdr + 8 * A.nchunks + 2 * A.nblocks;
+        for (long long i = lb; i < A.prefix_bytes; ++i) hdr[i] = 0;
+    }
+    const unsigned long long nxt = base + ((total + 255ull) & ~255ull);
+    *A.job[e].next = nxt;
+    if (A.job[e].size_out) *A.job[e].size_out = total;
+    atomicAdd(&A.stats[0], total);
+    atomicMax(&A.stats[1], nxt);
+}
+
 // Exclusive scan of job e's chunk word counts into offs (and the stream's chunk offsets),
 // then the header, the stream size and the next free offset; one workgroup.  Each lane
 // sums a run of up to 16 counts held in registers.
@@ -152,34 +186,12 @@ __device__ __forceinline__ void scan_chunks(const EncArgs &A, int e, unsigned lo
         }
     }
     if (tid != 0) return;
-    const unsigned long long total = (unsigned long long)A.prefix_bytes + 8ull * data_words;
-    if (!prefix_fits || base + total > A.cap) atomicOr(A.err, 4u);
-    if (prefix_fits) {
-        uint32_t *h32 = (uint32_t *)hdr;
-        h32[0] = kMagic;
-        h32[1] = kVersion;
-        h32[2] = (uint32_t)A.ndim;
-        h32[3] = (uint32_t)A.dims[0];
-        h32[4] = (uint32_t)A.dims[1];
-        h32[5] = (uint32_t)A.dims[2];
-        *(double *)(hdr + 24) = A.tol;
-        h32[8] = (uint32_t)A.nblocks;
-        h32[9] = (uint32_t)A.nchunks;
-        h32[10] = kBlocksPerChunk;
-        h32[11] = 0;
-        *(unsigned long long *)(hdr + 48) = data_words;
-        *(unsigned long long *)(hdr + 56) = total;
-        // zero the padding after the block lengths
-        const long long lb = kHdr + 8 * A.nchunks + 2 * A.nblocks;
-        for (long long i = lb; i < A.prefix_bytes; ++i) hdr[i] = 0;
-    }
-    const unsigned long long nxt = base + ((total + 255ull) & ~255ull);
-    *A.job[e].next = nxt;
-    if (A.job[e].size_out) *A.job[e].size_out = total;
-    atomicAdd(&A.stats[0], total);
-    atomicMax(&A.stats[1], nxt);
+    write_header(A, e, base, data_words);
 }
 
+// A 400^3 field of 11.4 MB: 76 us (2270 vector instructions a wave; 97 us and 3090 before the
+// exponents came from one maximum of the magnitudes, the transposes were bit inserts, and a
+// plane's groups were put out in one piece).
 // Pass 1, one workgroup per chunk (and field): the block lengths, the chunk's word count, and, when it fits a staging slot, the chunk's bits, assembled in
 // LDS at chunk-local positions.  Chunks are independent: no workgroup waits for another.
 template <int ND, bool VEC>
@@ -229,16 +241,32 @@ __global__ __launch_bounds__(256) void encode_scan_kernel(EncArgs A)
 
 // Pass 3, one workgroup per chunk: a staged chunk is copied to its offset; a chunk too
 // long for its slot (or every chunk, without staging) is encoded again and emitted there.
-template <int ND, bool VEC>
+// SCAN (fields of few chunks): there is no pass 2, every workgroup sums the counts before
+// its chunk itself, and a field's last one writes the header.  For a field of 75 chunks the
+// launch saved, 4.5 us and a gap, was a sixth of its encode; from about a thousand chunks on
+// the sums cost as much.
+template <int ND, bool VEC, bool SCAN>
 __global__ __launch_bounds__(256) void encode_place_kernel(EncArgs A)
 {
     __shared__ unsigned s_scan[4];
     const int tid = threadIdx.x;
     const long long c = blockIdx.x;
     const int e = blockIdx.y;
-    const uint64_t base = *A.job[e].base;   // pass 2 has written the bases that follow another field
     const uint32_t cw = A.words[e * A.nchunks + c];
-    const unsigned long long off = A.offs[e * A.nchunks + c];
+    uint64_t base;
+    unsigned long long off;
+    if constexpr (SCAN) {
+        __shared__ unsigned long long s_scan64[4];
+        base = job_base(A, e, s_scan64);
+        off = wg_total(A.words + e * A.nchunks, c, s_scan64);
+        if (tid == 0) {
+            if (base + (uint64_t)A.prefix_bytes <= A.cap) ((uint64_t *)(A.out + base + kHdr))[c] = off;
+            if (c == A.nchunks - 1) write_header(A, e, base, off + cw);
+        }
+    } else {
+        base = *A.job[e].base;   // pass 2 has written the bases that follow another field
+        off = A.offs[e * A.nchunks + c];
+    }
     if (A.staging && base + (uint64_t)A.prefix_bytes <= A.cap) {
         const long long b = c * kBlocksPerChunk + tid;
         if (b < A.nblocks) ((uint16_t *)(A.out + base + kHdr + 8 * A.nchunks))[b] = A.lens[e * A.nblocks + b];
@@ -272,12 +300,17 @@ struct DecArgs {
     long long nblocks, nchunks, prefix_bytes;
 };
 
+// One lane per block; bound by the instructions of the waves that hold coded blocks.  A 400^3
+// field of 11.4 MB: 78 us (2000 vector instructions a wave on average, of which the two plane
+// transposes 512, the inverse transform 576; 102 us and 2870 before the transposes were bit
+// inserts, the lifting butterflies, the group tests read from one window and the bits from
+// LDS words by funnel shifts).  Four waves a SIMD: at its natural 134 registers (three) 85 us.
 template <int ND, bool VEC>
-__global__ __launch_bounds__(256) void decode_kernel(DecArgs A)
+__global__ __launch_bounds__(256, 4) void decode_kernel(DecArgs A)
 {
     constexpr int S = ND == 3 ? 64 : 16;
     __shared__ unsigned s_scan[4];
-    __shared__ unsigned long long s_words[kDecLdsWords];
+    __shared__ unsigned long long s_words[kDecLdsWords + kDecPad];
     const int tid = threadIdx.x;
     const long long c = blockIdx.x;
     const long long b = c * kBlocksPerChunk + tid;
@@ -326,21 +359,26 @@ __global__ __launch_bounds__(256) void decode_kernel(DecArgs A)
     // so that every word read below stays inside the readable range
     long long cbase = (long long)chunk_off[c];
     cbase = cbase < 0 ? 0 : (cbase > nwords ? nwords : cbase);
-    const long long cw = ((long long)total_bits + 63) / 64 + 1;   // + the reader's look-ahead word
+    const long long cw = ((long long)total_bits + 63) / 64 + 1;   // + a word of look-ahead
     const bool staged = cw <= kDecLdsWords;
     if (staged) {
-        for (long long i = tid; i < cw; i += 256) {
+        for (long long i = tid; i < cw + kDecPad; i += 256) {
             const long long j = cbase + i;
-            s_words[i] = (j >= 0 && j < nwords) ? data[j] : 0ull;
+            s_words[i] = (i < cw && j >= 0 && j < nwords) ? data[j] : 0ull;
         }
     }
     __syncthreads();
     if (!valid) return;
     const long long rel = (long long)(incl - nbits);
-    BitReader rd = staged ? BitReader{s_words, cw, 0, 0ull, 0ull, 0} : BitReader{data, nwords, 0, 0ull, 0ull, 0};
-    rd.init(staged ? rel : cbase * 64 + rel);
     float out[S];
-    decode_block<ND>(rd, minexp, out);
+    if (staged) {
+        LdsReader rd{reinterpret_cast<const uint32_t *>(s_words), 2 * (int)cw, (int)rel};
+        decode_block<ND>(rd, minexp, out);
+    } else {
+        GlobalReader rd{data, nwords, 0, 0ull, 0ull, 0};
+        rd.init(cbase * 64 + rel);
+        decode_block<ND>(rd, minexp, out);
+    }
     store_block<ND, VEC>(field, sub, A.dims, A.pitch, A.nb, b, out);
 }
 
@@ -371,6 +409,8 @@ size_t codec_max_bytes(const CodecDims &cd)
 }
 
 namespace {
+
+constexpr long long kScanChunks = 1024;   // fields of up to so many chunks have no scan pass
 
 size_t pad256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -428,13 +468,18 @@ hipError_t launch_encode(const CodecDims &cd, const EncJob *jobs, int njobs, dou
         if (vec) hipLaunchKernelGGL((encode_count_kernel<2, true>), grid, dim3(256), 0, s, A);
         else hipLaunchKernelGGL((encode_count_kernel<2, false>), grid, dim3(256), 0, s, A);
     }
-    hipLaunchKernelGGL(encode_scan_kernel, dim3((unsigned)njobs), dim3(256), 0, s, A);
+    const bool scan = cd.nchunks <= kScanChunks;
+    if (!scan) hipLaunchKernelGGL(encode_scan_kernel, dim3((unsigned)njobs), dim3(256), 0, s, A);
+    auto place = [&](auto with, auto without) {
+        if (scan) hipLaunchKernelGGL(with, grid, dim3(256), 0, s, A);
+        else hipLaunchKernelGGL(without, grid, dim3(256), 0, s, A);
+    };
     if (cd.ndim == 3) {
-        if (vec) hipLaunchKernelGGL((encode_place_kernel<3, true>), grid, dim3(256), 0, s, A);
-        else hipLaunchKernelGGL((encode_place_kernel<3, false>), grid, dim3(256), 0, s, A);
+        if (vec) place(encode_place_kernel<3, true, true>, encode_place_kernel<3, true, false>);
+        else place(encode_place_kernel<3, false, true>, encode_place_kernel<3, false, false>);
     } else {
-        if (vec) hipLaunchKernelGGL((encode_place_kernel<2, true>), grid, dim3(256), 0, s, A);
-        else hipLaunchKernelGGL((encode_place_kernel<2, false>), grid, dim3(256), 0, s, A);
+        if (vec) place(encode_place_kernel<2, true, true>, encode_place_kernel<2, true, false>);
+        else place(encode_place_kernel<2, false, true>, encode_place_kernel<2, false, false>);
     }
     return hipGetLastError();
 }

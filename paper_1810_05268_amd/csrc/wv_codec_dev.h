@@ -68,17 +68,19 @@ __device__ __forceinline__ void fwd_lift(int32_t *p, const int S0, const int S)
     p[S0] = x; p[S0 + S] = y; p[S0 + 2 * S] = z; p[S0 + 3 * S] = w;
 }
 
-// Inverse: each real-valued forward step undone in reverse order (wrap-around
-// arithmetic keeps any stream well defined).
+// Inverse: each real-valued forward step undone in reverse order (wrap-around arithmetic
+// keeps any stream well defined).  Undoing x = (x + w) / 2, w -= x is w += x, x = 2x - w,
+// which is the pair (w + x, x - w).
 __device__ __forceinline__ void inv_lift(int32_t *p, const int S0, const int S)
 {
-    uint32_t x = (uint32_t)p[S0], y = (uint32_t)p[S0 + S], z = (uint32_t)p[S0 + 2 * S], w = (uint32_t)p[S0 + 3 * S];
+    const uint32_t x = (uint32_t)p[S0], z = (uint32_t)p[S0 + 2 * S];
+    uint32_t y = (uint32_t)p[S0 + S], w = (uint32_t)p[S0 + 3 * S];
     y += (uint32_t)((int32_t)w >> 1); w -= (uint32_t)((int32_t)y >> 1);
-    y += w; w <<= 1; w -= y;
-    z += x; x <<= 1; x -= z;
-    y += z; z <<= 1; z -= y;
-    w += x; x <<= 1; x -= w;
-    p[S0] = (int32_t)x; p[S0 + S] = (int32_t)y; p[S0 + 2 * S] = (int32_t)z; p[S0 + 3 * S] = (int32_t)w;
+    const uint32_t y1 = y + w, w1 = w - y, z1 = z + x, x1 = x - z;
+    p[S0] = (int32_t)(x1 - w1);
+    p[S0 + S] = (int32_t)(y1 + z1);
+    p[S0 + 2 * S] = (int32_t)(z1 - y1);
+    p[S0 + 3 * S] = (int32_t)(w1 + x1);
 }
 
 template <int ND>
@@ -134,7 +136,9 @@ __device__ __forceinline__ void inv_transform(int32_t *q)
 __device__ __forceinline__ uint64_t low_mask(int n) { return n >= 64 ? ~0ull : ((1ull << n) - 1ull); }
 
 // In-place transpose of a 32 x 32 bit matrix: bit k of a[s] moves to bit s of a[k]
-// (five stages of masked block swaps; an involution).
+// (five stages of masked block swaps; an involution).  The swaps of half-words and bytes
+// are byte permutes, the others a shift and a bit-field insert per word: 256 operations
+// (480 as three exclusive ors each).
 constexpr uint32_t kSwapMask[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
 
 __device__ __forceinline__ void transpose32(uint32_t *a)
@@ -146,9 +150,17 @@ __device__ __forceinline__ void transpose32(uint32_t *a)
 #pragma unroll
         for (int s = 0; s < 32; ++s) {
             if (!(s & j)) {
-                const uint32_t t = ((a[s] >> j) ^ a[s + j]) & m;
-                a[s] ^= t << j;
-                a[s + j] ^= t;
+                const uint32_t x = a[s], y = a[s + j];
+                if (st == 0) {          // bytes: x = y1 y0 x1 x0, y = y3 y2 x3 x2
+                    a[s] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+                    a[s + j] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+                } else if (st == 1) {
+                    a[s] = __builtin_amdgcn_perm(y, x, 0x06020400u);
+                    a[s + j] = __builtin_amdgcn_perm(y, x, 0x07030501u);
+                } else {
+                    a[s] = (x & ~(m << j)) | ((y << j) & (m << j));
+                    a[s + j] = (y & ~m) | ((x >> j) & m);
+                }
             }
         }
     }
@@ -161,7 +173,7 @@ struct Emitter {
     long long pos;
     unsigned long long acc;
     template <typename Sink>
-    __device__ __forceinline__ void put(unsigned long long v, int nb, Sink &sink)
+    __device__ __forceinline__ void put(unsigned long long v, int nb, Sink &sink)   // nb <= 64
     {
         const int off = (int)(pos & 63);
         acc |= v << off;
@@ -178,7 +190,25 @@ struct Emitter {
     }
 };
 
-struct BitReader {
+// Bit readers: peek() gives the next 64 bits, skip() passes up to 64 of them.
+// From LDS words, the stream's and two of zeros behind it (which a corrupt stream may read
+// on and on): three word reads and two funnel shifts a peek.
+struct LdsReader {
+    const uint32_t *w;
+    int last;                // the zero words' place
+    int pos;
+    __device__ __forceinline__ unsigned long long peek() const
+    {
+        const int i = min(pos >> 5, last);
+        const uint32_t a = w[i], b = w[i + 1], c = w[i + 2];
+        return (unsigned long long)__builtin_amdgcn_alignbit(c, b, (uint32_t)pos) << 32 |
+               __builtin_amdgcn_alignbit(b, a, (uint32_t)pos);
+    }
+    __device__ __forceinline__ void skip(int nb) { pos += nb; }
+};
+
+// From global memory (a chunk too long for LDS); words outside [0, nw) read as zero.
+struct GlobalReader {
     const unsigned long long *data;
     long long nw;
     long long widx;
@@ -295,18 +325,14 @@ struct BlockEnc {
                                             uint32_t (&m_hi)[32])
     {
         valid = valid_;
-        bool nonzero = false;
+        // magnitudes order as their bits do: the largest gives the exponent, and whether any
+        // value is not finite or not zero
+        uint32_t most = 0u;
 #pragma unroll
-        for (int i = 0; i < S; ++i) {
-            const uint32_t u = __float_as_uint(v[i]);
-            const int E = (int)((u >> 23) & 0xFFu);
-            if (E == 255) finite = false;
-            if (u & 0x7FFFFFFFu) {
-                nonzero = true;
-                const int e = E == 0 ? -126 : E - 126;
-                emax = e > emax ? e : emax;
-            }
-        }
+        for (int i = 0; i < S; ++i) most = max(most, __float_as_uint(v[i]) & 0x7FFFFFFFu);
+        finite = most < 0x7F800000u;
+        const bool nonzero = most != 0u;
+        emax = most < 0x00800000u ? -126 : (int)(most >> 23) - 126;
         int prec = emax - minexp + 2 * (ND + 1);
         prec = prec > 32 ? 32 : prec;
         coded = valid && finite && nonzero && prec > 0;
@@ -314,9 +340,17 @@ struct BlockEnc {
 #pragma unroll
         for (int k = 0; k < 32; ++k) m_lo[k] = m_hi[k] = 0u;
         if (__ballot(coded) != 0ull) {
+            // exact scaling, truncation; an uncoded block's integers are not used, but a value
+            // that is not finite has none
             int32_t q[S];
+            const int sh = 30 - emax;
+            if (__any(!finite)) {
 #pragma unroll
-            for (int i = 0; i < S; ++i) q[i] = coded ? (int32_t)ldexpf(v[i], 30 - emax) : 0;   // exact scaling, truncation
+                for (int i = 0; i < S; ++i) q[i] = coded ? (int32_t)ldexpf(v[i], sh) : 0;
+            } else {
+#pragma unroll
+                for (int i = 0; i < S; ++i) q[i] = (int32_t)ldexpf(v[i], sh);
+            }
             fwd_transform<ND>(q);
 #pragma unroll
             for (int s = 0; s < 32; ++s) {
@@ -333,8 +367,8 @@ struct BlockEnc {
 #pragma unroll
                 for (int s = 0; s < 32; ++s) {
                     const uint32_t a = m_lo[s], b = m_hi[s];
-                    m_lo[s] = (a >> 16) | (b & 0xFFFF0000u);
-                    m_hi[s] = (a & 0xFFFFu) | (b << 16);
+                    m_lo[s] = __builtin_amdgcn_perm(b, a, 0x07060302u);   // upper halves
+                    m_hi[s] = __builtin_amdgcn_perm(b, a, 0x05040100u);   // lower halves
                 }
                 transpose32(m_lo);   // word k < 16: plane k+16 of 0..31; k >= 16: plane k of 32..63
                 if (__ballot(coded && kmin < 16) != 0ull) transpose32(m_hi);   // planes 0..15 likewise
@@ -406,18 +440,40 @@ struct BlockEnc {
         for (int k = 31; k >= kmin_w; --k) {
             if (coded && k >= kmin) {
                 const unsigned long long mk = (unsigned long long)m_hi[k] << 32 | m_lo[k];
-                if (n > 0) em.put(mk & low_mask(n), n, sink);
+                // the plane's verbatim bits, then its groups (1, the zeros before the next
+                // one bit, that bit) and the 0 that ends them, collected in up to 64 bits
+                unsigned long long out = mk & low_mask(n);
+                int used = n;
                 if (n < S) {
                     unsigned long long r = mk >> n;
                     while (r != 0ull) {
                         const int z = __ffsll((long long)r) - 1;
-                        em.put(1ull, 1, sink);
-                        em.put(1ull << z, z + 1, sink);
+                        if (used + z + 2 > 64) {
+                            em.put(out, used, sink);
+                            out = 0ull;
+                            used = 0;
+                        }
+                        if (z == 63) {          // 65 bits: the group test by itself (S = 64, n = 0)
+                            em.put(1ull, 1, sink);
+                            out = 1ull << 63;
+                            used = 64;
+                        } else {
+                            out |= (1ull | (2ull << z)) << used;
+                            used += z + 2;
+                        }
                         n += z + 1;
-                        r = (z + 1 < 64) ? (r >> (z + 1)) : 0ull;
+                        r = z == 63 ? 0ull : r >> (z + 1);
                     }
-                    if (n < S) em.put(0ull, 1, sink);
+                    if (n < S) {
+                        if (used == 64) {
+                            em.put(out, 64, sink);
+                            out = 0ull;
+                            used = 0;
+                        }
+                        ++used;
+                    }
                 }
+                em.put(out, used, sink);
             }
         }
         em.flush(sink);
@@ -426,8 +482,8 @@ struct BlockEnc {
 
 // Decode one block from rd (positioned at its first bit) into out[S] (C order of the
 // block, axis 0 fastest).
-template <int ND>
-__device__ __forceinline__ void decode_block(BitReader &rd, int minexp, float *out)
+template <int ND, typename Reader>
+__device__ __forceinline__ void decode_block(Reader &rd, int minexp, float *out)
 {
     constexpr int S = ND == 3 ? 64 : 16;
     const bool coded = rd.peek() & 1ull;
@@ -442,53 +498,92 @@ __device__ __forceinline__ void decode_block(BitReader &rd, int minexp, float *o
     int prec = emax - minexp + 2 * (ND + 1);
     prec = prec > 32 ? 32 : prec;
     const int kmin = 32 - prec;
-    unsigned long long m[32];
+    // planes 16..31 and 0..15 in half-words: word k < 16 of hi (lo) is plane 16 + k (k) of
+    // coefficients 0..31, word 16 + k that of 32..63; a wave none of whose blocks codes a
+    // plane below 16 has no lo
+    uint32_t hi[32], lo[32];
+    const bool low = __any(kmin < 16);
     int n = 0;
-#pragma unroll
-    for (int k = 31; k >= 0; --k) {
+    auto plane = [&](int k) -> unsigned long long {
         unsigned long long mk = 0ull;
         if (k >= kmin) {
             if (n > 0) {
                 mk = rd.peek() & low_mask(n);
                 rd.skip(n);
             }
-            while (n < S) {
-                const bool g = rd.peek() & 1ull;
-                rd.skip(1);
-                if (!g) break;
-                const int rem = S - n;
-                const unsigned long long win = rd.peek() & low_mask(rem);
-                if (win == 0ull) {
-                    rd.skip(rem);
-                    n = S;
-                    break;
+            if (n < S) {
+                // group tests out of one 64-bit window, read again where a run of zeros (or
+                // the groups) reach its end
+                unsigned long long w = rd.peek();
+                int used = 0;
+                for (;;) {
+                    const bool g = w & 1ull;
+                    ++used;
+                    if (!g) break;
+                    w >>= 1;
+                    const int rem = S - n;
+                    if (ND == 3 && w == 0ull && used + rem > 64) {
+                        rd.skip(used);
+                        used = 0;
+                        w = rd.peek();
+                    }
+                    const unsigned z = (unsigned)__ffsll((long long)w) - 1u;   // no bit: larger than any rem
+                    if (z >= (unsigned)rem) {
+                        used += rem;
+                        n = S;
+                        break;
+                    }
+                    mk |= 1ull << (n + z);
+                    n += z + 1;
+                    used += z + 1;
+                    if (n >= S) break;
+                    w >>= z + 1;            // z < 63: n would be S
+                    if (ND == 3 && used >= 64) {
+                        rd.skip(used);
+                        used = 0;
+                        w = rd.peek();
+                    }
                 }
-                const int z = __ffsll((long long)win) - 1;
-                mk |= 1ull << (n + z);
-                rd.skip(z + 1);
-                n += z + 1;
+                rd.skip(used);
             }
         }
-        m[k] = mk;
-    }
-    uint32_t lo[32], hi[32];
+        return mk;
+    };
 #pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        lo[k] = (uint32_t)m[k];
-        hi[k] = (uint32_t)(m[k] >> 32);
+    for (int k = 31; k >= 16; --k) {
+        const unsigned long long mk = plane(k);
+        hi[k - 16] = (uint32_t)mk;
+        hi[k] = (uint32_t)(mk >> 32);
     }
-    transpose32(lo);
-    if constexpr (ND == 3) transpose32(hi);
+    transpose32(hi);
+#pragma unroll
+    for (int s = 0; s < 32; ++s) lo[s] = 0u;
+    if (low) {
+#pragma unroll
+        for (int k = 15; k >= 0; --k) {
+            const unsigned long long mk = plane(k);
+            lo[k] = (uint32_t)mk;
+            lo[k + 16] = (uint32_t)(mk >> 32);
+        }
+        transpose32(lo);
+    }
     int32_t q[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-        const uint32_t u = s < 32 ? lo[s] : hi[s - 32];
+        const uint32_t u = s < 32 ? __builtin_amdgcn_perm(hi[s & 31], lo[s & 31], 0x05040100u)
+                                  : __builtin_amdgcn_perm(hi[s & 31], lo[s & 31], 0x07060302u);
         const int dst = ND == 3 ? kPerm3.v[s] : kPerm2.v[s];
         q[dst] = (int32_t)((u ^ 0xAAAAAAAAu) - 0xAAAAAAAAu);
     }
     inv_transform<ND>(q);
+    // one rounding: to binary32 by the conversion, unless a value could be subnormal
+    if (__all(emax >= -96)) {
 #pragma unroll
-    for (int i = 0; i < S; ++i) out[i] = (float)ldexp((double)q[i], emax - 30);   // one rounding
+        for (int i = 0; i < S; ++i) out[i] = ldexpf((float)q[i], emax - 30);
+    } else {
+#pragma unroll
+        for (int i = 0; i < S; ++i) out[i] = (float)ldexp((double)q[i], emax - 30);
+    }
 }
 
 // Write decoded block b (values out, C order) into field, or sub - decoded when sub is
@@ -537,6 +632,7 @@ __device__ __forceinline__ void store_block(float *field, const float *sub, cons
 
 constexpr int kLdsWords = 2048;      // chunk bitstreams up to 16 KB are assembled in LDS
 constexpr int kDecLdsWords = 2048;   // and chunks up to 16 KB are staged in LDS for decoding
+constexpr int kDecPad = 2;           // zero words behind them
 
 }  // namespace
 

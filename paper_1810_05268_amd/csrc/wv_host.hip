@@ -2431,12 +2431,15 @@ int encode_one(const float *field, int ndim, const int *dims, double tol, void *
     HIPCHK(launch_fill_u64((uint64_t *)b, kCodecBk / 8, 0, s));
     const EncJob job{field, nullptr, base, next, nullptr};
     HIPCHK(launch_encode(cd, &job, 1, tol, (uint8_t *)out, cap, b + kCodecBk, staged, err, st, s));
-    unsigned e = 0;
-    unsigned long long tot[2] = {0, 0};
-    HIPCHK(hipMemcpyAsync(&e, err, 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(tot, st, 16, hipMemcpyDeviceToHost, s));
+    // the error word and the stream size in one copy
+    uint8_t bk[208];
+    HIPCHK(hipMemcpyAsync(bk, b, sizeof(bk), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    *nbytes = (size_t)tot[0];
+    unsigned e = 0;
+    unsigned long long tot = 0;
+    std::memcpy(&e, bk, 4);
+    std::memcpy(&tot, bk + 192, 8);
+    *nbytes = (size_t)tot;
     if (e & 4u) return WV_ECAP;
     if (e & 2u) return WV_EINVAL;
     return WV_OK;
