@@ -357,7 +357,7 @@ SERVING_VMAX = 3700.0   # m/s: bound of every serving model (layers up to 3.5 km
 
 def serving_leg(nreq, rate, pool_bytes, max_active, tol, cap, max_batch, saturation):
     """The serving stream: seeded Poisson arrivals of mixed shots through the engine, 2-D
-    shots batched (one persistent launch per batch).  Untimed calls measure the
+    shots batched (one call per batch).  Untimed calls measure the
     compressibility profiles of each class's first requests; every request of the class
     then gets a checkpoint budget of 1.5 x the compressed full trajectory of their
     elementwise maximum (capped) and the plan for it as the hint.  All shots take their

@@ -123,8 +123,8 @@ typedef struct {
     double ms_adjoint;   /* with timing: device ms in adjoint steps (stencil + gradient + residual injection) */
     double ms_store;     /* with timing: device ms writing checkpoints (copies or encodes) */
     double ms_restore;   /* with timing: device ms restoring checkpoints (decodes; uncompressed restores are free) */
-    double ms_fwd_kernel;/* with timing bit 1: device ms inside the forward stencil launches (one per advance) */
-    double ms_adj_kernel;/* with timing bit 1: device ms inside the adjoint+gradient stencil launches (one per reverse) */
+    double ms_fwd_kernel;/* with timing bit 1: device ms inside the forward stencil launches (one per advance; 2-D, time order 2: one per group of advances) */
+    double ms_adj_kernel;/* with timing bit 1: device ms inside the adjoint+gradient stencil launches (one per reverse; 2-D, time order 2: one per group of reverses) */
     long retries;        /* compressed runs repeated because checkpoints outgrew mem_budget (see WV_EARENA) */
     double profile[WV_PROFILE];  /* compressed runs: stream bytes of one field of u^k at k = 0 (the empty
                             field) and k = ceil(j nt / (WV_PROFILE-1)), j = 1..WV_PROFILE-1, taken from
@@ -292,7 +292,7 @@ int wv_zfpk_decode(const void *in, size_t nbytes, int ndim, const int *dims, flo
 
 /* ------------------------------------------------------------------ batched 2-D shots */
 
-/* Misfit and gradient of nshots 2-D shots at once, advanced by one persistent kernel.
+/* Misfit and gradient of nshots 2-D shots at once, advanced together.
  * Shots are independent (the paper computes one gradient per shot and sums them, Sec.
  * "Example adjoint problem: Seismic inversion"), and a small 2-D shot cannot fill the GPU
  * one step per launch.  The shots of a batch share the grid (n, h, nbl), space order,
@@ -300,15 +300,15 @@ int wv_zfpk_decode(const void *in, size_t nbytes, int ndim, const int *dims, flo
  * positions and observed data are their own.  They run the checkpoint schedule of
  * wv_misfit_gradient with the same slot count M (each shot has mem_budget bytes of
  * checkpoint memory; compressed, M is the smallest any shot's compressibility probe
- * plans, unless ratio_hint > 0 plans it), and one kernel launch executes the whole
- * reversal: the host turns the schedule into a program of phases (stencil steps, source
- * and residual injections, checkpoint encodes and decodes, the misfit), and every phase
- * runs for all shots, with a device-wide barrier between phases (a plain launch of at
+ * plans, unless ratio_hint > 0 plans it).  The host turns the schedule into a program of
+ * phases, each run for all shots: every group of forward or adjoint steps is one launch, and
+ * so is every run of other phases between them (checkpoint encodes and decodes, copies, data
+ * rows, the misfit), with a device-wide barrier between its phases (a plain launch of at
  * most as many workgroups as the device holds at once).  Each shot's arithmetic is the
  * solo call's, in the same order, so its misfit, gradient and d_sim are bit-identical to
  * wv_misfit_gradient's for that shot alone, whatever else is in the batch.  If a barrier
  * cannot complete within a fraction of a second (other streams' kernels keep some of
- * the launch's workgroups off the device), the launch ends early; a wide one is launched
+ * the launch's workgroups off the device), the run ends early; a wide one is launched
  * again with half the workgroups (twice at most), and then every shot runs alone,
  * through wv_misfit_gradient in its part of ws: the same results, with stats.retries
  * counting the launches that ended early.  (The environment variable WV_BATCH_SPIN_LIMIT, read at each

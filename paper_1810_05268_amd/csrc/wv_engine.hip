@@ -16,8 +16,8 @@
 // With batching on (wv_engine_set_batching), 2-D requests go to a batch lane instead:
 // one more worker takes every queued 2-D request that shares the oldest one's grid,
 // order, steps, time step, receiver count, tolerance and budget (up to max_batch of
-// them) and runs them as one batched call (wv_batch_misfit_gradient: one persistent
-// kernel advances all of them), while the 3-D requests keep their own workers.  Requests
+// them) and runs them as one batched call (wv_batch_misfit_gradient: every
+// launch advances all of them), while the 3-D requests keep their own workers.  Requests
 // that arrive while a batch runs join the next one.
 //
 // Every request is computed exactly as it would be alone (same kernels and reduction
@@ -287,8 +287,8 @@ struct wv_engine {
                 grads[i] = r->grad;
                 dsims[i] = r->d_sim;
             }
-            // a batch of one runs the solo path (the same bits; the persistent launch pays a
-            // device-wide barrier per phase that only several shots amortise)
+            // a batch of one runs the solo path (the same bits, without the device-wide
+            // barriers between the phases of a batch's launches)
             int rc = WV_EINVAL;
             if (bytes && n == 1)
                 rc = wv_misfit_gradient(&ms[0], &gs[0], dobs[0], batch[0]->mem_budget, batch[0]->tol,

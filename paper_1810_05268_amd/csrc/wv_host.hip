@@ -2062,7 +2062,7 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
     const Grid &g = su[0].g;
     const int cdims[3] = {g.nx, g.nz, 1};
     const CodecDims cd = codec_dims(2, cdims, g.px);
-    const int nwg = batch2d_resident_workgroups(g.K);
+    const int nwg = batch2d_resident_workgroups();
     if (nwg < 1) return hip_fail(hipErrorInvalidValue, "batch2d_resident_workgroups", __LINE__);
     // per-shot set-up, as a solo call: tables, w, velocity check, zeroed work arrays
     std::vector<Dev> dv((size_t)nshots);
@@ -2139,27 +2139,19 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
     }
     A.nrec = geoms[0].nrec;
     A.nt = N;
-    // Launch shape.  Every workgroup takes part in every grid barrier, whose cost grows
-    // with the number of arrivals, so the grid is no larger than the widest phase needs:
-    // a step phase takes one item per tile, the codec phases one per 256-block chunk and
-    // field.  Phases with more items loop over them.
+    // Launch shape of the persistent kernel.  Every workgroup takes part in every grid barrier,
+    // whose cost grows with the number of arrivals, so the grid is no larger than its widest
+    // phase needs: one item per 256-block chunk and field for the codec (phases with more
+    // loop over them); without the codec, a workgroup a CU for the misfit.
     const int steps = tile2d_choose(g.K, g.nx, g.nz, nshots);
-    {
-        const int K = g.K, core = kTileRegion - 2 * tile2d_halo(K, steps);
-        const long long tiles = (long long)((g.nx + core - 1) / core) * ((g.nz + core - 1) / core);
-        const long long widest = nshots * std::max(tiles, tol > 0 ? tile2d_jobs(K) * cd.nchunks / 2 : 1LL);
-        A.nwg = (int)std::min<long long>(nwg, std::max<long long>(widest, 8));
-    }
+    A.nwg = (int)std::min<long long>(
+        nwg, tol > 0 ? std::max<long long>((long long)nshots * tile2d_jobs(g.K) * cd.nchunks, 8) : 256);
     A.fstride = (long long)(L[0].fstride / 4);
     A.slot_elems = (long long)su[0].Pf * 2;
     A.bar = reinterpret_cast<unsigned *>(base + B.hdr);
     // WV_BATCH_SPIN_LIMIT (for tests of the fallback) lowers the barrier's poll bound
     A.spin_limit = 1u << 18;
     if (const char *sl = std::getenv("WV_BATCH_SPIN_LIMIT")) A.spin_limit = (unsigned)std::strtoul(sl, nullptr, 10);
-    for (int i = 0; i < nshots; ++i) {
-        A.src_pts = std::max(A.src_pts, shots[i].src.npts);
-        A.rec_pts = std::max(A.rec_pts, shots[i].rec.npts);
-    }
     HIPCHK(hipMemcpyAsync(base + B.desc, shots.data(), shots.size() * sizeof(BatchShot), hipMemcpyHostToDevice, s));
     int shrinks = 0;   // relaunches with half the workgroups after a barrier gave up
     for (int attempt = 0;; ++attempt) {
@@ -2172,7 +2164,6 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         // cannot happen: the program is bounded by the action count, and the executor's
         // bookkeeping always has the levels a step reads
         if (!plan.valid || (int)plan.ops.size() > B.max_ops) return WV_EINVAL;
-        A.nops = (int)plan.ops.size();
         for (int i = 0; i < nshots; ++i) {
             Dev &d = dv[i];
             HIPCHK(launch_fill_f32(d.Lm[0], su[i].Pf, 0.0f, s));
@@ -2189,7 +2180,19 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         HIPCHK(hipEventCreate(&e0));
         HIPCHK(hipEventCreate(&e1));
         HIPCHK(hipEventRecord(e0, s));
-        HIPCHK(launch_batch2d(A, g.K, s));
+        for (size_t i = 0; i < plan.ops.size();) {
+            auto steps_op = [&](size_t q) { return plan.ops[q].kind == kOpStep || plan.ops[q].kind == kOpAdj; };
+            if (steps_op(i)) {
+                HIPCHK(launch_batch_steps(A, plan.ops[i++], s));
+                continue;
+            }
+            size_t j = i;
+            while (j < plan.ops.size() && !steps_op(j)) ++j;
+            A.op0 = (int)i;
+            A.nops = (int)(j - i);
+            HIPCHK(launch_batch2d(A, s));
+            i = j;
+        }
         HIPCHK(hipEventRecord(e1, s));
         HIPCHK(hipStreamSynchronize(s));
         float ms = 0.0f;

@@ -212,9 +212,8 @@ hipError_t launch_decode(const CodecDims &cd, const uint8_t *in, const DecJob *j
                          hipStream_t s);
 
 // ---------------------------------------------------------------- batched 2-D solver (wv_batch.hip)
-// Several 2-D shots of one grid, order, step count and schedule advanced together by
-// one persistent kernel that runs a program of phases, all shots per phase, with a
-// device-wide barrier between phases.  Each shot keeps the buffers of a solo call
+// Several 2-D shots of one grid, order, step count and schedule advanced together: every
+// step of their program is for all of them.  Each shot keeps the buffers of a solo call
 // (field arrays dense in 2-D).
 struct BatchShot {
     float *U, *UB, *DB, *Lm, *Z, *W;   // rings of field arrays, BatchArgs::fstride elements apart
@@ -239,8 +238,7 @@ struct BatchShot {
 // id + i), or level l of checkpoint slot b (uncompressed) as kBufSlot + 2 b + l.
 enum BatchBuf { kBufNone = -1, kBufZ = 0, kBufDB = 1, kBufL = 2, kBufU = 8, kBufUB = 32, kBufSlot = 48 };
 static_assert(kBufU + tile2d_ring(1) <= kBufUB && kBufUB + tile2d_decoded(1) <= kBufSlot, "buffer ids");
-// Steps of a 2-D OT2 program (built by Prog2d).  Run by launches for a lone shot; in a batch
-// every shot executes each one, and a device-wide barrier follows each.
+// Steps of a 2-D OT2 program (built by Prog2d).
 //   kOpStep:   ns forward steps from u^n in a and u^{n-1} in b; step j's level goes to c[j]
 //              (kBufNone: not kept) with the source sample n + j injected; bit j of e: data row
 //              n + j from the level u^{n+j}
@@ -268,12 +266,11 @@ struct BatchArgs {
     const BatchShot *shots;
     int nshots;
     const BatchOp *ops;
-    int nops;
+    int op0, nops;            // the ops a launch of the persistent kernel executes
     double gscale;
     double tol;
     int minexp;
     int nrec;                 // receivers per shot (every shot of a batch has as many)
-    int src_pts, rec_pts;     // largest scatter-table size over the shots (sources, receivers)
     int nt;
     long long fstride;        // elements from one array of a ring to the next
     long long slot_elems;     // elements of one uncompressed checkpoint slot (two fields)
@@ -281,9 +278,11 @@ struct BatchArgs {
     int nwg;                  // workgroups of the launch (at most what the device holds at once)
     unsigned spin_limit;      // polls before a barrier gives up and the launch aborts
 };
-// Workgroups the persistent kernel can keep resident for space order 2K (0 on error).
-int batch2d_resident_workgroups(int K);
+// Workgroups the persistent kernel can keep resident (0 on error).
+int batch2d_resident_workgroups();
 // Launch of the persistent kernel with A.nwg workgroups.
-hipError_t launch_batch2d(const BatchArgs &A, int K, hipStream_t s);
+hipError_t launch_batch2d(const BatchArgs &A, hipStream_t s);
+// Launch of a group of forward or adjoint steps of every shot.
+hipError_t launch_batch_steps(const BatchArgs &A, const BatchOp &op, hipStream_t s);
 
 }  // namespace wv

@@ -1,5 +1,5 @@
-// The program of a 2-D OT2 run: what the solo executor launches one by one and the batched
-// solver's persistent kernel executes in one launch.  Host only.
+// The program of a 2-D OT2 run: what the solo executor and the batched solver launch
+// op by op (the latter several other ops than steps at once).  Host only.
 //
 // A schedule's steps, checkpoint writes, reads and reverse steps are collected and emitted in
 // groups: up to `steps` forward or reverse steps in one pass over the tiles (a level goes

@@ -1,4 +1,4 @@
-// Launches of the 2-D multi-step tiles (see wv_tile2d_dev.h) for one shot.
+// Launches of the 2-D multi-step tiles (see wv_tile2d_dev.h), for one shot or a batch.
 #include <hip/hip_ext.h>
 
 #include "wv_tile2d_dev.h"
@@ -7,32 +7,53 @@ namespace wv {
 
 namespace {
 
-template <int K, bool GRAD, int R>
-__global__ __launch_bounds__(tile2d_threads(R)) void tile2d_kernel(const Grid g, const Tile2dArgs A, int tiles_x,
-                                                                   int tiles_z)
+template <int K, bool GRAD>
+__global__ __launch_bounds__(kTileThreads) void tile2d_kernel(const Grid g, const Tile2dArgs A, int tiles_x,
+                                                              int tiles_z)
 {
     __shared__ __align__(16) Tile2dShared S;
     __shared__ __align__(16) typename Tile2dShared::template Levels<K> L;
     const int lid = xcd_remap(blockIdx.x, tiles_x * tiles_z);
-    tile2d<K, GRAD, R>(g, A, lid % tiles_x, lid / tiles_x, S, L);
+    tile2d<K, GRAD>(g, A, lid % tiles_x, lid / tiles_x, S, L);
 }
 
-// One row of four points a lane (16 waves a region) while every CU gets at most one region;
-// two rows (8 waves, two regions a CU at once) beyond.  On 552^2 points at order 8, three
-// forward steps take 9.5 us with one row and 11.8 us with two (196 regions), four steps
-// 15.7 and 14.1 us (324 regions); four rows (4 waves) 15.2 and 17.9 us.
 template <int K>
 hipError_t launch_k(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev)
 {
     const int core = kTileRegion - 2 * tile2d_halo(K, A.ns);
     const int tx = (g.nx + core - 1) / core, tz = (g.nz + core - 1) / core;
-    auto go = [&](auto kern, int threads) {
-        if (ev.start) hipExtLaunchKernelGGL(kern, dim3(tx * tz), dim3(threads), 0, s, ev.start, ev.stop, 0, g, A, tx, tz);
-        else hipLaunchKernelGGL(kern, dim3(tx * tz), dim3(threads), 0, s, g, A, tx, tz);
+    auto go = [&](auto kern) {
+        const dim3 grid(tx * tz), wg(kTileThreads);
+        if (ev.start) hipExtLaunchKernelGGL(kern, grid, wg, 0, s, ev.start, ev.stop, 0, g, A, tx, tz);
+        else hipLaunchKernelGGL(kern, grid, wg, 0, s, g, A, tx, tz);
     };
-    const bool one = (long long)tx * tz <= device_cus();
-    if (A.G) one ? go(tile2d_kernel<K, true, 1>, tile2d_threads(1)) : go(tile2d_kernel<K, true, 2>, tile2d_threads(2));
-    else one ? go(tile2d_kernel<K, false, 1>, tile2d_threads(1)) : go(tile2d_kernel<K, false, 2>, tile2d_threads(2));
+    if (A.G) go(tile2d_kernel<K, true>);
+    else go(tile2d_kernel<K, false>);
+    return hipGetLastError();
+}
+
+// The same steps of every shot of a batch (blockIdx.y).
+template <int K, bool GRAD>
+__global__ __launch_bounds__(kTileThreads) void tile2d_batch_kernel(const BatchArgs A, const BatchOp op,
+                                                                    int tiles_x, int tiles_z)
+{
+    __shared__ __align__(16) Tile2dShared S;
+    __shared__ __align__(16) typename Tile2dShared::template Levels<K> L;
+    const int lid = xcd_remap(blockIdx.x, tiles_x * tiles_z);
+    const ShotTile<GRAD> T(A, A.shots[blockIdx.y], op, A.g.P);
+    tile2d<K, GRAD>(A.g, T, lid % tiles_x, lid / tiles_x, S, L);
+}
+
+template <int K>
+hipError_t launch_batch_k(const BatchArgs &A, const BatchOp &op, hipStream_t s)
+{
+    const int core = kTileRegion - 2 * tile2d_halo(K, op.ns);
+    const int tx = (A.g.nx + core - 1) / core, tz = (A.g.nz + core - 1) / core;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(tx * tz, A.nshots), dim3(kTileThreads), 0, s, A, op, tx, tz);
+    };
+    if (op.kind == kOpAdj) go(tile2d_batch_kernel<K, true>);
+    else go(tile2d_batch_kernel<K, false>);
     return hipGetLastError();
 }
 
@@ -50,6 +71,23 @@ hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, Laun
     case 6: return launch_k<6>(g, A, s, ev);
     case 7: return launch_k<7>(g, A, s, ev);
     case 8: return launch_k<8>(g, A, s, ev);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_batch_steps(const BatchArgs &A, const BatchOp &op, hipStream_t s)
+{
+    if ((op.kind != kOpStep && op.kind != kOpAdj) || op.ns < 1 || op.ns > tile2d_steps(A.g.K))
+        return hipErrorInvalidValue;
+    switch (A.g.K) {
+    case 1: return launch_batch_k<1>(A, op, s);
+    case 2: return launch_batch_k<2>(A, op, s);
+    case 3: return launch_batch_k<3>(A, op, s);
+    case 4: return launch_batch_k<4>(A, op, s);
+    case 5: return launch_batch_k<5>(A, op, s);
+    case 6: return launch_batch_k<6>(A, op, s);
+    case 7: return launch_batch_k<7>(A, op, s);
+    case 8: return launch_batch_k<8>(A, op, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -9,10 +9,17 @@
 // step makes K more rows and columns at the region's rim invalid, and the core that is left
 // is written.  The rim is computed by the neighbouring workgroups too (with 4 steps of order
 // 8 a core of 32 x 32: twice the arithmetic), which costs less than a launch per step.
-//   * A lane owns R rows of 4 points: the two levels are in LDS (a step overwrites the older
-//     one, each lane its own points: one barrier a step), w and the damping in registers; a step reads
-//     R + 2K rows of 16 bytes for the z neighbours of its points and 2 ceil(K/4) more per
-//     row for the x neighbours.
+//   * A lane owns 4 points of a row (16 waves, one region a CU at a time): the two levels are in
+//     LDS (a step overwrites the older one, each lane its own points: one barrier a step), w and
+//     the damping in registers; a step reads 1 + 2K rows of 16 bytes for the z neighbours of its
+//     points and 2 ceil(K/4) more for the x neighbours.  More rows a lane read less, but leave
+//     fewer waves, whose latency shows: three forward steps (196 regions) take 9.5 us with one
+//     row a lane, 11.8 with two, 15.2 with four, and an adjoint group of eight such shots 47 with
+//     one and 84 with two, which spill.
+//   * A region is bound by latency (its loads, then a chain of steps) and by the set-up of its
+//     lanes.  Regions inside the grid and its absorbing layer skip the damping and the masks
+//     (4 to 10 % of a step from 100 x 90 to 4000 x 3000 points); a persistent workgroup that loads
+//     its next region ahead took 7 % longer with one region a CU and 2 to 10 % less with many.
 //   * Injected samples are summed before the steps, for all of them; each step's go to an LDS
 //     plane of the region, and the owner of a point adds its own in the step's order (the
 //     binary64 gradient too), so results do not depend on how steps are grouped.
@@ -31,7 +38,7 @@ namespace wv {
 namespace {
 
 constexpr int kTileEX = kTileRegion, kTileEY = kTileRegion;
-constexpr int tile2d_threads(int R) { return 16 * (kTileRegion / R); }
+constexpr int kTileThreads = 16 * kTileRegion;
 constexpr int kTileCap = 256;                // injected points and receivers of a region kept in LDS
 
 struct Tile2dShared {
@@ -95,13 +102,11 @@ __device__ __forceinline__ void div4(const float *n, const float *b, const float
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // rows of any length: 4-byte aligned
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
-// 4 values of row gz from column gx on, from a clamped address and without a branch, so that
-// all loads of a lane are in flight together; the caller zeroes what lies outside the grid.
-// gx is a multiple of 4, so only a row's last lane straddles its end; it reads on into the
-// next row (after the last row, into the workspace behind the array, which is padded).
-__device__ __forceinline__ f4u tile_load4(const Grid &g, const float *f, int gx, int gz)
+// 4 values of row z from column x on (inside the grid).  x is a multiple of 4, so only a row's
+// last lane straddles its end; it reads on into the next row (after the last row, into the
+// workspace behind the array, which is padded).
+__device__ __forceinline__ f4u tile_load4(const Grid &g, const float *f, int x, int z)
 {
-    const int z = min(max(gz, 0), g.nz - 1), x = min(max(gx, 0), (g.nx - 1) & ~3);
     return *reinterpret_cast<const f4u *>(f + (long long)z * g.nx + x);
 }
 
@@ -109,14 +114,13 @@ __device__ __forceinline__ f4u tile_load4(const Grid &g, const float *f, int gx,
 // of a row reads its last four values and moves them down (grids under 4 wide: one by one).
 __device__ __forceinline__ void tile_load_grad(const Grid &g, const double *f, int gx, int gz, double *v)
 {
-    const int z = min(max(gz, 0), g.nz - 1);
-    const double *row = f + (long long)z * g.nx;
+    const double *row = f + (long long)gz * g.nx;
     if (g.nx < 4) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = row[min(max(gx, 0) + i, g.nx - 1)];
+        for (int i = 0; i < 4; ++i) v[i] = row[min(gx + i, g.nx - 1)];
         return;
     }
-    const int x = min(max(gx, 0), g.nx - 4), sh = gx - x;
+    const int x = min(gx, g.nx - 4), sh = gx - x;
     const d2u a = *reinterpret_cast<const d2u *>(row + x), b = *reinterpret_cast<const d2u *>(row + x + 2);
     const double t0 = sh & 1 ? a.y : a.x, t1 = sh & 1 ? b.x : a.y, t2 = sh & 1 ? b.y : b.x, t3 = b.y;
     v[0] = sh & 2 ? t2 : t0;
@@ -125,37 +129,41 @@ __device__ __forceinline__ void tile_load_grad(const Grid &g, const double *f, i
     v[3] = t3;
 }
 
-// Tile (tix, tiz) of the launch or phase A describes (a Tile2dArgs, or a view of a batched
-// shot with the same members); every lane of the tile2d_threads(R)
-// calls it; a lane owns R rows of 4 points.
-template <int K, bool GRAD, int R, typename Args>
+// Region (tix, tiz) of the steps A describes (a Tile2dArgs, or a view of a batched shot with
+// the same members); every lane of the kTileThreads calls it.
+template <int K, bool GRAD, typename Args>
 __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, int tiz, Tile2dShared &S,
                                        typename Tile2dShared::template Levels<K> &L)
 {
 #pragma clang fp contract(off)
     constexpr int HXK = (K + 3) & ~3;
     constexpr int NXV = 1 + 2 * (HXK / 4);
-    constexpr int NT = tile2d_threads(R);
+    constexpr int NT = kTileThreads;
     static_assert(NT >= kTileCap, "a lane per listed point");
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
     const int nx = g.nx, nz = g.nz, ns = A.ns;
     const int H = tile2d_halo(K, ns), C = kTileEX - 2 * H;     // rim and core (both axes)
     const int gx0 = tix * C - H, gz0 = tiz * C - H;
-    const int gx = gx0 + 4 * tx, gz = gz0 + R * ty;
-    const bool core = tx >= H / 4 && tx < (H + C) / 4 && R * ty >= H && R * ty < H + C;
+    const int gx = gx0 + 4 * tx, gz = gz0 + ty;
+    const bool core = tx >= H / 4 && tx < (H + C) / 4 && ty >= H && ty < H + C;
+    // Where a lane loads from: its points, moved into the grid and into what is needed of an
+    // array, the region less a rim (u: none, u^{n-1} and w: K, the gradient and its states: H).
+    // So no load has a branch and all of a lane's are in flight together, and lanes outside
+    // repeat addresses of lanes inside.  What lies outside the grid is zeroed below; an array's
+    // rim is not used.
+    auto xin = [&](int rim) {
+        return min(max(gx, max(gx0 + (rim & ~3), 0)), min(gx0 + kTileEX - 4 - (rim & ~3), (nx - 1) & ~3));
+    };
+    auto zin = [&](int rim) { return min(max(gz, max(gz0 + rim, 0)), min(gz0 + kTileEY - 1 - rim, nz - 1)); };
 
-    // the lane's points: u^n (to LDS), u^{n-1}, w, damping, gradient
-    f4u un[R], pl[R], wl4[R];
-    float wr[R][4], am[R][4], ap[R][4], rp[R][4];   // 1 - a, 1 + a, 1 / (1 + a)
-    double G[GRAD ? R : 1][4];
-    bool damp = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        un[r] = tile_load4(g, A.u, gx, gz + r);
-        pl[r] = tile_load4(g, A.up, gx, gz + r);
-        wl4[r] = tile_load4(g, A.w, gx, gz + r);
-        if constexpr (GRAD) tile_load_grad(g, A.G, gx, gz + r, G[r]);
-    }
+    f4u un = tile_load4(g, A.u, xin(0), zin(0));
+    f4u up = tile_load4(g, A.up, xin(K), zin(K));
+    f4u w4 = tile_load4(g, A.w, xin(K), zin(K));
+    double G[4];
+    if constexpr (GRAD) tile_load_grad(g, A.G, xin(H), zin(H), G);
+    // regions that reach out of the grid or into its absorbing layer
+    const bool edge = gx0 < max(g.ix0[0], 0) || gx0 + kTileEX - 1 > min(g.ix1[0], nx - 1) ||
+                      gz0 < max(g.ix0[2], 0) || gz0 + kTileEY - 1 > min(g.ix1[2], nz - 1);
     if (tid == 0) S.n = S.nrec = 0;
     __syncthreads();
     // injected points of the region and receivers of the core
@@ -175,25 +183,31 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
             if (e < kTileCap) S.rec[e] = i;
         }
     }
+    // u^n and u^{n-1} go to LDS; w and the damping (1 - a, 1 + a, 1 / (1 + a)) stay
+    float wr[4], am[4], ap[4], rp[4];
+    bool damp = false;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int i = 0; i < 4; ++i) {
+        wr[i] = w4[i];
+        am[i] = ap[i] = 1.0f;
+    }
+    if (edge) {
+        const bool zok = (unsigned)gz < (unsigned)nz;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int x = gx + i, z = gz + r;
-            const bool in = x >= 0 && x < nx && z >= 0 && z < nz;
-            un[r][i] = in ? un[r][i] : 0.0f;
-            pl[r][i] = in ? pl[r][i] : 0.0f;
-            wr[r][i] = in ? wl4[r][i] : 0.0f;
-            const float a = in ? damping(g, x, 0, z) : 0.0f;
+            const bool in = zok & ((unsigned)(gx + i) < (unsigned)nx);
+            const float a0 = damping(g, gx + i, 0, gz);
+            const float a = in ? a0 : 0.0f;
+            un[i] = in ? un[i] : 0.0f;
+            up[i] = in ? up[i] : 0.0f;
+            wr[i] = in ? wr[i] : 0.0f;
             damp |= a != 0.0f;
-            am[r][i] = 1.0f - a;
-            ap[r][i] = 1.0f + a;
+            am[i] = 1.0f - a;
+            ap[i] = 1.0f + a;
         }
-        *reinterpret_cast<float4 *>(&L.u[0][R * ty + r + K][4 * tx + HXK]) =
-            make_float4(un[r][0], un[r][1], un[r][2], un[r][3]);
-        *reinterpret_cast<float4 *>(&L.u[1][R * ty + r + K][4 * tx + HXK]) =
-            make_float4(pl[r][0], pl[r][1], pl[r][2], pl[r][3]);
     }
+    *reinterpret_cast<float4 *>(&L.u[0][ty + K][4 * tx + HXK]) = make_float4(un[0], un[1], un[2], un[3]);
+    *reinterpret_cast<float4 *>(&L.u[1][ty + K][4 * tx + HXK]) = make_float4(up[0], up[1], up[2], up[3]);
     __syncthreads();
     const int ninj = S.n, nrec = S.nrec;
     const bool damped = __any(damp);
@@ -219,9 +233,7 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
     }
     if (damped) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) rp[r][i] = 1.0f / ap[r][i];
+        for (int i = 0; i < 4; ++i) rp[i] = 1.0f / ap[i];
     }
     // the lane's receiver: its corners' places in the region and their weights
     int goff[4] = {0, 0, 0, 0};
@@ -284,94 +296,129 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
             }
         }
         const int m = K * (j + 1);     // the rim that is invalid after this step
-        if (R * ty + R > m && R * ty < kTileEY - m && 4 * tx + 4 > m && 4 * tx < kTileEX - m) {
-            f4u uk[R];   // read in the core only by what is stored
-            if constexpr (GRAD) {
-                const float *lev = A.level(j);
+        if (ty >= m && ty < kTileEY - m && 4 * tx + 4 > m && 4 * tx < kTileEX - m) {
+            f4u uk;      // used in the core only
+            if constexpr (GRAD) uk = tile_load4(g, A.level(j), xin(H), zin(H));
+            float q[4][1 + 2 * K];
 #pragma unroll
-                for (int r = 0; r < R; ++r) uk[r] = tile_load4(g, lev, gx, gz + r);
-            }
-            float q[4][R + 2 * K];
-#pragma unroll
-            for (int r = 0; r < R + 2 * K; ++r) {
-                const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][R * ty + r][4 * tx + HXK]);
+            for (int r = 0; r < 1 + 2 * K; ++r) {
+                const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][ty + r][4 * tx + HXK]);
                 q[0][r] = t.x; q[1][r] = t.y; q[2][r] = t.z; q[3][r] = t.w;
             }
+            float xr[4 * NXV];
+#pragma unroll
+            for (int v = 0; v < NXV; ++v) {
+                if (v == HXK / 4) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) xr[4 * v + i] = q[i][K];
+                } else {
+                    const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][ty + K][4 * tx + 4 * v]);
+                    xr[4 * v] = t.x; xr[4 * v + 1] = t.y; xr[4 * v + 2] = t.z; xr[4 * v + 3] = t.w;
+                }
+            }
+            // the level before is the lane's own in the other buffer, about to be overwritten
+            const float4 p4 = *reinterpret_cast<const float4 *>(&L.u[cur ^ 1][ty + K][4 * tx + HXK]);
+            const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
+            float on[4], num[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float lap = lap2d<K>(g, q[i], &xr[HXK + i - K]);
+                const float wl = wr[i] * lap;
+                const float d = q[i][K] - pv[i];
+                num[i] = damped ? fmaf(am[i], d, wl) : d + wl;   // (1 - 0) d + wl rounds as d + wl
+                if constexpr (GRAD) G[i] = fma(A.gscale * (double)uk[i], (double)wl, G[i]);
+            }
+            if (damped) div4(num, ap, rp, num);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) on[i] = q[i][K] + num[i];
+            if (ninj) {
+                const float4 s4 = *reinterpret_cast<const float4 *>(&S.inj[ty][4 * tx]);
+                const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (sv[i] != 0.0f) {
+                        const float wi = wr[i] * sv[i];
+                        on[i] += damped ? wi / ap[i] : wi;
+                        if constexpr (GRAD) G[i] = fma(A.gscale * (double)uk[i], (double)wi, G[i]);
+                    }
+            }
+            *reinterpret_cast<float4 *>(&L.u[cur ^ 1][ty + K][4 * tx + HXK]) = make_float4(on[0], on[1], on[2], on[3]);
             float *const out = A.dest(j);
+            if (core && out && gz < nz) {
+                float *p = out + (long long)gz * nx + gx;
+                if (gx + 3 < nx) {
+                    const f4u t = {on[0], on[1], on[2], on[3]};
+                    *reinterpret_cast<f4u *>(p) = t;
+                } else {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float xr[4 * NXV];
-#pragma unroll
-                for (int v = 0; v < NXV; ++v) {
-                    if (v == HXK / 4) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) xr[4 * v + i] = q[i][r + K];
-                    } else {
-                        const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][R * ty + r + K][4 * tx + 4 * v]);
-                        xr[4 * v] = t.x; xr[4 * v + 1] = t.y; xr[4 * v + 2] = t.z; xr[4 * v + 3] = t.w;
-                    }
-                }
-                // the level before is the lane's own in the other buffer, about to be overwritten
-                const float4 p4 = *reinterpret_cast<const float4 *>(&L.u[cur ^ 1][R * ty + r + K][4 * tx + HXK]);
-                const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
-                float on[4], num[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float c = q[i][r + K];
-                    const float lap = lap2d<K>(g, &q[i][r], &xr[HXK + i - K]);
-                    const float wl = wr[r][i] * lap;
-                    const float d = c - pv[i];
-                    num[i] = damped ? fmaf(am[r][i], d, wl) : d + wl;   // (1 - 0) d + wl rounds as d + wl
-                    if constexpr (GRAD) G[r][i] = fma(A.gscale * (double)uk[r][i], (double)wl, G[r][i]);
-                }
-                if (damped) div4(num, ap[r], rp[r], num);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) on[i] = q[i][r + K] + num[i];
-                if (ninj) {
-                    const float4 s4 = *reinterpret_cast<const float4 *>(&S.inj[R * ty + r][4 * tx]);
-                    const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (sv[i] != 0.0f) {
-                            const float wi = wr[r][i] * sv[i];
-                            on[i] += damped ? wi / ap[r][i] : wi;
-                            if constexpr (GRAD) G[r][i] = fma(A.gscale * (double)uk[r][i], (double)wi, G[r][i]);
-                        }
-                }
-                *reinterpret_cast<float4 *>(&L.u[cur ^ 1][R * ty + r + K][4 * tx + HXK]) =
-                    make_float4(on[0], on[1], on[2], on[3]);
-                if (core && out && gz + r < nz) {
-                    float *p = out + (long long)(gz + r) * nx + gx;
-                    if (gx + 3 < nx) {
-                        const f4u t = {on[0], on[1], on[2], on[3]};
-                        *reinterpret_cast<f4u *>(p) = t;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            if (gx + i < nx) p[i] = on[i];
-                    }
+                    for (int i = 0; i < 3; ++i)
+                        if (gx + i < nx) p[i] = on[i];
                 }
             }
         }
         __syncthreads();
     }
     if constexpr (GRAD) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!core || gz + r >= nz || gx >= nx) continue;
-            double *p = A.G + (long long)(gz + r) * nx + gx;
+        if (core && gz < nz && gx < nx) {
+            double *p = A.G + (long long)gz * nx + gx;
             if (gx + 3 < nx) {
-                const d2u a = {G[r][0], G[r][1]}, b = {G[r][2], G[r][3]};
+                const d2u a = {G[0], G[1]}, b = {G[2], G[3]};
                 *reinterpret_cast<d2u *>(p) = a;
                 *reinterpret_cast<d2u *>(p + 2) = b;
             } else {
 #pragma unroll
                 for (int i = 0; i < 3; ++i)
-                    if (gx + i < nx) p[i] = G[r][i];
+                    if (gx + i < nx) p[i] = G[i];
             }
         }
     }
 }
+
+// The array a batched shot holds for a buffer id.
+__device__ __forceinline__ float *batch_buf(const BatchArgs &A, const BatchShot &S, int id, long long P)
+{
+    if (id < 0) return nullptr;
+    if (id >= kBufSlot)
+        return reinterpret_cast<float *>(S.arena) + (long long)((id - kBufSlot) / 2 - 1) * A.slot_elems +
+               (long long)(id & 1) * P;
+    if (id >= kBufUB) return S.UB + (id - kBufUB) * A.fstride;
+    if (id >= kBufU) return S.U + (id - kBufU) * A.fstride;
+    if (id >= kBufL) return S.Lm + (id - kBufL) * A.fstride;
+    return id == kBufDB ? S.DB : S.Z;
+}
+
+// The steps of one batched shot, as tile2d takes them.
+template <bool GRAD>
+struct ShotTile {
+    const BatchArgs &A;
+    const BatchShot &S;
+    const BatchOp &op;
+    long long P;
+    const float *u, *up, *w;
+    int ns;
+    const Sparse &inj;
+    const float *vals;
+    long long vstride;
+    const Sparse &gat;
+    float *rows;
+    unsigned gmask;
+    double *G;
+    double gscale;
+    __device__ ShotTile(const BatchArgs &A_, const BatchShot &S_, const BatchOp &op_, long long P_)
+        : A(A_), S(S_), op(op_), P(P_), u(batch_buf(A_, S_, op_.a, P_)), up(batch_buf(A_, S_, op_.b, P_)), w(S_.W),
+          ns(op_.ns), inj(GRAD ? S_.rec : S_.src),
+          vals(GRAD ? S_.res + (long long)op_.n * A_.nrec : S_.wavelet + op_.n), vstride(GRAD ? -A_.nrec : 1),
+          gat(S_.rec), rows(S_.dsim + (long long)op_.n * A_.nrec), gmask(GRAD ? 0u : (unsigned)op_.e), G(S_.G),
+          gscale(A_.gscale)
+    {
+    }
+    __device__ const float *level(int j) const { return batch_buf(A, S, op.c[j], P); }
+    __device__ float *dest(int j) const
+    {
+        if (!GRAD) return batch_buf(A, S, op.c[j], P);
+        return j == ns - 1 ? batch_buf(A, S, op.d[0], P) : (j == ns - 2 ? batch_buf(A, S, op.d[1], P) : nullptr);
+    }
+};
 
 }  // namespace
 

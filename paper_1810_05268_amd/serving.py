@@ -4,7 +4,7 @@ The engine (``wv_engine_*`` in include/wv.h) admits queued requests first fit in
 arrival order whenever a worker stream and a contiguous slice of the device pool
 (workspace plus checkpoint arena) are free, and runs the admitted shots
 concurrently on their own HIP streams; with batching on, 2-D requests that share a
-grid and schedule run together in one persistent launch.  This module owns the pool
+grid and schedule run together, a launch advancing all of them.  This module owns the pool
 tensor, keeps each request's device buffers alive until it completes, and replays
 timed request streams.  No solver arithmetic happens here.
 """
