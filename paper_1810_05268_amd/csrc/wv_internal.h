@@ -140,6 +140,7 @@ struct Tile2dArgs {
 };
 hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev = {});
 int device_cus();
+bool tile2d_march(int K, int nx, int nz);
 // steps per group for a grid, nshots shots advancing together
 int tile2d_choose(int K, int nx, int nz, int nshots);
 

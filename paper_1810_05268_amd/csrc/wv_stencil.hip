@@ -523,7 +523,7 @@ __global__ __launch_bounds__(256) void stencil2d(Grid g, const float *__restrict
                                                  const float *__restrict__ xtra2, double *__restrict__ G,
                                                  double gscale, int tiles_x, int zchunks, int zlen)
 {
-    static_assert(MODE == kOT4 || (MODE == kLapW && !GRAD), "the OT4 passes; w lap carries no gradient term");
+    static_assert(MODE != kLapW || !GRAD, "w lap carries no gradient term");
     __shared__ float row[256 + 2 * K];
     const int lid = xcd_remap(blockIdx.x, tiles_x * zchunks);
     const int tix = lid % tiles_x, zc = lid / tiles_x;
@@ -821,9 +821,6 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
             return launch3d<K, GM, true, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
         return launch3d<K, GM, false, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, cr, gscale, s, ev, side);
     }
-    if constexpr (MODE == kOT2) {
-        return hipErrorInvalidValue;   // 2-D OT2 steps run in tiles
-    } else {
     // 2-D grids are small (a few MB): a step is bound by the latency of each workgroup's
     // plane-by-plane march, not by bandwidth, so chunks are short (down to K planes, whose
     // 2K-plane warm-up loads are issued together) and the workgroups many
@@ -834,7 +831,6 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
     launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(tiles_x * zchunks), s, ev, g, fin, prev, fout, w, uk, xtra,
                  xtra2, G, gscale, tiles_x, zchunks, zlen);
     return hipGetLastError();
-    }
 }
 
 template <int GM, int MODE>

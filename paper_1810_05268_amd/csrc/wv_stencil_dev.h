@@ -37,9 +37,33 @@ __device__ __forceinline__ float damping(const Grid &g, int x, int y, int z)
 // what a stencil launch does with the Laplacian (see stencil3d)
 constexpr int kOT2 = 0, kLapW = 1, kOT4 = 2;
 
-// One point (x, z) of a 2-D OT4 pass, p its index.  q: the 2K+1 values of the marched
+// Which products are fused with a sum is written out here (and contraction is off), so that
+// every instance rounds alike whatever surrounds it.
+// The Laplacian of a point from its column q[0..2K] (q[K] the point) and row x[0..2K].
+template <int K>
+__device__ __forceinline__ float lap2d(const Grid &g, const float *q, const float *x)
+{
+#pragma clang fp contract(off)
+    const float c = q[K];
+    const float tx = (x[K + 1] - c) + (x[K - 1] - c);
+    const float tz = (q[K + 1] - c) + (q[K - 1] - c);
+    if constexpr (K == 1) {
+        return fmaf(g.cz[1], tz, g.cx[1] * tx);
+    } else {
+        float fx = 0.0f, fz = 0.0f;
+#pragma unroll
+        for (int k = 2; k <= K; ++k) {
+            fx = fmaf(g.cx[k], x[K + k] + x[K - k], fx);
+            fz = fmaf(g.cz[k], q[K + k] + q[K - k], fz);
+        }
+        return fmaf(g.cx[1], tx, fmaf(-g.cf2[0], c, fx)) + fmaf(g.cz[1], tz, fmaf(-g.cf2[2], c, fz));
+    }
+}
+
+// One point (x, z) of a 2-D march, p its index.  q: the 2K+1 values of the marched
 // field's column around z (q[K] the point itself); rowc: the point in the field's row z,
 // staged with its K neighbours on either side (rowc[-K..K]).  MODE as for stencil3d:
+//   kOT2: a step as the tiles round it (GRAD adds gscale u^k (w L) to G in binary64);
 //   kLapW: fout = w L;  kOT4: the second pass, with the damping division skipped where a = 0.
 // The Laplacian takes the k = 1 term from differences and the far terms as a plain sum
 // folded once against the centre.
@@ -49,8 +73,16 @@ __device__ __forceinline__ void point2d(const Grid &g, const float *q, const flo
                                         const float *__restrict__ uk, const float *__restrict__ xtra,
                                         const float *__restrict__ xtra2, double *__restrict__ G, double gscale)
 {
-    static_assert(MODE == kLapW || MODE == kOT4, "2-D OT2 steps run in tiles");
     const float c = q[K];
+    if constexpr (MODE == kOT2) {
+#pragma clang fp contract(off)
+        const float wl = __builtin_nontemporal_load(&w[p]) * lap2d<K>(g, q, rowc - K);
+        const float a = damping(g, x, 0, z);
+        const float d = c - __builtin_nontemporal_load(&prev[p]);
+        __builtin_nontemporal_store(c + (a == 0.0f ? d + wl : fmaf(1.0f - a, d, wl) / (1.0f + a)), &fout[p]);
+        if constexpr (GRAD) G[p] = fma(gscale * (double)__builtin_nontemporal_load(&uk[p]), (double)wl, G[p]);
+        return;
+    }
     float sx = g.cx[1] * ((rowc[1] - c) + (rowc[-1] - c));
     float sz = g.cz[1] * ((q[K + 1] - c) + (q[K - 1] - c));
     if constexpr (K > 1) {

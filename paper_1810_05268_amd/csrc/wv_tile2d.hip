@@ -62,6 +62,14 @@ hipError_t launch_batch_k(const BatchArgs &A, const BatchOp &op, hipStream_t s)
 hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev)
 {
     if (g.ndim != 2 || A.ns < 1 || A.ns > tile2d_steps(g.K)) return hipErrorInvalidValue;
+    if (A.ns == 1 && A.out[0] && tile2d_march(g.K, g.nx, g.nz)) {
+        hipError_t rc = A.gmask ? launch_gather(A.gat, A.u, A.rows, s) : hipSuccess;
+        if (rc == hipSuccess)
+            rc = A.G ? launch_adj_step(g, A.u, A.up, A.out[0], A.w, A.uk[0], A.G, A.gscale, s, ev, nullptr, kGAdd, {})
+                     : launch_fwd_step(g, A.u, A.up, A.out[0], A.w, s, ev, {});
+        if (rc == hipSuccess) rc = launch_inject_res(g, A.inj, A.vals, A.w, A.out[0], A.uk[0], A.G, A.gscale, s);
+        return rc;
+    }
     switch (g.K) {
     case 1: return launch_k<1>(g, A, s, ev);
     case 2: return launch_k<2>(g, A, s, ev);
@@ -101,22 +109,32 @@ int device_cus()
     return cus;
 }
 
-// A group of ns steps costs a launch and its loads, about 4 us, and ns times the work of the
-// regions a CU gets, r = ceil(regions / CUs): (0.8 + K / 4) us for one, three quarters of that
-// for each of several (measured at orders 4, 8 and 16 on 141^2 and 552^2 points; in a batch
-// a device-wide barrier stands for the launch).  More steps mean a wider rim and so more
-// regions; the least time per step over the counts a region allows.
+// Whether a shot's steps are marched one by one (stencil2d) instead: for operators wider than
+// order 8 on grids of more than 4 regions a CU, where a region's rim is most of it and its
+// loads are no longer hidden.  At order 16 on 4000 x 3000 points a forward step takes 112 us in
+// tiles and 76 marched, on 2000 x 1500 an adjoint one 61 and 43 (a forward one 31 either way);
+// at order 8 tiles are faster on both (66 and 74 us, 19 and 28).
+bool tile2d_march(int K, int nx, int nz)
+{
+    const int core = kTileRegion - 2 * tile2d_halo(K, 1);
+    return K > 4 && (long long)((nx + core - 1) / core) * ((nz + core - 1) / core) > 4LL * device_cus();
+}
+
+// Steps per group.  A group of ns steps costs a launch with its first regions, 5 + (0.9 + K / 6) ns
+// us, and every further region that a CU gets 3.8 + (0.7 + K / 20) ns us (fitted to forward steps
+// of orders 4, 8, 12 and 16 on 100 x 90 to 4000 x 3000 points, each at every ns; it picks the fastest
+// ns or one within 5 % of it on all of them).  More steps mean a wider rim and so more regions.
 int tile2d_choose(int K, int nx, int nz, int nshots)
 {
+    if (nshots == 1 && tile2d_march(K, nx, nz)) return 1;
     const int cus = device_cus();
-    const double start = nshots > 1 ? 8.0 : 4.0;
     int best = 1;
     double best_t = 0.0;
     for (int ns = 1; ns <= tile2d_steps(K); ++ns) {
         const int core = kTileRegion - 2 * tile2d_halo(K, ns);
         const long long n = (long long)((nx + core - 1) / core) * ((nz + core - 1) / core) * nshots;
         const double r = (double)((n + cus - 1) / cus);
-        const double t = start / ns + (0.8 + 0.25 * K) * (r > 1.0 ? 0.75 * r : 1.0);
+        const double t = (5.0 + (0.9 + K / 6.0) * ns + (r - 1.0) * (3.8 + (0.7 + 0.05 * K) * ns)) / ns;
         if (ns == 1 || t < best_t) {
             best = ns;
             best_t = t;

@@ -53,29 +53,6 @@ struct Tile2dShared {
     int n, nrec;
 };
 
-// Which products are fused with a sum is written out here (and contraction is off), so that
-// every instance rounds alike whatever surrounds it.
-// The Laplacian of a point from its column q[0..2K] (q[K] the point) and row x[0..2K].
-template <int K>
-__device__ __forceinline__ float lap2d(const Grid &g, const float *q, const float *x)
-{
-#pragma clang fp contract(off)
-    const float c = q[K];
-    const float tx = (x[K + 1] - c) + (x[K - 1] - c);
-    const float tz = (q[K + 1] - c) + (q[K - 1] - c);
-    if constexpr (K == 1) {
-        return fmaf(g.cz[1], tz, g.cx[1] * tx);
-    } else {
-        float fx = 0.0f, fz = 0.0f;
-#pragma unroll
-        for (int k = 2; k <= K; ++k) {
-            fx = fmaf(g.cx[k], x[K + k] + x[K - k], fx);
-            fz = fmaf(g.cz[k], q[K + k] + q[K - k], fz);
-        }
-        return fmaf(g.cx[1], tx, fmaf(-g.cf2[0], c, fx)) + fmaf(g.cz[1], tz, fmaf(-g.cf2[2], c, fz));
-    }
-}
-
 // n[i] / b[i], r the binary32 reciprocals of b (1 <= b < 4).  The first correction leaves less
 // than an ulp and the second rounds correctly, as long as the remainders are exact: below
 // 2^-100 they are not, and a wave with such a value divides (a long run is sensitive to a

@@ -59,3 +59,8 @@ def test_more_points_than_a_region_lists(off):
 @pytest.mark.parametrize("order", [4, 8, 16])
 def test_more_regions_than_compute_units(order):
     _check(_shot((1020, 790), 20, order, 13), (4,))
+
+
+@pytest.mark.parametrize("order", [10, 16])
+def test_wide_operators_on_large_grids_march(order):
+    _check(_shot((1661, 1570), 20, order, 9), (3,))
