@@ -11,10 +11,9 @@ template <int K, bool GRAD>
 __global__ __launch_bounds__(kTileThreads) void tile2d_kernel(const Grid g, const Tile2dArgs A, int tiles_x,
                                                               int tiles_z)
 {
-    __shared__ __align__(16) Tile2dShared S;
-    __shared__ __align__(16) typename Tile2dShared::template Levels<K> L;
+    __shared__ __align__(16) Tile2dShared<K> S;
     const int lid = xcd_remap(blockIdx.x, tiles_x * tiles_z);
-    tile2d<K, GRAD>(g, A, lid % tiles_x, lid / tiles_x, S, L);
+    tile2d<K, GRAD>(g, A, lid % tiles_x, lid / tiles_x, S);
 }
 
 template <int K>
@@ -37,11 +36,10 @@ template <int K, bool GRAD>
 __global__ __launch_bounds__(kTileThreads) void tile2d_batch_kernel(const BatchArgs A, const BatchOp op,
                                                                     int tiles_x, int tiles_z)
 {
-    __shared__ __align__(16) Tile2dShared S;
-    __shared__ __align__(16) typename Tile2dShared::template Levels<K> L;
+    __shared__ __align__(16) Tile2dShared<K> S;
     const int lid = xcd_remap(blockIdx.x, tiles_x * tiles_z);
     const ShotTile<GRAD> T(A, A.shots[blockIdx.y], op, A.g.P);
-    tile2d<K, GRAD>(A.g, T, lid % tiles_x, lid / tiles_x, S, L);
+    tile2d<K, GRAD>(A.g, T, lid % tiles_x, lid / tiles_x, S);
 }
 
 template <int K>

@@ -4,7 +4,7 @@
 // A 2-D field is a few MB, so a step launched by itself is bound by latency: the launch, a
 // workgroup's first loads and its march down the rows (7.1 us a forward step on 552^2 points
 // at order 8, 0.7 us of which its bytes need; 8.7 us an adjoint step).  Three steps in tiles
-// take 9.1 and 9.8 us, two thirds of it arithmetic.  Here a workgroup takes a 64 x 64 region of
+// take 8.5 and 9.9 us, over half of it arithmetic.  Here a workgroup takes a 64 x 64 region of
 // the grid into LDS and its registers and advances it by up to kTileSteps(K) steps; each
 // step makes K more rows and columns at the region's rim invalid, and the core that is left
 // is written.  The rim is computed by the neighbouring workgroups too (with 4 steps of order
@@ -20,8 +20,9 @@
 //     lanes.  Regions inside the grid and its absorbing layer skip the damping and the masks
 //     (4 to 10 % of a step from 100 x 90 to 4000 x 3000 points); a persistent workgroup that loads
 //     its next region ahead took 7 % longer with one region a CU and 2 to 10 % less with many.
-//   * Injected samples are summed before the steps, for all of them; each step's go to an LDS
-//     plane of the region, and the owner of a point adds its own in the step's order (the
+//   * Injected samples are summed before the steps, for all of them, by the lanes that find the
+//     points, while the fields load; each step's go to one of two LDS planes of the region a step
+//     ahead, and the owner of a point adds its own in the step's order (the
 //     binary64 gradient too), so results do not depend on how steps are grouped.
 //   * Divisions by 1 + a (in the absorbing layer) multiply by the reciprocal, formed once a
 //     region, and correct twice, which rounds as the division does (5 operations for 13);
@@ -41,17 +42,23 @@ constexpr int kTileEX = kTileRegion, kTileEY = kTileRegion;
 constexpr int kTileThreads = 16 * kTileRegion;
 constexpr int kTileCap = 256;                // injected points and receivers of a region kept in LDS
 
+// A workgroup's LDS.  All of it stays under half a CU's: not for a second workgroup, but because
+// the compiler takes less to mean that registers are free, and spills at K >= 6.
+template <int K>
 struct Tile2dShared {
     // two levels of the region with a guard rim for the lanes at its edge, whose results
-    // are not used (sized for K = 8)
-    template <int K>
-    struct Levels {
-        float u[2][kTileEY + 2 * K][kTileEX + 2 * ((K + 3) & ~3)];
-    };
-    float inj[kTileEY][kTileEX];             // a step's summed samples, 0 where there is no point
-    int ent[kTileCap], rec[kTileCap];
+    // are not used
+    float u[2][kTileEY + 2 * K][kTileEX + 2 * ((K + 3) & ~3)];
+    // the summed samples of a step and of the next one, 0 where there is no point, of the rows
+    // that are stepped at all
+    float inj[2][kTileEY - 2 * K][kTileEX];
+    float val[tile2d_steps(K)][kTileCap];    // those of the listed points for every step,
+    int loc[kTileCap];                       // and the points' places in a plane of inj
+    int rec[kTileCap];
     int n, nrec;
 };
+static_assert(sizeof(Tile2dShared<1>) <= 81920 && sizeof(Tile2dShared<2>) <= 81920 &&
+              sizeof(Tile2dShared<5>) <= 81920 && sizeof(Tile2dShared<8>) <= 81920);
 
 // n[i] / b[i], r the binary32 reciprocals of b (1 <= b < 4).  The first correction leaves less
 // than an ulp and the second rounds correctly, as long as the remainders are exact: below
@@ -109,8 +116,7 @@ __device__ __forceinline__ void tile_load_grad(const Grid &g, const double *f, i
 // Region (tix, tiz) of the steps A describes (a Tile2dArgs, or a view of a batched shot with
 // the same members); every lane of the kTileThreads calls it.
 template <int K, bool GRAD, typename Args>
-__device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, int tiz, Tile2dShared &S,
-                                       typename Tile2dShared::template Levels<K> &L)
+__device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, int tiz, Tile2dShared<K> &S)
 {
 #pragma clang fp contract(off)
     constexpr int HXK = (K + 3) & ~3;
@@ -145,11 +151,23 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
     __syncthreads();
     // injected points of the region and receivers of the core
     for (int i = tid; i < A.inj.npts; i += NT) {
-        const int p = A.inj.s_pts[i];
+        const int p = A.inj.s_pts[i], q0 = A.inj.s_start[i], q1 = A.inj.s_start[i + 1];
         const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
-        if (lx < 0 || lx >= kTileEX || lz < 0 || lz >= kTileEY) continue;
+        if (lx < 0 || lx >= kTileEX || lz < K || lz >= kTileEY - K) continue;
         const int e = atomicAdd(&S.n, 1);
-        if (e < kTileCap) S.ent[e] = i;
+        if (e >= kTileCap) continue;
+        float v[tile2d_steps(K)];
+#pragma unroll
+        for (int j = 0; j < tile2d_steps(K); ++j) v[j] = 0.0f;
+        for (int q = q0; q < q1; ++q) {   // as scatter_sum, all steps at once
+            const float wt = A.inj.s_wt[q];
+            const float *f = A.vals + A.inj.s_col[q];
+#pragma unroll
+            for (int j = 0; j < tile2d_steps(K); ++j) v[j] = fmaf(wt, f[min(j, ns - 1) * A.vstride], v[j]);
+        }
+        S.loc[e] = (lz - K) * kTileEX + lx;
+#pragma unroll
+        for (int j = 0; j < tile2d_steps(K); ++j) S.val[j][e] = v[j];
     }
     if (!GRAD && A.gmask) {
         for (int i = tid; i < A.gat.n; i += NT) {
@@ -183,29 +201,34 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
             ap[i] = 1.0f + a;
         }
     }
-    *reinterpret_cast<float4 *>(&L.u[0][ty + K][4 * tx + HXK]) = make_float4(un[0], un[1], un[2], un[3]);
-    *reinterpret_cast<float4 *>(&L.u[1][ty + K][4 * tx + HXK]) = make_float4(up[0], up[1], up[2], up[3]);
+    *reinterpret_cast<float4 *>(&S.u[0][ty + K][4 * tx + HXK]) = make_float4(un[0], un[1], un[2], un[3]);
+    *reinterpret_cast<float4 *>(&S.u[1][ty + K][4 * tx + HXK]) = make_float4(up[0], up[1], up[2], up[3]);
     __syncthreads();
     const int ninj = S.n, nrec = S.nrec;
     const bool damped = __any(damp);
-    // thread e < ninj sums the samples of entry e for every step
+    // step j's samples go to its plane (the same places every step)
     const bool listed = ninj <= kTileCap;
-    int iloc = -1;
-    float ival[tile2d_steps(K)];
-    if (ninj) {
-        for (int i = tid; i < kTileEX * kTileEY; i += NT) (&S.inj[0][0])[i] = 0.0f;
-        if (listed && tid < ninj) {
-            const int i = S.ent[tid], p = A.inj.s_pts[i], z = p / nx;
-            iloc = (z - gz0) * kTileEX + p - z * nx - gx0;
-#pragma unroll
-            for (int j = 0; j < tile2d_steps(K); ++j) ival[j] = 0.0f;
-            for (int q = A.inj.s_start[i]; q < A.inj.s_start[i + 1]; ++q) {   // as scatter_sum, all steps at once
-                const float wt = A.inj.s_wt[q];
-                const float *v = A.vals + A.inj.s_col[q];
-#pragma unroll
-                for (int j = 0; j < tile2d_steps(K); ++j) ival[j] = fmaf(wt, v[min(j, ns - 1) * A.vstride], ival[j]);
+    auto place = [&](int j) {
+        float *plane = &S.inj[j & 1][0][0];
+        if (listed) {
+            if (tid < ninj) plane[S.loc[tid]] = S.val[j][tid];
+        } else {
+            for (int i = tid; i < A.inj.npts; i += NT) {
+                const int p = A.inj.s_pts[i];
+                const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
+                if (lx >= 0 && lx < kTileEX && lz >= K && lz < kTileEY - K)
+                    plane[(lz - K) * kTileEX + lx] = scatter_sum(A.inj, i, A.vals + j * A.vstride);
             }
         }
+    };
+    if (ninj) {
+        if (ty >= K && ty < kTileEY - K) {
+            const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            *reinterpret_cast<float4 *>(&S.inj[0][ty - K][4 * tx]) = zero;
+            *reinterpret_cast<float4 *>(&S.inj[1][ty - K][4 * tx]) = zero;
+        }
+        __syncthreads();
+        place(0);
         __syncthreads();
     }
     if (damped) {
@@ -230,24 +253,9 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
 #pragma unroll 1
     for (int j = 0; j < ns; ++j) {
         const int cur = j & 1;
-        if (ninj) {       // this step's samples
-            if (listed) {
-                float v = ival[0];
-#pragma unroll
-                for (int q = 1; q < tile2d_steps(K); ++q) v = q == j ? ival[q] : v;
-                if (iloc >= 0) (&S.inj[0][0])[iloc] = v;
-            } else {
-                for (int i = tid; i < A.inj.npts; i += NT) {
-                    const int p = A.inj.s_pts[i];
-                    const int z = p / nx, lx = p - z * nx - gx0, lz = z - gz0;
-                    if (lx >= 0 && lx < kTileEX && lz >= 0 && lz < kTileEY)
-                        S.inj[lz][lx] = scatter_sum(A.inj, i, A.vals + j * A.vstride);
-                }
-            }
-            __syncthreads();
-        }
+        if (ninj && j + 1 < ns) place(j + 1);
         if (!GRAD && (A.gmask >> j & 1)) {
-            const float *lev = &L.u[cur][0][0];
+            const float *lev = &S.u[cur][0][0];
             float *row = A.rows + (long long)j * A.gat.n;
             if (nrec <= kTileCap) {
                 if (rr >= 0) {
@@ -266,7 +274,7 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
                     for (int c = 0; c < A.gat.nc; ++c) {
                         const int p = A.gat.g_idx[i * A.gat.nc + c];
                         const int z = p / nx;
-                        s = fmaf(A.gat.g_wt[i * A.gat.nc + c], L.u[cur][z - gz0 + K][p - z * nx - gx0 + HXK], s);
+                        s = fmaf(A.gat.g_wt[i * A.gat.nc + c], S.u[cur][z - gz0 + K][p - z * nx - gx0 + HXK], s);
                     }
                     row[i] = s;
                 }
@@ -279,7 +287,7 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
             float q[4][1 + 2 * K];
 #pragma unroll
             for (int r = 0; r < 1 + 2 * K; ++r) {
-                const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][ty + r][4 * tx + HXK]);
+                const float4 t = *reinterpret_cast<const float4 *>(&S.u[cur][ty + r][4 * tx + HXK]);
                 q[0][r] = t.x; q[1][r] = t.y; q[2][r] = t.z; q[3][r] = t.w;
             }
             float xr[4 * NXV];
@@ -289,12 +297,12 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
 #pragma unroll
                     for (int i = 0; i < 4; ++i) xr[4 * v + i] = q[i][K];
                 } else {
-                    const float4 t = *reinterpret_cast<const float4 *>(&L.u[cur][ty + K][4 * tx + 4 * v]);
+                    const float4 t = *reinterpret_cast<const float4 *>(&S.u[cur][ty + K][4 * tx + 4 * v]);
                     xr[4 * v] = t.x; xr[4 * v + 1] = t.y; xr[4 * v + 2] = t.z; xr[4 * v + 3] = t.w;
                 }
             }
             // the level before is the lane's own in the other buffer, about to be overwritten
-            const float4 p4 = *reinterpret_cast<const float4 *>(&L.u[cur ^ 1][ty + K][4 * tx + HXK]);
+            const float4 p4 = *reinterpret_cast<const float4 *>(&S.u[cur ^ 1][ty + K][4 * tx + HXK]);
             const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
             float on[4], num[4];
 #pragma unroll
@@ -309,17 +317,25 @@ __device__ __forceinline__ void tile2d(const Grid &g, const Args &A, int tix, in
 #pragma unroll
             for (int i = 0; i < 4; ++i) on[i] = q[i][K] + num[i];
             if (ninj) {
-                const float4 s4 = *reinterpret_cast<const float4 *>(&S.inj[ty][4 * tx]);
+                const float4 s4 = *reinterpret_cast<const float4 *>(&S.inj[cur][ty - K][4 * tx]);
                 const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
+                if (sv[0] != 0.0f || sv[1] != 0.0f || sv[2] != 0.0f || sv[3] != 0.0f) {
+                    float wi[4], di[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (sv[i] != 0.0f) {
-                        const float wi = wr[i] * sv[i];
-                        on[i] += damped ? wi / ap[i] : wi;
-                        if constexpr (GRAD) G[i] = fma(A.gscale * (double)uk[i], (double)wi, G[i]);
+                    for (int i = 0; i < 4; ++i) wi[i] = di[i] = wr[i] * sv[i];
+                    if (damped) div4(wi, ap, rp, di);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bool here = sv[i] != 0.0f;
+                        on[i] = here ? on[i] + di[i] : on[i];
+                        if constexpr (GRAD) {
+                            const double t = fma(A.gscale * (double)uk[i], (double)wi[i], G[i]);
+                            G[i] = here ? t : G[i];
+                        }
                     }
+                }
             }
-            *reinterpret_cast<float4 *>(&L.u[cur ^ 1][ty + K][4 * tx + HXK]) = make_float4(on[0], on[1], on[2], on[3]);
+            *reinterpret_cast<float4 *>(&S.u[cur ^ 1][ty + K][4 * tx + HXK]) = make_float4(on[0], on[1], on[2], on[3]);
             float *const out = A.dest(j);
             if (core && out && gz < nz) {
                 float *p = out + (long long)gz * nx + gx;
