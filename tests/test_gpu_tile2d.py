@@ -64,3 +64,18 @@ def test_more_regions_than_compute_units(order):
 @pytest.mark.parametrize("order", [10, 16])
 def test_wide_operators_on_large_grids_march(order):
     _check(_shot((1661, 1570), 20, order, 9), (3,))
+
+
+@pytest.mark.parametrize("order", [12, 16])
+def test_marched_steps_round_as_tiles(order):
+    """A large grid's shot marches alone and runs in tiles in a batch: the same bits."""
+    import torch
+    from tests.test_gpu_batch import _batch, _device, _shots
+    devs, dobs, _ = _device(_shots((1661, 1570), 90, order, 2, seed=order))
+    dobs = [torch.zeros_like(d) for d in dobs]   # the models differ too deep to show in 90 steps
+    budget = 10 * devs[0].slot_bytes
+    phis, grads, dsims, _ = _batch(devs, dobs, budget, 0.0, 0.0)
+    for i, d in enumerate(devs):
+        phi, g, _, ds = d.misfit_gradient(dobs[i], budget, 0.0, want_dsim=True)
+        assert phi > 0 and phis[i] == phi
+        assert torch.equal(dsims[i], ds) and torch.equal(grads[i], g)
