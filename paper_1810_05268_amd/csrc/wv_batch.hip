@@ -379,7 +379,7 @@ __device__ __forceinline__ void phase_copy(const BatchCtx &C, int src, int dst)
     });
 }
 
-// Steps A.op0 .. A.op0 + A.nops - 1 of the program (no forward or adjoint steps).  Once a
+// Ops A.op0 .. A.op0 + A.nops - 1 of those the persistent kernel runs (no forward or adjoint steps).  Once a
 // barrier of an earlier launch has given up, the abort word keeps the later ones from running.
 __global__ __launch_bounds__(256) void batch2d_kernel(BatchArgs A)
 {

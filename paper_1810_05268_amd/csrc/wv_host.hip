@@ -2014,7 +2014,7 @@ int batch_setup(int nshots, const wv_model *ms, const wv_geom *gs, size_t budget
         L[i] = plan_layout(&m, &gs[i], su[i], WV_OP_GRADIENT, budget);
     }
     const CodecDims cd = codec_dims(2, std::array<int, 3>{su[0].g.nx, su[0].g.nz, 1}.data(), su[0].g.px);
-    B.max_ops = 10 * m0.nt + 64;
+    B.max_ops = Prog2d::most_other_ops(m0.nt);
     B.hdr = 0;
     B.desc = kBatchHdr;
     B.ops = align_up(B.desc + (size_t)nshots * sizeof(BatchShot), 256);
@@ -2161,9 +2161,14 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         make_schedule(N, M, !(tol > 0), acts);
         Prog2d plan(g.K, steps);
         plan.schedule(acts, second_level_needed(acts, M), M, tol > 0, true, ActionCodes{});
-        // cannot happen: the program is bounded by the action count, and the executor's
+        // what the persistent kernel reads of the program; the steps, of which a run with few
+        // slots has many more, go to their launches by value
+        std::vector<BatchOp> other;
+        for (const BatchOp &op : plan.ops)
+            if (!Prog2d::steps(op)) other.push_back(op);
+        // cannot happen: these are bounded by the action count, and the executor's
         // bookkeeping always has the levels a step reads
-        if (!plan.valid || (int)plan.ops.size() > B.max_ops) return WV_EINVAL;
+        if (!plan.valid || (int)other.size() > B.max_ops) return WV_EINVAL;
         for (int i = 0; i < nshots; ++i) {
             Dev &d = dv[i];
             HIPCHK(launch_fill_f32(d.Lm[0], su[i].Pf, 0.0f, s));
@@ -2174,24 +2179,22 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
             HIPCHK(launch_fill_f32(shots[i].dsim, geoms[i].nrec, 0.0f, s));
         }
         HIPCHK(launch_fill_u64(reinterpret_cast<uint64_t *>(base + B.hdr), kBatchHdr / 8, 0, s));
-        HIPCHK(hipMemcpyAsync(base + B.ops, plan.ops.data(), plan.ops.size() * sizeof(BatchOp),
-                              hipMemcpyHostToDevice, s));
+        HIPCHK(hipMemcpyAsync(base + B.ops, other.data(), other.size() * sizeof(BatchOp), hipMemcpyHostToDevice, s));
         hipEvent_t e0, e1;
         HIPCHK(hipEventCreate(&e0));
         HIPCHK(hipEventCreate(&e1));
         HIPCHK(hipEventRecord(e0, s));
+        A.op0 = 0;
         for (size_t i = 0; i < plan.ops.size();) {
-            auto steps_op = [&](size_t q) { return plan.ops[q].kind == kOpStep || plan.ops[q].kind == kOpAdj; };
-            if (steps_op(i)) {
+            if (Prog2d::steps(plan.ops[i])) {
                 HIPCHK(launch_batch_steps(A, plan.ops[i++], s));
                 continue;
             }
-            size_t j = i;
-            while (j < plan.ops.size() && !steps_op(j)) ++j;
-            A.op0 = (int)i;
-            A.nops = (int)(j - i);
+            const size_t i0 = i;
+            while (i < plan.ops.size() && !Prog2d::steps(plan.ops[i])) ++i;
+            A.nops = (int)(i - i0);
             HIPCHK(launch_batch2d(A, s));
-            i = j;
+            A.op0 += A.nops;
         }
         HIPCHK(hipEventRecord(e1, s));
         HIPCHK(hipStreamSynchronize(s));

@@ -266,8 +266,8 @@ struct BatchArgs {
     CodecDims cd;
     const BatchShot *shots;
     int nshots;
-    const BatchOp *ops;
-    int op0, nops;            // the ops a launch of the persistent kernel executes
+    const BatchOp *ops;       // the program's ops but for its steps
+    int op0, nops;            // the ops (of those that are no steps) a launch of the persistent kernel executes
     double gscale;
     double tol;
     int minexp;

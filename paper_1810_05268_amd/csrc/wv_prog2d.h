@@ -25,9 +25,17 @@ public:
     int u = kBufZ, up = kBufZ;            // buffers of u^n and u^{n-1} (kBufNone: not decoded)
     int lam = kBufL, lamp = kBufL + 1;    // buffers of lam^k and lam^{k+1}
 
-    // steps: most steps of a group (1 .. tile2d_steps(K))
-    Prog2d(int K, int steps)
-        : T(steps), NU(tile2d_ring(K)), ND(tile2d_decoded(K)), NE(tile2d_jobs(K))
+    // Whether an op is a group of steps.  Of the others a reversal of nt steps has at most so
+    // many, whatever its slots: every state is reached for storing or reversing at most once
+    // from a restore, so there are at most nt stores (a copy or a field of an encode for each of
+    // their two levels), 2 nt + 1 restores (a decode each, and one for the second level), nt data
+    // rows, and the residual and the misfit.  Groups of steps grow as nt^2 with one slot.
+    static bool steps(const BatchOp &op) { return op.kind == kOpStep || op.kind == kOpAdj; }
+    static int most_other_ops(int nt) { return 10 * nt + 64; }
+
+    // group: most steps of a group (1 .. tile2d_steps(K))
+    Prog2d(int K, int group)
+        : T(group), NU(tile2d_ring(K)), ND(tile2d_decoded(K)), NE(tile2d_jobs(K))
     {
     }
 
