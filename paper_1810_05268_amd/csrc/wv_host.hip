@@ -1442,7 +1442,8 @@ struct ActionCodes {
     int advance = ADVANCE, store = STORE, restore = RESTORE, reverse = REVERSE;
 };
 
-// A 2-D OT2 reversal: the schedule's program, launch by launch.
+// A 2-D OT2 reversal: the schedule's program, launch by launch as it is built (with few slots
+// it has nt^2 / 2 steps, and the device starts with the first).
 int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const std::vector<char> &need2, int M,
                 ActionTimer &timer)
 {
@@ -1451,18 +1452,8 @@ int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const 
     const long long nrec = R.geo->nrec;
     const bool comp = R.tol > 0;
     Prog2d p(R.su.g.K, tile2d_choose(R.su.g.K, R.su.g.nx, R.su.g.nz, 1));
-    p.schedule(acts, need2, M, comp, run.data != nullptr, ActionCodes{});
-    if (!p.valid) return WV_EINVAL;
-    R.advances = p.advances;
-    R.stores = p.stores;
-    R.fields = p.fields;
-    R.restores = p.restores;
-    R.reverses = p.reverses;
-    R.decodes = p.decodes;
-    R.max_depth = p.max_depth;
-    int rc = WV_OK;
-    for (BatchOp &op : p.ops) {
-        int kind = ADVANCE;
+    auto launch = [&](BatchOp &op) -> int {
+        int rc = WV_OK, kind = ADVANCE;
         switch (op.kind) {
         case kOpResid:
             if (R.optimistic) {
@@ -1470,13 +1461,13 @@ int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const 
                 if ((rc = read_err(d, run.s, &e))) return rc;
                 if (e & 4u) return WV_EARENA;   // not every state fits: the caller plans from the sizes
             }
-            if (!R.misfit_mode) continue;
+            if (!R.misfit_mode) return WV_OK;
             HIPCHK(launch_check_finite(run.ptr(op.a), R.su.Pf, d.err, run.s));
             HIPCHK(launch_residual_misfit(run.data, R.dobs, d.res, (long long)(N + 1) * nrec, nrec, d.partials, kParts,
                                           d.misfit, run.s));
             kind = REVERSE;
             break;
-        case kOpMisfit: continue;
+        case kOpMisfit: return WV_OK;
         case kOpEnc:
             if (R.optimistic && R.arena_full) {
                 // this attempt will stop: only the profile's samples are still measured
@@ -1499,8 +1490,20 @@ int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const 
             if ((rc = run.run(op))) return rc;
             kind = op.kind == kOpAdj ? REVERSE : (op.kind == kOpDec ? RESTORE : (op.kind == kOpCopy ? STORE : ADVANCE));
         }
-        if ((rc = timer.mark(kind))) return rc;
-    }
+        return timer.mark(kind);
+    };
+    int rc = WV_OK;
+    p.stream(acts, need2, M, comp, run.data != nullptr, ActionCodes{},
+             [&](BatchOp &op) { return (rc = launch(op)) == WV_OK; });
+    if (rc) return rc;
+    if (!p.valid) return WV_EINVAL;
+    R.advances = p.advances;
+    R.stores = p.stores;
+    R.fields = p.fields;
+    R.restores = p.restores;
+    R.reverses = p.reverses;
+    R.decodes = p.decodes;
+    R.max_depth = p.max_depth;
     return WV_OK;
 }
 
@@ -2159,13 +2162,15 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         if (M < 1) return WV_EBUDGET;
         std::vector<int32_t> acts;
         make_schedule(N, M, !(tol > 0), acts);
-        Prog2d plan(g.K, steps);
-        plan.schedule(acts, second_level_needed(acts, M), M, tol > 0, true, ActionCodes{});
-        // what the persistent kernel reads of the program; the steps, of which a run with few
-        // slots has many more, go to their launches by value
+        const std::vector<char> need2 = second_level_needed(acts, M);
+        // What the persistent kernel reads of the program; the steps, of which a run with few
+        // slots has many more, go to their launches by value, as the program is built again.
         std::vector<BatchOp> other;
-        for (const BatchOp &op : plan.ops)
+        Prog2d plan(g.K, steps);
+        plan.stream(acts, need2, M, tol > 0, true, ActionCodes{}, [&](const BatchOp &op) {
             if (!Prog2d::steps(op)) other.push_back(op);
+            return true;
+        });
         // cannot happen: these are bounded by the action count, and the executor's
         // bookkeeping always has the levels a step reads
         if (!plan.valid || (int)other.size() > B.max_ops) return WV_EINVAL;
@@ -2184,18 +2189,27 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         HIPCHK(hipEventCreate(&e0));
         HIPCHK(hipEventCreate(&e1));
         HIPCHK(hipEventRecord(e0, s));
-        A.op0 = 0;
-        for (size_t i = 0; i < plan.ops.size();) {
-            if (Prog2d::steps(plan.ops[i])) {
-                HIPCHK(launch_batch_steps(A, plan.ops[i++], s));
-                continue;
-            }
-            const size_t i0 = i;
-            while (i < plan.ops.size() && !Prog2d::steps(plan.ops[i])) ++i;
-            A.nops = (int)(i - i0);
-            HIPCHK(launch_batch2d(A, s));
+        A.op0 = A.nops = 0;
+        auto launch_other = [&]() -> int {
+            if (A.nops) HIPCHK(launch_batch2d(A, s));
             A.op0 += A.nops;
-        }
+            A.nops = 0;
+            return WV_OK;
+        };
+        auto launch = [&](const BatchOp &op) -> int {
+            if (!Prog2d::steps(op)) {
+                ++A.nops;
+                return WV_OK;
+            }
+            const int r = launch_other();
+            if (r) return r;
+            HIPCHK(launch_batch_steps(A, op, s));
+            return WV_OK;
+        };
+        Prog2d again(g.K, steps);
+        again.stream(acts, need2, M, tol > 0, true, ActionCodes{},
+                     [&](const BatchOp &op) { return (rc = launch(op)) == WV_OK; });
+        if (rc || (rc = launch_other())) return rc;
         HIPCHK(hipEventRecord(e1, s));
         HIPCHK(hipStreamSynchronize(s));
         float ms = 0.0f;

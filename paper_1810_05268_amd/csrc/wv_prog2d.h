@@ -106,11 +106,32 @@ public:
 
     // the reversal that acts prescribe (action triples; codes as the executor's), with
     // M slots, plain or compressed; need2 flags the stores that keep both levels; rows: the
-    // first sweep gathers data rows (a gradient of a given residual wants none)
+    // first sweep gathers data rows (a gradient of a given residual wants none).  The whole
+    // program: nt^2 / (2 T) groups of steps with one slot
     template <typename Codes>
     void schedule(const std::vector<int32_t> &acts, const std::vector<char> &need2, int M, bool comp, bool rows,
                   Codes code)
     {
+        std::vector<BatchOp> all;
+        stream(acts, need2, M, comp, rows, code, [&](const BatchOp &op) {
+            all.push_back(op);
+            return true;
+        });
+        ops.swap(all);
+    }
+
+    // The same op by op, none of them kept: sink(op) takes each as the schedule reaches it, and
+    // ends the program when it returns false.
+    template <typename Codes, typename Sink>
+    void stream(const std::vector<int32_t> &acts, const std::vector<char> &need2, int M, bool comp, bool rows,
+                Codes code, Sink sink)
+    {
+        auto drain = [&]() {
+            for (BatchOp &op : ops)
+                if (!sink(op)) return false;
+            ops.clear();
+            return true;
+        };
         std::vector<char> slot2((size_t)M + 2, 0);
         int hot_slot = -1, hot_k = -1, hot_buf = kBufNone, pend_slot = -1, cur_n = 0;
         bool up_pending = false, hot_db = false, started = false;
@@ -146,6 +167,7 @@ public:
                 for (int n = a; n < b; ++n) {
                     step(n, rows && n + 1 > gathered, n == b - 1 ? last : (n == b - 2 ? prev : kBufNone));
                     if (n + 1 > gathered) gathered = n + 1;
+                    if (!drain()) return;
                 }
                 cur_n = b;
                 advances += b - a;
@@ -213,9 +235,12 @@ public:
                 reverses++;
                 if ((int)adj.size() >= collect) flush_adj();
             }
+            if (!drain()) return;
         }
+        if (!valid) return;
         flush_adj();
         flush();
+        (void)drain();
     }
 
 private:
