@@ -313,6 +313,7 @@ struct Layout {
     size_t total;
     size_t arena_bytes;
     size_t fstride;          // bytes from one array of a ring to the next
+    Rings2d rings;           // 2-D OT2
     long long nchunks_max;
     int offs_n;
 };
@@ -772,7 +773,8 @@ size_t field_stream_max(const Setup &su)
     return codec_max_bytes(codec_dims(su.ndim, cdims, su.g.px)) + 256;
 }
 
-Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int op, size_t budget)
+// nshots: shots of the batch the call is part of (1: a call of its own)
+Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int op, size_t budget, int nshots = 1)
 {
     Layout L{};
     size_t off = 0;
@@ -784,10 +786,15 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     const size_t fb = (size_t)su.Pf * 4;
     // 2-D OT2 runs keep rings of levels and of decoded checkpoints (see Prog2d)
     const bool prog = su.prog2d();
-    const int K = su.g.K;
+    const int cdims[3] = {su.g.nx, su.ndim == 3 ? su.g.ny : su.g.nz, su.ndim == 3 ? su.g.nz : 1};
+    const CodecDims cd = codec_dims(su.ndim, cdims, su.g.px);
+    if (prog)
+        L.rings = Prog2d::rings(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, nshots), cd.nchunks, device_cus(),
+                                op == WV_OP_GRADIENT);
+    const Rings2d &R = L.rings;
     L.fstride = align_up(fb, 256);
     L.bk = take(kBk);
-    L.U0 = take(prog ? tile2d_ring(K) * L.fstride : fb);
+    L.U0 = take(prog ? R.levels * L.fstride : fb);
     if (prog) L.U1 = L.U0 + L.fstride;
     else L.U1 = take(fb);
     L.W = take(fb);
@@ -809,10 +816,10 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     }
     const size_t data_bytes = (size_t)(m->nt + 1) * geo->nrec * 4;
     if (op == WV_OP_GRADIENT) {
-        L.L0 = take(prog ? 4 * L.fstride : fb);
+        L.L0 = take(prog ? (R.steps > 1 ? 4 : 3) * L.fstride : fb);
         if (prog) L.L1 = L.L0 + L.fstride;
         else L.L1 = take(fb);
-        L.UB = take(prog ? tile2d_decoded(K) * L.fstride : fb);
+        L.UB = take(prog ? R.decoded * L.fstride : fb);
         L.DB = take(fb);
         if (ot4) L.VU = take(fb);               // OT4 adjoint: w lap u^k for the gradient term
         // 3-D OT2 adjoint: the gradient term an even step carries to the next one
@@ -820,11 +827,9 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
         L.res = take(data_bytes);
         L.dsim = take(data_bytes);
         L.partials = take(kParts * 8);
-        const int cdims[3] = {su.g.nx, su.ndim == 3 ? su.g.ny : su.g.nz, su.ndim == 3 ? su.g.nz : 1};
-        const CodecDims cd = codec_dims(su.ndim, cdims, su.g.px);
         L.nchunks_max = cd.nchunks;
         // the encoder's chunk counts, offsets, block lengths and slots
-        L.enc = take(encode_work_bytes(cd, true, prog ? tile2d_jobs(K) : 1));
+        L.enc = take(encode_work_bytes(cd, true, prog ? R.jobs : 1));
         L.offs_n = 2 * (m->nt + 3);
         L.offs = take((size_t)L.offs_n * 8);
         L.sizes = take((size_t)(m->nt + 1) * 8);   // stream bytes of u^k for each stored state k
@@ -1368,7 +1373,7 @@ int wv_forward(const wv_model *m, const wv_geom *geo, float *data, float *state_
     Fwd f{d, su, geo, s};
     f.at(d.Z, d.Z);
     if (su.prog2d()) {
-        Prog2d p(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, 1));
+        Prog2d p(d.L.rings);
         Run2d run{d, su, geo, s, data};
         for (int n = 0; n < m->nt; ++n) {
             p.step(n, true);
@@ -1451,7 +1456,7 @@ int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const 
     const int N = R.m->nt;
     const long long nrec = R.geo->nrec;
     const bool comp = R.tol > 0;
-    Prog2d p(R.su.g.K, tile2d_choose(R.su.g.K, R.su.g.nx, R.su.g.nz, 1));
+    Prog2d p(d.L.rings);
     auto launch = [&](BatchOp &op) -> int {
         int rc = WV_OK, kind = ADVANCE;
         switch (op.kind) {
@@ -1846,7 +1851,7 @@ int probe_ratio(GradRun &R, double *ratio, double *prof)
     HIPCHK(launch_fill_u64(at<uint64_t>(d.base, d.L.bk + kStats), 2, 0, s));
     int rc;
     int next_sample = 1;
-    Prog2d p(R.su.g.K, tile2d_choose(R.su.g.K, R.su.g.nx, R.su.g.nz, 1));
+    Prog2d p(d.L.rings);
     Run2d run{d, R.su, R.geo, s};
     // u^{n+1}; in memory when a sample needs it
     auto step = [&](int n, bool want) -> int {
@@ -2014,7 +2019,7 @@ int batch_setup(int nshots, const wv_model *ms, const wv_geom *gs, size_t budget
         if (!same) return WV_EINVAL;
         int rc = prepare(&m, &gs[i], su[i]);
         if (rc) return rc;
-        L[i] = plan_layout(&m, &gs[i], su[i], WV_OP_GRADIENT, budget);
+        L[i] = plan_layout(&m, &gs[i], su[i], WV_OP_GRADIENT, budget, nshots);
     }
     const CodecDims cd = codec_dims(2, std::array<int, 3>{su[0].g.nx, su[0].g.nz, 1}.data(), su[0].g.px);
     B.max_ops = Prog2d::most_other_ops(m0.nt);
@@ -2023,9 +2028,13 @@ int batch_setup(int nshots, const wv_model *ms, const wv_geom *gs, size_t budget
     B.ops = align_up(B.desc + (size_t)nshots * sizeof(BatchShot), 256);
     B.shot0 = align_up(B.ops + (size_t)B.max_ops * sizeof(BatchOp), 256);
     size_t lay = 0;
-    for (int i = 0; i < nshots; ++i) lay = std::max(lay, L[i].total);
+    for (int i = 0; i < nshots; ++i) {
+        lay = std::max(lay, L[i].total);
+        // a batch that cannot run together runs each shot alone in its part
+        if (nshots > 1) lay = std::max(lay, plan_layout(&ms[i], &gs[i], su[i], WV_OP_GRADIENT, budget).total);
+    }
     B.chunk_off = align_up(lay, 256);
-    B.shot_bytes = align_up(B.chunk_off + (size_t)tile2d_jobs(su[0].g.K) * cd.nchunks * 4, 256);
+    B.shot_bytes = align_up(B.chunk_off + (size_t)L[0].rings.jobs * cd.nchunks * 4, 256);
     B.total = B.shot0 + (size_t)nshots * B.shot_bytes;
     return WV_OK;
 }
@@ -2146,9 +2155,9 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
     // whose cost grows with the number of arrivals, so the grid is no larger than its widest
     // phase needs: one item per 256-block chunk and field for the codec (phases with more
     // loop over them); without the codec, a workgroup a CU for the misfit.
-    const int steps = tile2d_choose(g.K, g.nx, g.nz, nshots);
+    const Rings2d &rings = L[0].rings;
     A.nwg = (int)std::min<long long>(
-        nwg, tol > 0 ? std::max<long long>((long long)nshots * tile2d_jobs(g.K) * cd.nchunks, 8) : 256);
+        nwg, tol > 0 ? std::max<long long>((long long)nshots * rings.jobs * cd.nchunks, 8) : 256);
     A.fstride = (long long)(L[0].fstride / 4);
     A.slot_elems = (long long)su[0].Pf * 2;
     A.bar = reinterpret_cast<unsigned *>(base + B.hdr);
@@ -2166,7 +2175,7 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
         // What the persistent kernel reads of the program; the steps, of which a run with few
         // slots has many more, go to their launches by value, as the program is built again.
         std::vector<BatchOp> other;
-        Prog2d plan(g.K, steps);
+        Prog2d plan(rings);
         plan.stream(acts, need2, M, tol > 0, true, ActionCodes{}, [&](const BatchOp &op) {
             if (!Prog2d::steps(op)) other.push_back(op);
             return true;
@@ -2206,7 +2215,7 @@ int wv_batch_misfit_gradient(int nshots, const wv_model *models, const wv_geom *
             HIPCHK(launch_batch_steps(A, op, s));
             return WV_OK;
         };
-        Prog2d again(g.K, steps);
+        Prog2d again(rings);
         again.stream(acts, need2, M, tol > 0, true, ActionCodes{},
                      [&](const BatchOp &op) { return (rc = launch(op)) == WV_OK; });
         if (rc || (rc = launch_other())) return rc;
@@ -2354,7 +2363,7 @@ int wv_compressibility(const wv_model *m, const wv_geom *geo, double tol, int st
     Fwd f{d, su, geo, s};
     f.at(d.Z, d.Z);
     int k = 0;
-    Prog2d p(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, 1));
+    Prog2d p(d.L.rings);
     Run2d run{d, su, geo, s};
     for (int n = 0; n < m->nt; ++n) {
         if (su.prog2d()) {

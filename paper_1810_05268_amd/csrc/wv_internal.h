@@ -115,10 +115,14 @@ constexpr int kTileSteps = 8, kTileRegion = 64;   // a workgroup holds 64 x 64 p
 constexpr int tile2d_steps(int K) { return K <= 2 ? 8 : (K == 8 ? 2 : 16 / K); }
 // rim of a region that ns steps make invalid, in whole lanes' blocks
 constexpr int tile2d_halo(int K, int ns) { return (K * ns + 3) & ~3; }
-// Fields of one encode or decode of a 2-D OT2 run (a field of a few hundred points a side is a
-// few dozen chunks, which leave the chip idle: the more together the better), and its field
-// arrays: forward levels (as many waiting to be encoded or read by reverse steps, a group's
-// steps and its base) and decoded checkpoints.
+// What a 2-D OT2 run works with (see Prog2d::rings): its groups, and the field arrays they take.
+struct Rings2d {
+    int steps;      // most steps of a group
+    int jobs;       // most fields of one encode or decode
+    int levels;     // arrays of the ring of forward levels
+    int decoded;    // and of decoded checkpoints
+};
+// bounds of the same for an order
 constexpr int tile2d_jobs(int K) { return tile2d_steps(K) > 4 ? tile2d_steps(K) : 4; }
 constexpr int tile2d_ring(int K) { return 2 * tile2d_jobs(K) + 3; }
 constexpr int tile2d_decoded(int K) { return tile2d_jobs(K) + 2; }

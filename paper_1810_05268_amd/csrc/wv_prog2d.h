@@ -33,11 +33,29 @@ public:
     static bool steps(const BatchOp &op) { return op.kind == kOpStep || op.kind == kOpAdj; }
     static int most_other_ops(int nt) { return 10 * nt + 64; }
 
-    // group: most steps of a group (1 .. tile2d_steps(K))
-    Prog2d(int K, int group)
-        : T(group), NU(tile2d_ring(K)), ND(tile2d_decoded(K)), NE(tile2d_jobs(K))
+    // What a run of order 2 K works with, in groups of up to T steps, on fields of so many codec
+    // chunks.  A forward run holds the two levels a group starts from and the two it leaves.  A
+    // gradient run also holds the levels that wait for an encode or for their reverse steps, and
+    // the checkpoints decoded for those: with so many arrays no schedule of 60 or 301 steps at
+    // 1 to 301 slots has more launches than with any number.
+    // Fields are encoded and decoded several at a time: one of 552 x 552 points is 75 chunks of
+    // 256 lanes, which leave the chip idle, and larger ones save launches and the scan's one
+    // workgroup (40 steps of 4000 x 3000 points with 8 states' memory: 4.8 ms by eights and 5.9 one
+    // by one at order 2, 8.8 by fours and 9.3 at order 8).  From 64 chunks a CU on (8192 x 8192
+    // points, 268 MB an array) arrays count: each goes alone, and at most four levels wait for
+    // reverse steps (groups of eight, at orders 2 and 4: up to 4 % more launches).
+    static Rings2d rings(int K, int T, long long chunks, int cus, bool gradient)
     {
+        if (!gradient) return {T, 1, T > 1 ? 4 : 3, 0};
+        const int jobs = (int)std::min<long long>(tile2d_jobs(K), (64LL * cus + chunks - 1) / chunks);
+        const int most = jobs > 1 ? std::max(T, jobs) : std::min(T, 4);
+        return {T, jobs, T > 1 ? most + 4 : most + 2, most};
     }
+
+    explicit Prog2d(const Rings2d &r) : T(r.steps), NU(r.levels), ND(r.decoded), NE(r.jobs) {}
+
+    // with as many buffers as any run of order 2 K has
+    Prog2d(int K, int group) : Prog2d(Rings2d{group, tile2d_jobs(K), tile2d_ring(K), tile2d_decoded(K)}) {}
 
     // u^{n+1} from the current state, into dest if given (kept); gather: its data row is wanted
     void step(int n, bool gather, int dest = kBufNone)
@@ -56,6 +74,8 @@ public:
             base_row = carry;
             carry = false;
         }
+        // u^{n-1} leaves the state: nothing can ask for it any more
+        if (pend.size() >= 2 && !pend[pend.size() - 2].keep) pend[pend.size() - 2].out = kBufNone;
         pend.push_back({n, out, gather, dest == out});
         up = u;
         u = out;
@@ -197,12 +217,7 @@ public:
                 } else if (comp) {
                     if (hot_slot != b || hot_k != a) {
                         u = up = kBufNone;
-                        int id = kBufNone;
-                        for (int t = 0; t < 2 && id == kBufNone; ++t) {
-                            for (int j = 0; j < ND && id == kBufNone; ++j)
-                                if (!busy(kBufUB + j)) id = kBufUB + j;
-                            if (id == kBufNone) flush_adj();
-                        }
+                        const int id = free_decoded();
                         push_dec(id, kBufNone, 2 * b);
                         hot_buf = id;
                         hot_slot = b;
@@ -287,13 +302,27 @@ private:
         return false;
     }
 
+    // where the next level goes
     int free_level()
     {
         for (int t = 0;; ++t) {
             for (int i = 0; i < NU; ++i)
                 if (!busy(kBufU + i)) return kBufU + i;
-            if (t == 0) flush_adj();   // NU holds a full group and its base without it
+            // the level that leaves the state with this step, if it is only passed through
+            if (pend.size() >= 2 && !pend[pend.size() - 2].keep) return up;
+            if (t == 0) flush_adj();
             else flush();
+        }
+    }
+
+    // where the next checkpoint is decoded (the state has just left, so that the flushes free all)
+    int free_decoded()
+    {
+        for (;;) {
+            for (int i = 0; i < ND; ++i)
+                if (!busy(kBufUB + i)) return kBufUB + i;
+            flush_adj();
+            flush_dec();
         }
     }
 
