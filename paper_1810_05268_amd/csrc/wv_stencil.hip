@@ -39,6 +39,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "wv_chunks3d.h"
 #include "wv_stencil_dev.h"
 
 namespace wv {
@@ -730,40 +731,14 @@ void choose_chunks(long long tiles, int nz, int min_len, int target, int &zchunk
     zchunks = (nz + zlen - 1) / zlen;
 }
 
-// z chunks of a 3-D launch.  A workgroup's time is a start, in which it reads the 2K + 1
-// planes of its queue, and a march of zlen planes; what counts is how many workgroups a CU
-// gets, r = ceil(workgroups / CUs), not whether they all fit at once.  Measured on 168^3 and
-// 200^3 points at order 8 and 296^3 at order 12, a CU with r workgroups takes about
-// 0.35 us (max(r, 2.3) zlen + 2 (2K + 1) r): up to two marches hide each other's latency,
-// more share its throughput, and each start costs.  The least of that over all chunk counts
-// (168^3: 14 chunks of 12 planes, 22 us a forward step; 10 of 17, as many as filled the
-// resident workgroups, 26 us; 200^3: 10 of 20, 31.6 us, against 12 of 17 and 37.7 us).
+// z chunks of a 3-D launch (see chunks3d).
 template <typename Kern>
-void choose_chunks3d(Kern kern, long long tiles, int nz, int K, int &zchunks, int &zlen)
+void choose_chunks3d(Kern kern, long long tiles, int nz, int K, bool grad, int &zchunks, int &zlen)
 {
-    int dev = 0, cus = 256, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
+    int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0) != hipSuccess || per_cu < 1) per_cu = 1;
-    double best = 0.0;
-    zchunks = 0;
-    for (int zc = 1; zc <= nz; ++zc) {
-        const int zl = (nz + zc - 1) / zc;
-        if (zchunks && zl == zlen) continue;             // the same chunks
-        const int n = (nz + zl - 1) / zl;
-        const long long r = (tiles * n + cus - 1) / cus;
-        auto cost = [&](long long c) {
-            return c ? std::max((double)c, 2.3) * zl + 2.0 * (2 * K + 1) * (double)c : 0.0;
-        };
-        const double t = (double)(r / per_cu) * cost(per_cu) + cost(r % per_cu);
-        if (!zchunks || t < best) {
-            best = t;
-            zchunks = n;
-            zlen = zl;
-        }
-        if (r > 8LL * per_cu) break;                     // only more starts from here
-    }
+    zlen = chunks3d(tiles, nz, K, grad, per_cu, device_cus());
+    zchunks = (nz + zlen - 1) / zlen;
 }
 
 // Kernel launch; with events, the dispatch itself records them around the kernel.
@@ -784,7 +759,7 @@ hipError_t launch3d(const Grid &g, const float *fin, const float *prev, float *f
     auto kern = stencil3d<K, GM, WHOLE, MODE>;
     const int tiles_x = (g.nx + 31) / 32, tiles_y = (g.ny + 31) / 32;
     int zchunks, zlen;
-    choose_chunks3d(kern, (long long)tiles_x * tiles_y, g.nz, K, zchunks, zlen);
+    choose_chunks3d(kern, (long long)tiles_x * tiles_y, g.nz, K, GM != kGNone, zchunks, zlen);
     const int nwg = tiles_x * tiles_y * zchunks;
     Side3d S{};
     if (side.inj) {
