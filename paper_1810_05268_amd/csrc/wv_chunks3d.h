@@ -31,9 +31,9 @@ inline int chunks3d(long long tiles, int nz, int K, bool grad, int per_cu, int c
 {
     double best = 0.0;
     int zlen = 0;
-    for (int zc = 1; zc <= nz; ++zc) {
-        const int zl = (nz + zc - 1) / zc;
-        if (zl == zlen) continue;                        // the same chunks
+    // each length that some chunk count has, the longest first: about 2 sqrt(nz) of them (this
+    // runs at every launch: all counts of 1000 planes took 9 us, against 17 us of such a step)
+    for (int zl = nz; zl >= 1;) {
         const int n = (nz + zl - 1) / zl;
         const long long r = (tiles * n + cus - 1) / cus;
         auto cost = [&](long long c) {
@@ -45,7 +45,9 @@ inline int chunks3d(long long tiles, int nz, int K, bool grad, int per_cu, int c
             best = t;
             zlen = zl;
         }
-        if (r > 8LL * per_cu) break;                     // only more starts from here
+        if (zl == 1 || r > 8LL * per_cu) break;          // only more starts from here
+        const int zc = (nz + zl - 2) / (zl - 1);         // the least count with shorter chunks
+        zl = (nz + zc - 1) / zc;
     }
     return zlen;
 }
