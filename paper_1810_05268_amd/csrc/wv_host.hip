@@ -788,9 +788,13 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     const bool prog = su.prog2d();
     const int cdims[3] = {su.g.nx, su.ndim == 3 ? su.g.ny : su.g.nz, su.ndim == 3 ? su.g.nz : 1};
     const CodecDims cd = codec_dims(su.ndim, cdims, su.g.px);
-    if (prog)
-        L.rings = Prog2d::rings(su.g.K, tile2d_choose(su.g.K, su.g.nx, su.g.nz, nshots), cd.nchunks, device_cus(),
-                                op == WV_OP_GRADIENT);
+    if (prog) {
+        const int K = su.g.K, nx = su.g.nx, nz = su.g.nz;
+        const bool gradient = op == WV_OP_GRADIENT;
+        const bool march = nshots == 1 && tile2d_march(K, nx, nz, gradient ? kRunGradient : kRunForward);
+        L.rings = Prog2d::rings(K, march ? 1 : tile2d_choose(K, nx, nz, nshots), cd.nchunks, device_cus(), gradient,
+                                march);
+    }
     const Rings2d &R = L.rings;
     L.fstride = align_up(fb, 256);
     L.bk = take(kBk);
@@ -816,7 +820,7 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     }
     const size_t data_bytes = (size_t)(m->nt + 1) * geo->nrec * 4;
     if (op == WV_OP_GRADIENT) {
-        L.L0 = take(prog ? (R.steps > 1 ? 4 : 3) * L.fstride : fb);
+        L.L0 = take(prog ? R.lam * L.fstride : fb);
         if (prog) L.L1 = L.L0 + L.fstride;
         else L.L1 = take(fb);
         L.UB = take(prog ? R.decoded * L.fstride : fb);
@@ -1123,6 +1127,7 @@ struct Run2d {
     const CodecDims *cd = nullptr;
     double tol = 0.0;
     ActionTimer *kt = nullptr;          // optional per-launch timing of the stencils
+    bool march = d.L.rings.march;
 
     float *ptr(int id) const
     {
@@ -1152,6 +1157,7 @@ struct Run2d {
         if (op.e && !data) return WV_EINVAL;   // a program without rows gathers none
         A.gmask = (unsigned)op.e;
         A.rows = data ? data + (size_t)op.n * geo->nrec : nullptr;
+        A.march = march;
         return launch(A, 0);
     }
     int adjoint(const BatchOp &op)
@@ -1169,6 +1175,7 @@ struct Run2d {
         A.vstride = -(long long)geo->nrec;
         A.G = G;
         A.gscale = gscale;
+        A.march = march;
         return launch(A, 1);
     }
     int launch(const Tile2dArgs &A, int kind)
@@ -1516,8 +1523,10 @@ int run_program(GradRun &R, Run2d &run, const std::vector<int32_t> &acts, const 
 int run_adjoint_src(GradRun &R, Run2d &run)
 {
     run.G = nullptr;
-    int lam = 0, lamp = 1, out = 2;
+    run.march = tile2d_march(R.su.g.K, R.su.g.nx, R.su.g.nz, kRunAdjointSrc) || R.d.L.rings.march;
+    int lam = 0, lamp = 1;
     for (int k = R.m->nt; k >= 1; --k) {
+        const int out = run.march ? lamp : 3 - lam - lamp;
         BatchOp op{};
         op.n = k;
         op.ns = 1;
@@ -1528,10 +1537,8 @@ int run_adjoint_src(GradRun &R, Run2d &run)
         int rc = run.adjoint(op);
         if (rc) return rc;
         HIPCHK(launch_gather_sum(R.d.src, run.ptr(kBufL + out), R.src_adj + (k - 1), run.s));
-        const int next = 3 - lam - out;
         lamp = lam;
         lam = out;
-        out = next;
         R.reverses++;
     }
     return WV_OK;

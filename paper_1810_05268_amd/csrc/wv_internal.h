@@ -55,16 +55,18 @@ struct Sparse {
     int *s_pos;
 };
 
-// What a 3-D step's launch does beside the step.
+// What a step's launch does beside the step.
 struct StepSide {
-    // injects into the level it writes at the points of inj (np > 0): plane holds their
-    // values in np pitched planes, each multiplied by *scale when scale is set
+    // injects into the level it writes at the points of inj.  3-D (np > 0): plane holds their
+    // values in np pitched planes, each multiplied by *scale when scale is set; 2-D: the samples
+    // are vals
     const Sparse *inj = nullptr;
     const float *plane = nullptr, *scale = nullptr;
+    const float *vals = nullptr;
     // gathers the receivers of its input level into row
     const Sparse *gat = nullptr;
     float *row = nullptr;
-    // sums the samples next_vals at the points of next into the planes next_plane (the
+    // 3-D: sums the samples next_vals at the points of next into the planes next_plane (the
     // values a later step injects; places of no point are not written)
     const Sparse *next = nullptr;
     const float *next_vals = nullptr;
@@ -88,9 +90,9 @@ hipError_t launch_fwd_step(const Grid &g, const float *u_in, const float *u_prev
 constexpr int kGNone = 0, kGAdd = 1, kGCarryOut = 2, kGCarryIn = 3;
 // Adjoint step (lam_in = lam^k, lam_next = lam^{k+1}, lam_out = lam^{k-1}, may equal
 // lam_next): the same update, and (if G) G += gscale * uk * (w lap lam_in), or the
-// carried form gmode selects with the array carry (pitched like a field).  Single OT2 steps
-// are for 3-D grids; 2-D grids take launch_tile2d.
-// An injection adds its gradient term too.
+// carried form gmode selects with the array carry (pitched like a field).  An injection adds
+// its gradient term too.
+// 2-D OT2 steps go through launch_tile2d, which marches some grids with these two.
 hipError_t launch_adj_step(const Grid &g, const float *lam_in, const float *lam_next, float *lam_out,
                            const float *w, const float *uk, double *G, double gscale, hipStream_t s,
                            LaunchEvents ev = {}, float *carry = nullptr, int gmode = kGAdd,
@@ -121,6 +123,8 @@ struct Rings2d {
     int jobs;       // most fields of one encode or decode
     int levels;     // arrays of the ring of forward levels
     int decoded;    // and of decoded checkpoints
+    int lam;        // adjoint levels
+    bool march;     // steps march one by one instead of running in tiles
 };
 // bounds of the same for an order
 constexpr int tile2d_jobs(int K) { return tile2d_steps(K) > 4 ? tile2d_steps(K) : 4; }
@@ -139,12 +143,15 @@ struct Tile2dArgs {
     const float *uk[kTileSteps];    // with G: u^k of step j, and the gradient (dense)
     double *G;
     double gscale;
+    bool march;                     // of ns = 1 with out[0] set: marched instead, with the same bits
     __host__ __device__ const float *level(int j) const { return uk[j]; }
     __host__ __device__ float *dest(int j) const { return out[j]; }
 };
 hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev = {});
 int device_cus();
-bool tile2d_march(int K, int nx, int nz);
+// whether the steps of a call for one shot march
+enum { kRunForward, kRunGradient, kRunAdjointSrc };
+bool tile2d_march(int K, int nx, int nz, int run);
 // steps per group for a grid, nshots shots advancing together
 int tile2d_choose(int K, int nx, int nz, int nshots);
 

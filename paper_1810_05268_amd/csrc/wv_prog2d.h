@@ -34,7 +34,8 @@ public:
     static int most_other_ops(int nt) { return 10 * nt + 64; }
 
     // What a run of order 2 K works with, in groups of up to T steps, on fields of so many codec
-    // chunks.  A forward run holds the two levels a group starts from and the two it leaves.  A
+    // chunks.  Marched steps (T = 1) write the level they start from last, so that a CU finds more
+    // of what it reads in the L2.  A forward run holds the two levels a group starts from and the two it leaves.  A
     // gradient run also holds the levels that wait for an encode or for their reverse steps, and
     // the checkpoints decoded for those: with so many arrays no schedule of 60 or 301 steps at
     // 1 to 301 slots has more launches than with any number.
@@ -44,18 +45,19 @@ public:
     // by one at order 2, 8.8 by fours and 9.3 at order 8).  From 64 chunks a CU on (8192 x 8192
     // points, 268 MB an array) arrays count: each goes alone, and at most four levels wait for
     // reverse steps (groups of eight, at orders 2 and 4: up to 4 % more launches).
-    static Rings2d rings(int K, int T, long long chunks, int cus, bool gradient)
+    static Rings2d rings(int K, int T, long long chunks, int cus, bool gradient, bool march)
     {
-        if (!gradient) return {T, 1, T > 1 ? 4 : 3, 0};
+        const int lam = march ? 2 : (T > 1 ? 4 : 3);
+        if (!gradient) return {T, 1, lam, 0, 0, march};
         const int jobs = (int)std::min<long long>(tile2d_jobs(K), (64LL * cus + chunks - 1) / chunks);
         const int most = jobs > 1 ? std::max(T, jobs) : std::min(T, 4);
-        return {T, jobs, T > 1 ? most + 4 : most + 2, most};
+        return {T, jobs, most + (march ? 1 : (T > 1 ? 4 : 2)), most, lam, march};
     }
 
-    explicit Prog2d(const Rings2d &r) : T(r.steps), NU(r.levels), ND(r.decoded), NE(r.jobs) {}
+    explicit Prog2d(const Rings2d &r) : T(r.steps), NU(r.levels), ND(r.decoded), NE(r.jobs), march(r.march) {}
 
     // with as many buffers as any run of order 2 K has
-    Prog2d(int K, int group) : Prog2d(Rings2d{group, tile2d_jobs(K), tile2d_ring(K), tile2d_decoded(K)}) {}
+    Prog2d(int K, int group) : Prog2d(Rings2d{group, tile2d_jobs(K), tile2d_ring(K), tile2d_decoded(K), 4, false}) {}
 
     // u^{n+1} from the current state, into dest if given (kept); gather: its data row is wanted
     void step(int n, bool gather, int dest = kBufNone)
@@ -112,8 +114,8 @@ public:
             op.a = lam;
             op.b = lamp;
             for (int j = 0; j < op.ns; ++j) op.c[j] = adj[i + j].second;
-            int fr[2], nf = 0;
-            for (int q = 0; q < 4 && nf < 2; ++q)
+            int fr[2] = {lamp, kBufNone}, nf = 0;
+            for (int q = 0; q < 4 && nf < 2 && !march; ++q)
                 if (kBufL + q != lam && kBufL + q != lamp) fr[nf++] = kBufL + q;
             op.d[0] = fr[0];
             op.d[1] = op.ns > 1 ? fr[1] : kBufNone;
@@ -270,6 +272,7 @@ private:
         int dest, sub, base;
     };
     const int T, NU, ND, NE;
+    const bool march;
     std::vector<Step> pend;
     int base_u = kBufNone, base_up = kBufNone;
     bool base_row = false, carry = false;   // the base's / the current level's data row is still to be gathered
@@ -286,10 +289,11 @@ private:
         return op;
     }
 
-    // whether something collected, or the current state, still reads or writes the buffer
-    bool busy(int id) const
+    // whether the current state is in the buffer, or something collected still reads or writes it
+    bool busy(int id) const { return id == u || id == up || wanted(id); }
+
+    bool wanted(int id) const
     {
-        if (id == u || id == up) return true;
         if (!pend.empty() && (id == base_u || id == base_up)) return true;
         for (const Step &p : pend)
             if (p.out == id) return true;
@@ -306,6 +310,7 @@ private:
     int free_level()
     {
         for (int t = 0;; ++t) {
+            if (march && up >= kBufU && up < kBufU + NU && !wanted(up)) return up;
             for (int i = 0; i < NU; ++i)
                 if (!busy(kBufU + i)) return kBufU + i;
             // the level that leaves the state with this step, if it is only passed through

@@ -514,22 +514,55 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
     }
 }
 
-// 2-D OT4 (OT2 runs in tiles, see wv_tile2d_dev.h): a workgroup owns 256 consecutive x and
-// marches down z (the second axis).  `prev` and `fout` may be the same array (read, then
-// written, by the same lane).  MODE as for the 3-D kernel.
+// What a marched 2-D OT2 step's launch does beside the step (see StepSide): both as launches of
+// their own took 2.7 us more, of 60 for a forward step of 4000 x 3000 points at order 16.
+struct Side2d {
+    Sparse inj;                      // samples inj_vals at its points, when set
+    const float *inj_vals;
+    Sparse gat;                      // receivers of the input level into row, by gat_wg workgroups
+    float *row;
+    int gat_wg;
+};
+
+// 2-D march: OT4, and OT2 where tiles are slower (see tile2d_march): a workgroup owns 256
+// consecutive x and marches down z (the second axis).  `prev` and `fout` may be the same array
+// (read, then written, by the same lane).  MODE as for the 3-D kernel.
+// With samples to inject, an OT2 workgroup then adds those of its strip and rows to the level it
+// has just written, as inject_kernel would after the step (the same arithmetic in the same
+// order).  Further workgroups gather the receivers.
 template <int K, bool GRAD, int MODE>
 __global__ __launch_bounds__(256) void stencil2d(Grid g, const float *__restrict__ fin, const float *prev,
                                                  float *fout, const float *__restrict__ w,
                                                  const float *__restrict__ uk, const float *__restrict__ xtra,
                                                  const float *__restrict__ xtra2, double *__restrict__ G,
-                                                 double gscale, int tiles_x, int zchunks, int zlen)
+                                                 double gscale, int tiles_x, int zchunks, int zlen, Side2d S)
 {
     static_assert(MODE != kLapW || !GRAD, "w lap carries no gradient term");
     __shared__ float row[256 + 2 * K];
-    const int lid = xcd_remap(blockIdx.x, tiles_x * zchunks);
+    const int nwg = tiles_x * zchunks;
+    if constexpr (MODE == kOT2) {
+        if ((int)blockIdx.x >= nwg) {
+            const int r = ((int)blockIdx.x - nwg) * 256 + (int)threadIdx.x;
+            if (r < S.gat.n) S.row[r] = gather_point(S.gat, r, fin);
+            return;
+        }
+    }
+    const int lid = xcd_remap(blockIdx.x, nwg);
     const int tix = lid % tiles_x, zc = lid / tiles_x;
     const int z0 = zc * zlen, z1 = min(z0 + zlen, g.nz);
     march2d<K, GRAD, MODE>(g, fin, prev, fout, w, uk, xtra, xtra2, G, gscale, tix, z0, z1, row);
+    if constexpr (MODE == kOT2) {
+        if (S.inj_vals) {
+            __syncthreads();
+            const int nx = g.nx, x0 = tix * 256, x1 = min(x0 + 256, nx);
+            for (int i = threadIdx.x; i < S.inj.npts; i += 256) {
+                const int p = S.inj.s_pts[i];
+                const int z = p / nx, x = p - z * nx;
+                if (z < z0 || z >= z1 || x < x0 || x >= x1) continue;
+                inject_point<GRAD>(g, S.inj, i, p, x, 0, z, S.inj_vals, w, fout, uk, G, p, gscale);
+            }
+        }
+    }
 }
 
 // Adds w s / (1+a) at the source (or receiver) points of the level just written.
@@ -802,9 +835,19 @@ hipError_t launch_k(const Grid &g, const float *fin, const float *prev, float *f
     const int tiles_x = (g.nx + 255) / 256;
     int zchunks, zlen;
     choose_chunks(tiles_x, g.nz, K, 2048, zchunks, zlen);
-    if (side.inj || side.row || side.next) return hipErrorInvalidValue;
-    launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(tiles_x * zchunks), s, ev, g, fin, prev, fout, w, uk, xtra,
-                 xtra2, G, gscale, tiles_x, zchunks, zlen);
+    Side2d S{};
+    if (side.next || (MODE != kOT2 && (side.inj || side.row))) return hipErrorInvalidValue;
+    if (side.inj) {
+        S.inj = *side.inj;
+        S.inj_vals = side.vals;
+    }
+    if (side.gat && side.row) {
+        S.gat = *side.gat;
+        S.row = side.row;
+        S.gat_wg = (S.gat.n + 255) / 256;
+    }
+    launch_timed(stencil2d<K, GM == kGAdd, MODE>, dim3(tiles_x * zchunks + S.gat_wg), s, ev, g, fin, prev, fout, w, uk,
+                 xtra, xtra2, G, gscale, tiles_x, zchunks, zlen, S);
     return hipGetLastError();
 }
 

@@ -16,6 +16,8 @@ __global__ __launch_bounds__(kTileThreads) void tile2d_kernel(const Grid g, cons
     tile2d<K, GRAD>(g, A, lid % tiles_x, lid / tiles_x, S);
 }
 
+constexpr int kMarchPoints = 4096;   // at most so many are injected by the marching workgroups
+
 template <int K>
 hipError_t launch_k(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev)
 {
@@ -60,12 +62,23 @@ hipError_t launch_batch_k(const BatchArgs &A, const BatchOp &op, hipStream_t s)
 hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, LaunchEvents ev)
 {
     if (g.ndim != 2 || A.ns < 1 || A.ns > tile2d_steps(g.K)) return hipErrorInvalidValue;
-    if (A.ns == 1 && A.out[0] && tile2d_march(g.K, g.nx, g.nz)) {
-        hipError_t rc = A.gmask ? launch_gather(A.gat, A.u, A.rows, s) : hipSuccess;
-        if (rc == hipSuccess)
-            rc = A.G ? launch_adj_step(g, A.u, A.up, A.out[0], A.w, A.uk[0], A.G, A.gscale, s, ev, nullptr, kGAdd, {})
-                     : launch_fwd_step(g, A.u, A.up, A.out[0], A.w, s, ev, {});
-        if (rc == hipSuccess) rc = launch_inject_res(g, A.inj, A.vals, A.w, A.out[0], A.uk[0], A.G, A.gscale, s);
+    if (A.march && A.ns == 1 && A.out[0]) {
+        // every workgroup looks through the injected points
+        const bool fused = A.inj.npts <= kMarchPoints;
+        StepSide side;
+        if (fused) {
+            side.inj = &A.inj;
+            side.vals = A.vals;
+        }
+        if (A.gmask) {
+            side.gat = &A.gat;
+            side.row = A.rows;
+        }
+        hipError_t rc = A.G ? launch_adj_step(g, A.u, A.up, A.out[0], A.w, A.uk[0], A.G, A.gscale, s, ev, nullptr,
+                                              kGAdd, side)
+                            : launch_fwd_step(g, A.u, A.up, A.out[0], A.w, s, ev, side);
+        if (rc == hipSuccess && !fused)
+            rc = launch_inject_res(g, A.inj, A.vals, A.w, A.out[0], A.uk[0], A.G, A.gscale, s);
         return rc;
     }
     switch (g.K) {
@@ -107,15 +120,28 @@ int device_cus()
     return cus;
 }
 
-// Whether a shot's steps are marched one by one (stencil2d) instead: for operators wider than
-// order 8 on grids of more than 4 regions a CU, where a region's rim is most of it and its
-// loads are no longer hidden.  At order 16 on 4000 x 3000 points a forward step takes 112 us in
-// tiles and 76 marched, on 2000 x 1500 an adjoint one 61 and 43 (a forward one 31 either way);
-// at order 8 tiles are faster on both (66 and 74 us, 19 and 28).
-bool tile2d_march(int K, int nx, int nz)
+// Whether the steps of a call march one by one (stencil2d) instead of running in tiles, which a
+// region's rim and its loads, no longer hidden behind each other, make slower on large grids, the
+// wider the operator the sooner.  By the regions of one step a CU would get; microseconds a step,
+// marched / in the best groups:
+//   forward calls: order 10, 1200 x 900 points (1.9) 14.6 / 15.7; order 16, 1500 x 1200 (3.1)
+//     22.7 / 27.0; order 8, 3000 x 2200 (8.4) 41.6 / 41.9 and 4000 x 3000 (15) 65.4 / 70.7; order 6,
+//     4000 x 3000 64.3 / 64.0 and 6000 x 5000 (38) 146 / 166; orders 2 and 4 there 116 / 74 and
+//     147 / 113.
+//   gradients (a forward and an adjoint step): order 8, 4000 x 3000 167 / 164 and 6000 x 5000
+//     396 / 416; order 6 there 396 / 353; order 10, 1500 x 1200 43.8 / 42.8, 2000 x 1500 (5.2)
+//     57.5 / 61.6; order 16, 1200 x 900 43.4 / 35.4 and 1500 x 1200 51.9 / 55.0.
+//   the adjoint of the source, whose every level is sampled, goes step by step: order 4, 250 x 200
+//     (0.1) 13.4 / 14.8, 1200 x 900 (1.5) 17.6 / 20.2, 6000 x 5000 155 / 224; order 16, 552 x 552
+//     (0.6) 19.0 / 15.6, 1500 x 1200 27.6 / 30.7.
+bool tile2d_march(int K, int nx, int nz, int run)
 {
     const int core = kTileRegion - 2 * tile2d_halo(K, 1);
-    return K > 4 && (long long)((nx + core - 1) / core) * ((nz + core - 1) / core) > 4LL * device_cus();
+    const double r = (double)((nx + core - 1) / core) * ((nz + core - 1) / core) / device_cus();
+    if (run == kRunAdjointSrc) return K <= 4 || r > 1.0;
+    if (K <= 2) return false;
+    if (run == kRunForward) return r > (K == 3 ? 16.0 : (K == 4 ? 10.0 : 1.5));
+    return K > 3 && r > (K == 4 ? 20.0 : (K <= 6 ? 4.0 : 2.5));
 }
 
 // Steps per group.  A group of ns steps costs a launch with its first regions, 5 + (0.9 + K / 6) ns
@@ -124,7 +150,6 @@ bool tile2d_march(int K, int nx, int nz)
 // ns or one within 5 % of it on all of them).  More steps mean a wider rim and so more regions.
 int tile2d_choose(int K, int nx, int nz, int nshots)
 {
-    if (nshots == 1 && tile2d_march(K, nx, nz)) return 1;
     const int cus = device_cus();
     int best = 1;
     double best_t = 0.0;

@@ -2,7 +2,7 @@
 // op does is concurrent on the device, so its reads are taken before any of its writes, it
 // writes no array twice, and none that it reads.
 //   stdin: cases of "K T chunks M comp nact" and nact action triples, or "K T 0 0 0 n": n steps of
-//   a forward run
+//   a forward run; T = 0: steps that march, which may write the level they read last
 //   stdout: a line a case with the arrays; exit code 1 with a message on the first fault
 #include <cstdio>
 #include <cstdlib>
@@ -52,15 +52,16 @@ int main()
                 if (j < need2.size() && acts[3 * j] == 1) need2[holder[acts[3 * i + 2]]] = 1;
             }
         }
-        const Rings2d R = Prog2d::rings(K, T, chunks ? chunks : 1, 256, !forward);
-        NEED(R.steps == T && R.jobs >= 1 && R.jobs <= kEncJobs && R.jobs <= kTileSteps);
+        const bool march = T == 0;
+        if (march) T = 1;
+        const Rings2d R = Prog2d::rings(K, T, chunks ? chunks : 1, 256, !forward, march);
+        NEED(R.steps == T && R.march == march && R.jobs >= 1 && R.jobs <= kEncJobs && R.jobs <= kTileSteps);
         NEED(kBufU + R.levels <= kBufUB && kBufUB + R.decoded <= kBufSlot);
-        const int nlam = T > 1 ? 4 : 3;
         std::map<int, std::string> mem{{kBufZ, "0"}, {kBufL, "L"}, {kBufL + 1, "L"}}, arena;
         auto lam = [&](int k) { return k >= N ? std::string("L") : "l" + std::to_string(k); };
         auto writable = [&](int id) {
             return (id >= kBufU && id < kBufU + R.levels) ||
-                   (!forward && (id == kBufDB || (id >= kBufL && id < kBufL + nlam) ||
+                   (!forward && (id == kBufDB || (id >= kBufL && id < kBufL + R.lam) ||
                                  (id >= kBufUB && id < kBufUB + R.decoded) ||
                                  (!comp && id >= kBufSlot + 2 && id < kBufSlot + 2 + 2 * M)));
         };
@@ -131,6 +132,10 @@ int main()
                 break;
             case kOpMisfit: break;
             default: NEED(false);
+            }
+            if (march && (op.kind == kOpStep || op.kind == kOpAdj) && op.a != op.b) {
+                reads.erase(op.b);   // each lane its own point
+                if (op.kind == kOpAdj) NEED(op.c[0] != op.b);
             }
             for (int id : writes) NEED(!reads.count(id));
             for (const auto &[id, v] : after) mem[id] = v;

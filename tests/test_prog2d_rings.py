@@ -35,7 +35,7 @@ def test_gradient_programs_fit_the_arrays(run, comp):
     (every state recomputed from the first) to one a state."""
     lines, n = [], 0
     for K in (1, 3, 4, 6, 8):
-        for T in sorted({1, 2, _most(K)}):
+        for T in sorted({0, 1, 2, _most(K)}):   # 0: steps march
             for chunks in CHUNKS:
                 for nt in (1, 2, 9, 40, 101):
                     for M in sorted({1, 2, 5, 20, max(1, nt - 1), nt}):
@@ -49,7 +49,7 @@ def test_gradient_programs_fit_the_arrays(run, comp):
 
 
 def test_forward_programs_and_sizes(run):
-    got = run([f"{K} {T} 0 0 0 {nt}" for K in (1, 4, 8) for T in sorted({1, 2, _most(K)}) for nt in (1, 2, 3, 9, 40)])
+    got = run([f"{K} {T} 0 0 0 {nt}" for K in (1, 4, 8) for T in sorted({0, 1, 2, _most(K)}) for nt in (1, 2, 3, 9, 40)])
     assert all(levels <= 4 and decoded == 0 for _, levels, decoded in got)
     # a field that fills the chip alone, one step a launch: two levels, the next, one decoded
     a = P.schedule(40, 5, write_min=False)
