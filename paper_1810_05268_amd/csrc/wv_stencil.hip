@@ -364,10 +364,12 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
             for (int i = 0; i < 4; ++i) sy[i] += fmaf(-cf2, q[i][K], fy[i]);
         }
         // damping a = dampx dx^2 + dampy dy^2 + dampz dz^2; the change of this step is
-        // formed from the two levels and added once
+        // formed from the two levels and added once.  Which product is fused with a sum is written
+        // out where the compiler could choose: it did so by the unrolled copy of the plane, and the
+        // corners of the layer came to depend, in their last bit, on how z is split
         const int dy_ = layer_depth(y, g.ix0[1], g.ix1[1]);
         const int dz_ = layer_depth(z, g.ix0[2], g.ix1[2]);
-        const float ayz = g.dampy * (float)(dy_ * dy_) + g.dampz * (float)(dz_ * dz_);
+        const float ayz = fmaf(g.dampz, (float)(dz_ * dz_), g.dampy * (float)(dy_ * dy_));
         const float pin[4] = {S.p.x, S.p.y, S.p.z, S.p.w};
         const float win[4] = {S.w.x, S.w.y, S.w.z, S.w.w};
         const float uin[4] = {S.u.x, S.u.y, S.u.z, S.u.w};
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(256, 2) void stencil3d(const Grid g, const float *_
                 const int dx_ = layer_depth(x0 + i, g.ix0[0], g.ix1[0]);
                 const float a = fmaf(g.dampx, (float)(dx_ * dx_), ayz);
                 const float r = __builtin_amdgcn_rcpf(1.0f + a);
-                on[i] = ctr + ((1.0f - a) * (ctr - pin[i]) + wl[i]) * r;
+                on[i] = fmaf(fmaf(1.0f - a, ctr - pin[i], wl[i]), r, ctr);
             }
         }
         // injected values of this plane (0 where a point has none): w s and w s / (1+a)
