@@ -271,7 +271,7 @@ __global__ __launch_bounds__(256) void encode_place_kernel(EncArgs A)
         const long long b = c * kBlocksPerChunk + tid;
         if (b < A.nblocks) ((uint16_t *)(A.out + base + kHdr + 8 * A.nchunks))[b] = A.lens[e * A.nblocks + b];
     }
-    if (base + (uint64_t)A.prefix_bytes + (off + cw) * 8ull > A.cap) return;   // flagged by pass 2
+    if (base + (uint64_t)A.prefix_bytes + (off + cw) * 8ull > A.cap) return;   // write_header flags it
     unsigned long long *data = (unsigned long long *)(A.out + base + A.prefix_bytes) + off;
     if (A.staging && cw <= (uint32_t)A.slot_words) {
         const unsigned long long *slot = A.staging + (e * A.nchunks + c) * (long long)A.slot_words;

@@ -17,8 +17,8 @@ constexpr int kBlocksPerChunk = 256; // codec: blocks per chunk (one workgroup)
 // absent (ny = 1) and the model's second axis is z.
 // The solver's field arrays (wavefields, w, checkpoint slots) are pitched: point
 // (x, y, z) sits at x + px (y + ny z), with px = nx rounded up to 32 in 3-D, so that
-// every row starts on a 128-byte line (columns nx..px-1 hold zeros and are never
-// read as grid points).  In 2-D px = nx.  Arrays the caller owns (velocity,
+// every row starts on a 128-byte line (the columns from nx to a multiple of four
+// hold zeros, those after them nothing that is read).  In 2-D px = nx.  Arrays the caller owns (velocity,
 // gradient, final state) are dense: x + nx (y + ny z).
 struct Grid {
     int nx, ny, nz;          // padded extents
@@ -35,10 +35,10 @@ struct Grid {
     long long P;             // elements of one field array: px * ny * nz
 };
 
-// Sparse point operators (sources / receivers), built on the host.
 // A 3-D step injects in its own launch when the points lie in few grid planes (a surface
 // survey: one plane on the nodes, two between them); more planes take a launch of their own.
 constexpr int kInjPlanes = 4;
+// Sparse point operators (sources / receivers), built on the host.
 //   gather:  out[r] = sum_c wt[r*nc + c] * f[idx[r*nc + c]]
 //   scatter: unique points pts[i], entries [start[i], start[i+1]) of (col, wt)
 struct Sparse {
@@ -193,7 +193,7 @@ struct CodecDims {
 // pitch 0: dense rows (pitch = dims[0])
 CodecDims codec_dims(int ndim, const int *dims, int pitch = 0);
 size_t codec_max_bytes(const CodecDims &cd);
-// Encode fields of one geometry in three launches, job by job into out + *base (device
+// Encode fields of one geometry, in two launches or (many chunks) three, job by job into out + *base (device
 // offset), capacity cap bytes from `out`; *next = *base + stream bytes rounded up to 256.  A
 // job whose base is the word the job before it writes as its next starts where that ends.
 // work: encode_work_bytes(cd, staged, jobs) bytes, 256-byte aligned, any contents (chunk

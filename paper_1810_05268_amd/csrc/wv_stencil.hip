@@ -5,8 +5,8 @@
 //   u^{n+1} = [2u^n - (1-a)u^{n-1} + w(lap u^n + s^n)]/(1+a),   w = dt^2 c^2,
 // so a step moves exactly three reads and one write per point.  It is evaluated as
 //   u^{n+1} = u^n + [(1-a)(u^n - u^{n-1}) + w lap u^n]/(1+a)
-// (the source term is added by the injection kernel): the small per-step change is
-// formed first and added once, which keeps binary32 rounding near 5e-6 relative over
+// (the source term is added after it, by the same launch where it can be): the small per-step
+// change is formed first and added once, which keeps binary32 rounding near 5e-6 relative over
 // thousands of steps.  The adjoint of the recursion has the same form run backward
 // in time (lam^{k-1} overwrites lam^{k+1}) with the residual injected at the
 // receivers; the gradient of the misfit with respect to m accumulates

@@ -60,10 +60,11 @@ struct Tile2dShared {
 static_assert(sizeof(Tile2dShared<1>) <= 81920 && sizeof(Tile2dShared<2>) <= 81920 &&
               sizeof(Tile2dShared<5>) <= 81920 && sizeof(Tile2dShared<8>) <= 81920);
 
-// n[i] / b[i], r the binary32 reciprocals of b (1 <= b < 4).  The first correction leaves less
-// than an ulp and the second rounds correctly, as long as the remainders are exact: below
-// 2^-100 they are not, and a wave with such a value divides (a long run is sensitive to a
-// single bit: the smallest values are those ahead of a wavefront, which grow by many orders).
+// n[i] / b[i], r the binary32 reciprocals of b (b >= 1: 1 + a, at most 8.4 in the corners of a
+// layer one cell thick).  The first correction leaves less than an ulp and the second rounds
+// correctly, as long as the remainders are exact and nothing overflows: for |n| below 2^-100 they
+// may not be, and a wave with such a value divides (a long run is sensitive to a single bit: the
+// smallest values are those ahead of a wavefront, which grow by many orders).
 __device__ __forceinline__ void div4(const float *n, const float *b, const float *r, float *q)
 {
 #pragma clang fp contract(off)

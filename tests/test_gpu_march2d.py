@@ -63,3 +63,22 @@ def test_adjoint_of_the_source(n, order):
     ref = S.adjoint_src(r.astype(np.float64))
     assert np.any(ref)
     assert rel_l2(G.adjoint_src(torch.as_tensor(r, device="cuda")).cpu().numpy(), ref) <= 1e-4
+
+
+@pytest.mark.parametrize("nbl", [1, 2])
+def test_thin_layers_divide_alike(nbl):
+    """Marched steps divide by 1 + a, tiles multiply by its corrected reciprocal.  At the stability
+    limit a layer of one cell has 1 + a up to 6.6 at order 10; source and receivers lie at its corner."""
+    import torch
+    from tests.test_gpu_batch import _batch, _device, _shots
+    shots = []
+    for sh in _shots((1018, 1010), 40, 10, 2, seed=nbl):
+        x, z = np.meshgrid(np.arange(24) * 7.0, np.arange(24) * 7.0)
+        shots.append(W.replace(sh, nbl=nbl, cfl_frac=0.99, src=np.array([[30.0, 40.0]]),
+                               rec=np.stack([x.ravel(), z.ravel()], axis=1)))
+    devs, dobs, _ = _device(shots)
+    zero = [torch.zeros_like(d) for d in dobs]
+    _, _, dsims, _ = _batch(devs, zero, 20 * devs[0].slot_bytes, 0.0, 0.0)
+    for d, ds in zip(devs, dsims):
+        data = d.forward()
+        assert torch.count_nonzero(data[-1]) == data.shape[1] and torch.equal(data, ds)
