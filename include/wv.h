@@ -153,9 +153,9 @@ double wv_cfl_dt_to(int ndim, const double *h, int space_order, double vmax, int
  * the checkpoint arena of mem_budget bytes is part of the workspace).  Returns 0
  * on invalid arguments.  Host only.
  * Beside the arena and the data rows a forward call of time order 2 takes four field arrays
- * in 3-D and five or six in 2-D (whose steps run in groups), a gradient call ten in 3-D.  In 2-D
- * it takes 23 at order 8 (20 to 35 at the others), of which 13 hold levels and decoded
- * checkpoints and four stage the encoder; grids of 67 million points and more take 16 (11 to 20). */
+ * in 3-D and four to six in 2-D (whose steps run in groups), a gradient call ten in 3-D.  In 2-D
+ * it takes 23 at order 8 (18 to 35 at the others), of which 13 hold levels and decoded
+ * checkpoints and four stage the encoder; grids of 67 million points and more take 16 (9 to 20). */
 size_t wv_workspace_bytes(const wv_model *model, const wv_geom *geom, int op, size_t mem_budget);
 
 /* Elements of one solver field array.  The library keeps its own wavefields, w and
