@@ -11,16 +11,16 @@ namespace wv {
 // chunk; what counts is how many workgroups a CU gets, r = ceil(workgroups / CUs), not whether
 // they all fit at once.  Counted in planes marched, a CU with r workgroups that are resident
 // together takes max(r, 2.05) zlen (two marches hide each other's latency, more share its
-// throughput) and for their starts 0.7 (2K + 1) sqrt(r) + 0.4 r; a plane of a step with a
-// gradient is twice the traffic, so that 1.3 marches fill a CU and a start counts half.  The
-// least of that over all chunk counts.
+// throughput; 2.03 at orders 2 and 4, where three are about even with two) and for their starts
+// 0.7 (2K + 1) sqrt(r) + 0.4 r (0.8 r at order 2); a plane of a step with a gradient is twice the
+// traffic, so that 1.3 marches fill a CU and a start counts half.  The least of that over all
+// chunk counts.
 // Fitted to 47 grids of 24^3 to 400^3 points, cubes and slabs, at orders 2 to 16, each at up to
-// 16 chunk lengths: within 0.7 % of the best of them on average.  On 60 other grids at orders 4 to
-// 16 one kernel of 480 takes over 2 % longer than with chunks that fill the resident workgroups
-// once and hold at least 4K planes.  Where it differs from an earlier fit, to 168^3 and 200^3
-// points at order 8 and 296^3 at order 12, which weighed starts three times as much, kernels take
-// 8 % less on average, and at most 6.5 % more (forward steps at order 4, where three marches a CU
-// and two are about even).  Microseconds a forward / adjoint step:
+// 16 chunk lengths: within 0.7 % of the best of them on average.  On 170 other grids 12 kernels of
+// 2040 take over 3 % longer than with chunks that fill the resident workgroups once and hold at
+// least 4K planes, most of them forward steps at order 2.  An earlier fit, to 168^3 and 200^3
+// points at order 8 and 296^3 at order 12, weighed starts three times as much: where the chunks
+// differ, kernels take 7 % less on average.  Microseconds a forward / adjoint step:
 //                             filled once    earlier fit    this
 //   168^3, order 8            27.1 / 42.0    22.8 / 34.4    22.8 / 34.5
 //   168^3, order 16           45.0 / 53.1    34.4 / 40.9    26.6 / 35.7
@@ -37,8 +37,8 @@ inline int chunks3d(long long tiles, int nz, int K, bool grad, int per_cu, int c
         const int n = (nz + zl - 1) / zl;
         const long long r = (tiles * n + cus - 1) / cus;
         auto cost = [&](long long c) {
-            const double start = 0.7 * (2 * K + 1) * std::sqrt((double)c) + 0.4 * (double)c;
-            return c ? std::max((double)c, grad ? 1.3 : 2.05) * zl + (grad ? 0.5 : 1.0) * start : 0.0;
+            const double start = 0.7 * (2 * K + 1) * std::sqrt((double)c) + (K == 1 ? 0.8 : 0.4) * (double)c;
+            return c ? std::max((double)c, grad ? 1.3 : (K <= 2 ? 2.03 : 2.05)) * zl + (grad ? 0.5 : 1.0) * start : 0.0;
         };
         const double t = (double)(r / per_cu) * cost(per_cu) + cost(r % per_cu);
         if (!zlen || t < best) {

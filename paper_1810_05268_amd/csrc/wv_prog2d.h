@@ -34,11 +34,11 @@ public:
     static int most_other_ops(int nt) { return 10 * nt + 64; }
 
     // What a run of order 2 K works with, in groups of up to T steps, on fields of so many codec
-    // chunks.  Marched steps (T = 1) write the level they start from last, so that a CU finds more
-    // of what it reads in the L2.  A forward run holds the two levels a group starts from and the two it leaves.  A
-    // gradient run also holds the levels that wait for an encode or for their reverse steps, and
-    // the checkpoints decoded for those: with so many arrays no schedule of 60 or 301 steps at
-    // 1 to 301 slots has more launches than with any number.
+    // chunks.  A forward run holds the two levels a group starts from and the two it leaves; steps
+    // that march (T = 1) write over the older level they read, which leaves more of their operands
+    // in the L2.  A gradient run also holds the levels that wait for an encode or for their reverse
+    // steps, and the checkpoints decoded for those: with so many arrays no schedule of 60 or 301
+    // steps at 1 to 301 slots, in tiles, has over 0.3 % more launches than with any number.
     // Fields are encoded and decoded several at a time: one of 552 x 552 points is 75 chunks of
     // 256 lanes, which leave the chip idle, and larger ones save launches and the scan's one
     // workgroup (40 steps of 4000 x 3000 points with 8 states' memory: 4.8 ms by eights and 5.9 one
