@@ -773,8 +773,9 @@ size_t field_stream_max(const Setup &su)
     return codec_max_bytes(codec_dims(su.ndim, cdims, su.g.px)) + 256;
 }
 
-// nshots: shots of the batch the call is part of (1: a call of its own)
-Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int op, size_t budget, int nshots = 1)
+// batch: shots of the batch the call is part of (0: a call of its own).  A batch runs in tiles,
+// which cannot write over what they read, also if it is of one shot.
+Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int op, size_t budget, int batch = 0)
 {
     Layout L{};
     size_t off = 0;
@@ -791,9 +792,9 @@ Layout plan_layout(const wv_model *m, const wv_geom *geo, const Setup &su, int o
     if (prog) {
         const int K = su.g.K, nx = su.g.nx, nz = su.g.nz;
         const bool gradient = op == WV_OP_GRADIENT;
-        const bool march = nshots == 1 && tile2d_march(K, nx, nz, gradient ? kRunGradient : kRunForward);
-        L.rings = Prog2d::rings(K, march ? 1 : tile2d_choose(K, nx, nz, nshots), cd.nchunks, device_cus(), gradient,
-                                march);
+        const bool march = !batch && tile2d_march(K, nx, nz, gradient ? kRunGradient : kRunForward);
+        const int steps = march ? 1 : tile2d_choose(K, nx, nz, std::max(batch, 1));
+        L.rings = Prog2d::rings(K, steps, cd.nchunks, device_cus(), gradient, march);
     }
     const Rings2d &R = L.rings;
     L.fstride = align_up(fb, 256);
@@ -2038,7 +2039,7 @@ int batch_setup(int nshots, const wv_model *ms, const wv_geom *gs, size_t budget
     for (int i = 0; i < nshots; ++i) {
         lay = std::max(lay, L[i].total);
         // a batch that cannot run together runs each shot alone in its part
-        if (nshots > 1) lay = std::max(lay, plan_layout(&ms[i], &gs[i], su[i], WV_OP_GRADIENT, budget).total);
+        lay = std::max(lay, plan_layout(&ms[i], &gs[i], su[i], WV_OP_GRADIENT, budget).total);
     }
     B.chunk_off = align_up(lay, 256);
     B.shot_bytes = align_up(B.chunk_off + (size_t)L[0].rings.jobs * cd.nchunks * 4, 256);

@@ -81,6 +81,8 @@ hipError_t launch_tile2d(const Grid &g, const Tile2dArgs &A, hipStream_t s, Laun
             rc = launch_inject_res(g, A.inj, A.vals, A.w, A.out[0], A.uk[0], A.G, A.gscale, s);
         return rc;
     }
+    for (int j = 0; j < A.ns; ++j)   // a tile's neighbours read what it writes over
+        if (A.out[j] && (A.out[j] == A.u || A.out[j] == A.up)) return hipErrorInvalidValue;
     switch (g.K) {
     case 1: return launch_k<1>(g, A, s, ev);
     case 2: return launch_k<2>(g, A, s, ev);
@@ -98,6 +100,10 @@ hipError_t launch_batch_steps(const BatchArgs &A, const BatchOp &op, hipStream_t
 {
     if ((op.kind != kOpStep && op.kind != kOpAdj) || op.ns < 1 || op.ns > tile2d_steps(A.g.K))
         return hipErrorInvalidValue;
+    // a tile's neighbours read what it writes over
+    const int32_t *out = op.kind == kOpAdj ? op.d : op.c;
+    for (int j = 0; j < (op.kind == kOpAdj ? 2 : op.ns); ++j)
+        if (out[j] != kBufNone && (out[j] == op.a || out[j] == op.b)) return hipErrorInvalidValue;
     switch (A.g.K) {
     case 1: return launch_batch_k<1>(A, op, s);
     case 2: return launch_batch_k<2>(A, op, s);

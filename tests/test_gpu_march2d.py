@@ -52,6 +52,18 @@ def test_marched_gradient_injects_as_tiles(half, off):
         assert torch.equal(dsims[i], ds) and torch.equal(grads[i], g)
 
 
+def test_batch_of_one_runs_in_tiles():
+    """On a grid whose solo calls march, in place: the same bits."""
+    import torch
+    from tests.test_gpu_batch import _batch
+    devs, dobs, _ = _pair((1220, 1200), 12, 16, 6, 1, 4.0)
+    zero = torch.zeros_like(dobs[0])
+    budget = 4 * devs[0].slot_bytes
+    phi, g, _, ds = devs[0].misfit_gradient(zero, budget, 0.0, want_dsim=True)
+    phis, grads, dsims, _ = _batch(devs[:1], [zero], budget, 0.0, 0.0)
+    assert phis[0] == phi and torch.equal(dsims[0], ds) and torch.equal(grads[0], g)
+
+
 @pytest.mark.parametrize("n,order", [((60, 50), 4), ((960, 870), 4), ((760, 770), 16), ((350, 360), 16), ((901, 870), 8)])
 def test_adjoint_of_the_source(n, order):
     import torch
